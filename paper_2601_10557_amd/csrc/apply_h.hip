@@ -385,7 +385,9 @@ __device__ __forceinline__ void hx_tile(const ApplyHArgs<typename Tr::R>& a, int
       for (int r = 0; r < Tr::NACC; ++r) acc[i][j][r] = R(0);
 
   const int ak = Tr::a_k(lane), arow = Tr::a_row(lane), bcol = Tr::acc_col(lane);
-  const int live = (N - (n0 + wn0) + Tr::NB - 1) / Tr::NB;  // wave-uniform
+  // live column blocks of this wave (wave-uniform): none when the last tile
+  // ends before the wave's columns; the wave still copies and joins barriers
+  const int live = max(0, (N - (n0 + wn0) + Tr::NB - 1) / Tr::NB);
 
   constexpr int PRE = NST - 1;
   if (nsl > 0) {

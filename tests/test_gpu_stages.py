@@ -107,6 +107,21 @@ def test_apply_h_fp64_every_tile_plan(prob, solver, plan, k, monkeypatch):
     assert np.max(np.abs(Y - ref)) <= 1e-12 * np.max(np.abs(ref))
 
 
+# K-real columns whose last 128-wide tile ends before the columns of the
+# second wave (1 to 33 of them; the first forced plan is that tile), and the
+# same for the 64-wide tile (1 column past it)
+@pytest.mark.parametrize("k,plan", [(129, "0,1"), (130, "0,3"), (161, "0,1"), (129, "1,1"), (129, "1,4")])
+def test_apply_h_fp64_kreal_short_last_tile(prob, solver80, k, plan, monkeypatch):
+    print_case("apply_h_fp64_kreal_short_tile", m=prob.m, k=k, plan=plan)
+    monkeypatch.setenv("CHASE_PH_APPLY_PLAN", plan)
+    rng = np.random.default_rng(600 + k)
+    a = complex_normal(rng, (prob.m, k))
+    X = np.concatenate([a, a.conj()], axis=0)
+    Y = to_host(solver80.apply_h(to_dev(X), prec=_lib.FP64_KREAL))
+    ref = ham.apply_h(prob.A, prob.B, X)
+    assert np.max(np.abs(Y - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
 # 2k a few columns past a multiple of 128 (k % 64 <= 20; k >= 64): the
 # library splits the launch by columns, in one launch (c64 with 64 < k <= 80:
 # one column of wide tiles instead)
