@@ -15,6 +15,7 @@
 #include "common.h"
 #include "dense.h"
 #include "geev.h"
+#include "hx.h"
 #include "vec.h"
 
 using namespace chase;
@@ -27,23 +28,24 @@ struct chase_ph_s {
   hipStream_t st = nullptr;
   int64_t m = 0, n = 0;
   int nevex = 0, kmax = 0, kp = 0;
-  // D = [A + B, i (A - B)] column-interleaved (m x 2m, ldd): the real
-  // operand of every H X product, in c128 (D64) and, for the mixed / FP32
-  // filter, in c64 (D32)
-  c128* D64 = nullptr;
+  // the real operand of every H X product: M64 (hx.h) of the c128 products,
+  // D32 = [A + B, i (A - B)] column-interleaved (m x 2m, ldd) of the c64 ones
+  double* M64 = nullptr;
   c64* D32 = nullptr;
   int64_t ldd = 0;
-  bool d64_ready = false;
+  bool m64_ready = false;
   bool shadow_ready = false;
-  // packed real coordinates of the H X operand (k-pair layout: yrows row
-  // pairs of ldyr reals, in doubles; the c64 path uses it as floats)
+  // packed operand of the products on complex columns (X4 for c128, the
+  // k-pair layout of yrows row pairs of ldyr reals for c64); calls with more
+  // than kcap columns run in chunks
   double* Yr = nullptr;
   int64_t ldyr = 0;
-  int kcap = 0;    // columns the packed buffer holds (calls with more run in chunks)
+  int kcap = 0;
   int64_t yrows = 0;
-  // filter work buffers (n x nevex)
-  c128* F1 = nullptr;
-  c128* FT = nullptr;
+  // c128 filter state in X4, 2 nevex real columns of pitch xld: even and odd
+  // degrees and the product in between; c64 filter work buffers (n x nevex)
+  int64_t xld = 0;
+  double* X64[3] = {};
   c64* W32 = nullptr;
   c64* F1_32 = nullptr;
   c64* FT_32 = nullptr;
@@ -86,6 +88,7 @@ struct chase_ph_s {
   double* dab = nullptr;  // 2 * steps * vecs
   void* ws = nullptr;
   size_t ws_bytes = 0;
+  size_t ws32_bytes = 0;  // part of it that the c64 products plan with
   DenseWs dws;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   double last_ms = 0;
@@ -165,11 +168,20 @@ Err gemm(chase_ph_t h, int ta, int tb, int64_t M, int64_t N, int64_t K, c128 alp
   return zgemm(g, split ? h->ws : nullptr, split ? h->ws_bytes : 0, h->st);
 }
 
+// Block of 2 nevex real columns in X4, all zero: the products write the live
+// rows only, the pad rows stay zero.
+Err alloc_x4(chase_ph_t h, double** p) {
+  const size_t reals = (size_t)hx_block_reals(h->m, 2 * (int64_t)h->nevex);
+  CHASE_TRY(dalloc(h, p, reals));
+  CHASE_HIP(hipMemsetAsync(*p, 0, reals * sizeof(double), h->st));
+  return ok();
+}
+
 // D in c64 and the mixed path's work buffers.  alloc_shadow only
 // allocates; ensure_shadow also builds D32 the first time a stage call
 // needs it; the solver builds it again inside every timed solve
-// (refresh_shadow), so a solve's time includes the conversion.  D64 is
-// allocated at create and built the same way (refresh_d64, on first use and
+// (refresh_shadow), so a solve's time includes the conversion.  M64 is
+// allocated at create and built the same way (refresh_m64, on first use and
 // inside every solve).
 Err alloc_shadow(chase_ph_t h) {
   if (h->D32) return ok();
@@ -197,9 +209,9 @@ Err ensure_shadow(chase_ph_t h) {
   return refresh_shadow(h);
 }
 
-Err refresh_d64(chase_ph_t h) {
-  CHASE_TRY(make_d<c128>(h->A, h->p.tda ? nullptr : h->B, h->ld, h->p.a_conj, h->D64, h->ldd, h->m, h->st));
-  h->d64_ready = true;
+Err refresh_m64(chase_ph_t h) {
+  CHASE_TRY(hx_make_operand(h->A, h->p.tda ? nullptr : h->B, h->ld, h->p.a_conj, h->M64, h->m, h->st));
+  h->m64_ready = true;
   return ok();
 }
 
@@ -236,26 +248,25 @@ Err prof_end(chase_ph_t h, int prec, int k, size_t elem, bool has_p, bool has_q,
   return ok();
 }
 
-// Y = alpha H X + beta P + gamma Q on k columns
-Err apply64(chase_ph_t h, int k, const c128* X, int64_t ldx, c128* Y, int64_t ldy, double alpha = 1,
-            const c128* P = nullptr, int64_t ldp = 0, double beta = 0, const c128* Q = nullptr, int64_t ldq = 0,
-            double gamma = 0, int kreal = 0) {
-  ApplyHArgs<double> a{};
-  a.D = h->D64; a.ldd = h->ldd; a.m = h->m; a.k = k;
-  a.yr = h->Yr; a.ldyr = h->ldyr; a.yrows = h->yrows; a.kcap = h->kcap;
-  if (k > 0 && !h->d64_ready) CHASE_TRY(refresh_d64(h));
-  a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy; a.P = P; a.ldp = ldp; a.Q = Q; a.ldq = ldq;
-  a.alpha = alpha; a.beta = beta; a.gamma = gamma; a.kreal = kreal; a.tda = h->p.tda;
+// Y = H X (TDA handle: A X) on k complex columns
+Err apply64(chase_ph_t h, int k, const c128* X, int64_t ldx, c128* Y, int64_t ldy, int kreal = 0) {
   if (k <= 0) return ok();
+  if (!h->m64_ready) CHASE_TRY(refresh_m64(h));
+  HxApply a;
+  a.M = h->M64; a.m = h->m; a.k = k;
+  a.kind = h->p.tda ? HX_TDA : kreal ? HX_KREAL : HX_GENERAL;
+  a.X = X; a.ldx = ldx; a.Y = Y; a.ldy = ldy;
+  a.yr = h->Yr; a.kcap = h->kcap;
   CHASE_TRY(prof_begin(h));
-  CHASE_TRY(launch_apply_h_f64(a, h->ws, h->ws_bytes, h->st));
-  return prof_end(h, CHASE_PH_FP64, k, sizeof(c128), P != nullptr, Q != nullptr, kreal != 0 || h->p.tda);
+  CHASE_TRY(hx_apply(a, h->ws, h->ws_bytes, h->st));
+  return prof_end(h, CHASE_PH_FP64, k, sizeof(c128), false, false, kreal != 0 || h->p.tda);
 }
 
+// Y = alpha H X + beta P + gamma Q + diag(dcol) S on k columns
 Err apply32(chase_ph_t h, int k, const c64* X, int64_t ldx, c64* Y, int64_t ldy, float alpha = 1,
             const c64* P = nullptr, int64_t ldp = 0, float beta = 0, const c64* Q = nullptr, int64_t ldq = 0,
             float gamma = 0, const c64* S = nullptr, int64_t lds = 0, const float* dcol = nullptr) {
-  ApplyHArgs<float> a{};
+  ApplyHArgs a{};
   a.D = h->D32; a.ldd = h->ldd; a.m = h->m; a.k = k;
   a.yr = reinterpret_cast<float*>(h->Yr); a.ldyr = h->ldyr; a.yrows = h->yrows; a.kcap = h->kcap;
   if (k > 0 && !h->shadow_ready) CHASE_TRY(refresh_shadow(h));
@@ -265,17 +276,74 @@ Err apply32(chase_ph_t h, int k, const c64* X, int64_t ldx, c64* Y, int64_t ldy,
   a.S = S; a.lds = lds; a.dcol = dcol; a.tda = h->p.tda;
   if (k <= 0) return ok();
   CHASE_TRY(prof_begin(h));
-  CHASE_TRY(launch_apply_h_f32(a, h->ws, h->ws_bytes, h->st));
+  CHASE_TRY(launch_apply_h_f32(a, h->ws, h->ws32_bytes, h->st));
   return prof_end(h, CHASE_PH_FP32, k, sizeof(c64), P != nullptr, Q != nullptr, h->p.tda != 0);
 }
 
+// One c128 product of a filter on k columns held in X4 (two real columns
+// each, one on a TDA handle).
+Err step64(chase_ph_t h, int k, const double* y, double* out, int rot, double alpha = 1, const double* P = nullptr,
+           double beta = 0, const double* Q = nullptr, double gamma = 0) {
+  if (!h->m64_ready) CHASE_TRY(refresh_m64(h));
+  HxStep a;
+  a.M = h->M64; a.m = h->m; a.ldc = h->xld; a.N = h->p.tda ? k : 2 * k;
+  a.y = y; a.out = out; a.P = P; a.Q = Q;
+  a.alpha = alpha; a.beta = beta; a.gamma = gamma; a.rot = rot;
+  CHASE_TRY(prof_begin(h));
+  CHASE_TRY(hx_step(a, h->ws, h->ws_bytes, h->st));
+  return prof_end(h, CHASE_PH_FP64, k, sizeof(c128), P != nullptr, Q != nullptr, h->p.tda != 0);
+}
+
 // Scaled Chebyshev recurrence on H^2 (eq. 4.1, Zhou-Saad scaling); see
-// chase_ph_filter.  Buffers: W (user, ldw), F1 and FT (ld n).  W_s lives in
+// chase_ph_filter.  The block is packed once and stays in X4 until the
+// columns' degrees are done: W_s in X[s % 2] (the second product of each
+// degree writes W_s in place over W_{s-2}), the product in between in X[2].
+Err filter64(chase_ph_t h, int k, c128* W, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
+             double mu_n, int* launches, double* flops) {
+  double* const (&X)[3] = h->X64;
+  const double c = 0.5 * (mu_n * mu_n + mu_nevex * mu_nevex);
+  const double e = 0.5 * (mu_n * mu_n - mu_nevex * mu_nevex);
+  const double sigma1 = e / (mu1 * mu1 - c);
+  double sigma = sigma1;
+  const int maxd = d[k - 1];
+  CHASE_TRY(hx_pack(W, ldw, h->m, k, HX_GENERAL, X[0], h->xld, h->st));
+  int j0 = 0;
+  for (int s = 1; s <= maxd; ++s) {
+    while (j0 < k && d[j0] < s) ++j0;
+    const int kc = k - j0;
+    const int64_t off = 8 * (int64_t)j0;  // two quads per column
+    const double* cur = X[(s - 1) % 2] + off;
+    double* next = X[s % 2] + off;
+    CHASE_TRY(step64(h, kc, cur, X[2] + off, HX_I));
+    if (s == 1) {
+      CHASE_TRY(step64(h, kc, X[2] + off, next, HX_MINUS_I, sigma1 / e, cur, -sigma1 * c / e));
+    } else {
+      const double sn = 1.0 / (2.0 / sigma1 - sigma);
+      CHASE_TRY(step64(h, kc, X[2] + off, next, HX_MINUS_I, 2.0 * sn / e, cur, -2.0 * sn * c / e, next,
+                           -sigma * sn));
+      sigma = sn;
+    }
+    *launches += 2;
+    *flops += 2 * hx_flops((double)h->n, kc, false);
+  }
+  // columns of even degree ended in X[0], of odd degree in X[1]
+  for (int j = 0; j < k;) {
+    int j2 = j;
+    while (j2 < k && d[j2] % 2 == d[j] % 2) ++j2;
+    CHASE_TRY(hx_unpack(X[d[j] % 2] + 8 * (int64_t)j, h->xld, h->m, j2 - j, HX_GENERAL, W + (int64_t)j * ldw, ldw,
+                        h->st));
+    j = j2;
+  }
+  return ok();
+}
+
+// The same recurrence with c64 products.  Buffers: W (user, ldw), F1 and FT (ld n).  W_s lives in
 // W for even s and in F1 for odd s; the second product of each degree
 // writes W_{s} in place over W_{s-2}.
-template <typename R, typename C>
-Err filter_impl(chase_ph_t h, int k, C* W, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
-                double mu_n, C* F1, C* FT, int* launches, double* flops) {
+Err filter32(chase_ph_t h, int k, c64* W, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
+             double mu_n, int* launches, double* flops) {
+  using C = c64;
+  C *F1 = h->F1_32, *FT = h->FT_32;
   const int64_t n = h->n;
   const double c = 0.5 * (mu_n * mu_n + mu_nevex * mu_nevex);
   const double e = 0.5 * (mu_n * mu_n - mu_nevex * mu_nevex);
@@ -287,10 +355,7 @@ Err filter_impl(chase_ph_t h, int k, C* W, int64_t ldw, const std::vector<int>& 
                  const C* Q, int64_t ldq, double ga) -> Err {
     ++*launches;
     *flops += hx_flops((double)n, kc, false);
-    if constexpr (sizeof(R) == 4)
-      return apply32(h, kc, X, ldx, Y, ldy, (float)al, P, ldp, (float)be, Q, ldq, (float)ga);
-    else
-      return apply64(h, kc, X, ldx, Y, ldy, al, P, ldp, be, Q, ldq, ga);
+    return apply32(h, kc, X, ldx, Y, ldy, (float)al, P, ldp, (float)be, Q, ldq, (float)ga);
   };
   for (int s = 1; s <= maxd; ++s) {
     while (j0 < k && d[j0] < s) ++j0;
@@ -430,9 +495,9 @@ Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int
   CHASE_HIP(hipEventRecord(h->e0, h->st));
   if (prec == CHASE_PH_FP32) {
     CHASE_TRY(ensure_shadow(h));
-    CHASE_TRY((filter_impl<float, c64>(h, k, (c64*)dW, ldw, d, mu1, mu_nevex, mu_n, h->F1_32, h->FT_32, &launches, &fl)));
+    CHASE_TRY(filter32(h, k, (c64*)dW, ldw, d, mu1, mu_nevex, mu_n, &launches, &fl));
   } else {
-    CHASE_TRY((filter_impl<double, c128>(h, k, (c128*)dW, ldw, d, mu1, mu_nevex, mu_n, h->F1, h->FT, &launches, &fl)));
+    CHASE_TRY(filter64(h, k, (c128*)dW, ldw, d, mu1, mu_nevex, mu_n, &launches, &fl));
   }
   CHASE_HIP(hipEventRecord(h->e1, h->st));
   CHASE_HIP(hipEventSynchronize(h->e1));
@@ -653,7 +718,7 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
             int64_t ldt, bool kreal_q = false, int backup = -1, bool* used_backup = nullptr) {
   const int kp = pad64(k);
   const int64_t m = h->m, n = h->n;
-  CHASE_TRY(apply64(h, k, Q, ldq, T, ldt, 1, nullptr, 0, 0, nullptr, 0, 0, kreal_q ? 1 : 0));  // T = H Q
+  CHASE_TRY(apply64(h, k, Q, ldq, T, ldt, kreal_q ? 1 : 0));  // T = H Q
   if (kreal_q) {
     CHASE_TRY(pair_mix(const_cast<c128*>(Q), ldq, n, k / 2, h->st));
     CHASE_TRY(pair_mix(T, ldt, n, k / 2, h->st));  // = H (Q after the mix)
@@ -990,30 +1055,24 @@ std::vector<int> tda_nex_candidates(int nex_max) {
 // eq. 2.1 on [mu_nevex, mu_m], normalised at mu_1,
 //   W_1 = (sigma_1 / e)(A - c) W_0,
 //   W_{s+1} = (2 sigma_{s+1} / e)(A - c) W_s - sigma_s sigma_{s+1} W_{s-1},
-// one H X call (TDA mode) per degree with the update fused; W_s alternates
-// between W and F1 (ld m).
+// one product per degree with the update fused, on real coordinates in X4
+// from the first to the last (W_s in X[s % 2], over W_{s-2}).
 Err filter_tda(chase_ph_t h, int k, c128* W, int64_t ldw, int deg, double mu1, double mu_nevex, double mu_m,
                double* flops) {
   if (k == 0) return ok();
-  const int64_t m = h->m;
   const double c = 0.5 * (mu_m + mu_nevex), e = 0.5 * (mu_m - mu_nevex);
   const double s1 = e / (mu1 - c);
-  c128* cur = h->F1;
-  int64_t ldc = m;
-  c128* prev = W;
-  int64_t ldp = ldw;
-  CHASE_TRY(apply64(h, k, W, ldw, h->F1, m, s1 / e, W, ldw, -s1 * c / e));
+  double* const (&X)[3] = h->X64;
+  CHASE_TRY(hx_pack(W, ldw, h->m, k, HX_TDA, X[0], h->xld, h->st));
+  CHASE_TRY(step64(h, k, X[0], X[1], HX_NONE, s1 / e, X[0], -s1 * c / e));
   double sigma = s1;
   for (int s = 1; s < deg; ++s) {
     const double sn = 1.0 / (2.0 / s1 - sigma);
-    CHASE_TRY(apply64(h, k, cur, ldc, prev, ldp, 2.0 * sn / e, cur, ldc, -2.0 * sn * c / e, prev, ldp, -sigma * sn));
-    std::swap(cur, prev);
-    std::swap(ldc, ldp);
+    double *cur = X[s % 2], *next = X[(s + 1) % 2];
+    CHASE_TRY(step64(h, k, cur, next, HX_NONE, 2.0 * sn / e, cur, -2.0 * sn * c / e, next, -sigma * sn));
     sigma = sn;
   }
-  if (cur != W)
-    CHASE_HIP(hipMemcpy2DAsync(W, ldw * sizeof(c128), cur, ldc * sizeof(c128), m * sizeof(c128), k,
-                               hipMemcpyDeviceToDevice, h->st));
+  CHASE_TRY(hx_unpack(X[deg % 2], h->xld, h->m, k, HX_TDA, W, ldw, h->st));
   *flops += deg * hx_flops((double)h->n, k, true);
   return ok();
 }
@@ -1063,7 +1122,7 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
   CHASE_HIP(hipEventCreate(&t1));
   CHASE_HIP(hipEventRecord(t0, h->st));
 
-  CHASE_TRY(refresh_d64(h));  // the real operand D of every c128 H X product, inside the timed solve
+  CHASE_TRY(refresh_m64(h));  // the real operand of every c128 H X product, inside the timed solve
   CHASE_TRY(scale_lower_half(W0, ldw0, h->Wk, n, m, nevex, p.gamma, h->st));  // Alg. 3, line 1 / Section 4.6
   double mu1, mu_nevex, mu_n;
   CHASE_TRY(tm.start());
@@ -1387,7 +1446,7 @@ Err solve_tda_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, i
   CHASE_HIP(hipEventCreate(&t0));
   CHASE_HIP(hipEventCreate(&t1));
   CHASE_HIP(hipEventRecord(t0, h->st));
-  CHASE_TRY(refresh_d64(h));  // D = [A, i A], inside the timed solve
+  CHASE_TRY(refresh_m64(h));  // the real form of A, inside the timed solve
 
   CHASE_TRY(tm.start());
   TdaDensity dens;
@@ -1542,14 +1601,14 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   const size_t kp2 = (size_t)h->kp * h->kp;
   CHASE_HIP(hipEventCreate(&h->e0));
   CHASE_HIP(hipEventCreate(&h->e1));
-  h->ldd = (h->m + 63) / 64 * 64;
-  CHASE_TRY(dalloc(h, &h->D64, (size_t)h->ldd * 2 * h->m));
+  CHASE_TRY(dalloc(h, &h->M64, (size_t)hx_operand_reals(h->m)));
   h->kcap = std::max(h->kmax, 512);
+  h->ldd = (h->m + 63) / 64 * 64;
   h->ldyr = 4 * (int64_t)h->kcap + 8;
   h->yrows = (h->m + 31) / 32 * 32;
-  CHASE_TRY(dalloc(h, &h->Yr, (size_t)h->ldyr * h->yrows));
-  CHASE_TRY(dalloc(h, &h->F1, (size_t)n * h->nevex));
-  CHASE_TRY(dalloc(h, &h->FT, (size_t)n * h->nevex));
+  CHASE_TRY(dalloc(h, &h->Yr, (size_t)std::max(hx_block_reals(h->m, 2 * (int64_t)h->kcap), h->ldyr * h->yrows)));
+  h->xld = hx_ldc(2 * (int64_t)h->nevex);
+  for (double*& x : h->X64) CHASE_TRY(alloc_x4(h, &x));
   CHASE_TRY(dalloc(h, &h->Xs, (size_t)n * h->kmax));
   CHASE_TRY(dalloc(h, &h->Xt, (size_t)n * h->kmax));
   CHASE_TRY(dalloc(h, &h->Tq, (size_t)n * h->kmax));
@@ -1602,10 +1661,13 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   // counts, Ritz values, residuals: at most kmax doubles)
   h->dws.hpin_bytes = std::max<size_t>(4096, sizeof(double) * (size_t)h->kmax);
   CHASE_HIP(hipHostMalloc(&h->dws.hpin, h->dws.hpin_bytes, hipHostMallocDefault));
-  // zgemm split-K partials (up to 8 k x k blocks) and apply_h split-K
-  // partials (up to 8 x m x 2 nevex complex), within [16 MiB, 1 GiB]
+  // zgemm split-K partials (up to 8 k x k blocks) and the partial tiles of
+  // the H X products (two per workgroup: 128 MiB when all 512 take part,
+  // which small m never do), within [16 MiB, 1 GiB]
   h->ws_bytes = std::max(kp2 * sizeof(c128) * 8, (size_t)8 * h->m * h->kmax * sizeof(c128));
   h->ws_bytes = std::min<size_t>((size_t)1 << 30, std::max<size_t>((size_t)16 << 20, h->ws_bytes));
+  h->ws32_bytes = h->ws_bytes;
+  h->ws_bytes = std::max(h->ws_bytes, std::min<size_t>((size_t)128 << 20, (size_t)h->m << 16));
   CHASE_TRY(dalloc(h, (char**)&h->ws, h->ws_bytes));
   h->dws.gemm_ws = h->ws;
   h->dws.gemm_ws_bytes = h->ws_bytes;
@@ -1709,8 +1771,7 @@ chase_ph_status chase_ph_apply_h(chase_ph_t h, int32_t k, const void* dX, int64_
     e = ensure_shadow(h);
     if (!e) e = apply32(h, k, (const c64*)dX, ldx, (c64*)dY, ldy);
   } else {
-    e = apply64(h, k, (const c128*)dX, ldx, (c128*)dY, ldy, 1, nullptr, 0, 0, nullptr, 0, 0,
-                prec == CHASE_PH_FP64_KREAL ? 1 : 0);
+    e = apply64(h, k, (const c128*)dX, ldx, (c128*)dY, ldy, prec == CHASE_PH_FP64_KREAL ? 1 : 0);
   }
   if (e) return finish(h, e);
   float ms = 0;

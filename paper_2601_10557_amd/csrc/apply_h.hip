@@ -47,14 +47,15 @@
 namespace chase {
 namespace {
 
+using R = float;
+using C = c64;
+
 // MFMA shapes.  phys_row(r, l): the real row (within a fragment of MB rows)
 // of accumulator r of lane l; the accumulators 2t, 2t + 1 hold the real rows
 // 2i, 2i + 1 of one complex row i.  a_row(l): the fragment row whose A
 // operand lane l supplies (a permutation for the f64 shape, so that the
 // output rows land as stated).
 struct TF32 {  // v_mfma_f32_32x32x2f32
-  using R = float;
-  using C = c64;
   using Acc = floatx16;
   static constexpr int MB = 32, NB = 32, KB = 2, NACC = 16;
   __device__ static int a_row(int l) { return l & 31; }
@@ -65,8 +66,6 @@ struct TF32 {  // v_mfma_f32_32x32x2f32
 };
 
 struct TF32S {  // v_mfma_f32_16x16x4f32: narrow launches
-  using R = float;
-  using C = c64;
   using Acc = floatx4;
   static constexpr int MB = 16, NB = 16, KB = 4, NACC = 4;
   __device__ static int a_row(int l) { return l & 15; }
@@ -74,22 +73,6 @@ struct TF32S {  // v_mfma_f32_16x16x4f32: narrow launches
   __device__ static int phys_row(int r, int l) { return 4 * (l >> 4) + r; }
   __device__ static int acc_col(int l) { return l & 15; }
   __device__ static Acc mfma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-};
-
-struct TF64 {  // v_mfma_f64_16x16x4f64
-  using R = double;
-  using C = c128;
-  using Acc = doublex4;
-  static constexpr int MB = 16, NB = 16, KB = 4, NACC = 4;
-  // output row rho = (l >> 4) + 4 r of the MFMA is fed from real row
-  // pi(rho) = 8 (r >> 1) + 2 (l >> 4) + (r & 1), so accumulators 0, 1 and 2, 3
-  // of a lane are the real rows 2q, 2q + 1 and 8 + 2q, 9 + 2q (q = l >> 4)
-  __device__ static int pi(int rho) { return 8 * ((rho >> 2) >> 1) + 2 * (rho & 3) + ((rho >> 2) & 1); }
-  __device__ static int a_row(int l) { return pi(l & 15); }
-  __device__ static int a_k(int l) { return l >> 4; }
-  __device__ static int phys_row(int r, int l) { return pi((l >> 4) + 4 * r); }
-  __device__ static int acc_col(int l) { return l & 15; }
-  __device__ static Acc mfma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 };
 
 // f(integral_constant<B>) ... f(integral_constant<E - 1>)
@@ -111,8 +94,7 @@ __device__ __forceinline__ int xcd_remap(int w, int T) {
 
 // Y[orow, ocol] = alpha h + beta P + gamma Q + dcol S (each read before the
 // write, so Y may alias P or Q)
-template <typename R, typename C>
-__device__ __forceinline__ void store_hx(const ApplyHArgs<R>& a, int64_t orow, int ocol, R hr, R hi) {
+__device__ __forceinline__ void store_hx(const ApplyHArgs& a, int64_t orow, int ocol, R hr, R hi) {
   R yr = a.alpha * hr, yi = a.alpha * hi;
   if (a.P) {
     const C p = a.P[(int64_t)ocol * a.ldp + orow];
@@ -139,28 +121,21 @@ __device__ __forceinline__ void store_hx(const ApplyHArgs<R>& a, int64_t orow, i
 // Epilogue of complex row ci for real column col: (tr, ti) is t of this
 // column (K-real: column col of X; otherwise u_j for even col, v_j for odd)
 // and (pr, pi_) t of the other column of the pair.
-template <typename R, typename C>
-__device__ __forceinline__ void finish_pair(const ApplyHArgs<R>& a, int64_t ci, int col, R tr, R ti, R pr, R pi_) {
+__device__ __forceinline__ void finish_pair(const ApplyHArgs& a, int64_t ci, int col, R tr, R ti, R pr, R pi_) {
   const int64_t m = a.m;
   if (a.tda) {
-    store_hx<R, C>(a, ci, col, tr, ti);        // A x
-    return;
-  }
-  if (a.kreal) {
-    store_hx<R, C>(a, ci, col, tr, ti);        // t
-    store_hx<R, C>(a, ci + m, col, -tr, ti);   // -conj(t)
+    store_hx(a, ci, col, tr, ti);        // A x
     return;
   }
   const int odd = col & 1;
   const R ur = odd ? pr : tr, ui = odd ? pi_ : ti, vr = odd ? tr : pr, vi = odd ? ti : pi_;
   if (!odd)
-    store_hx<R, C>(a, ci, col >> 1, ur - vi, ui + vr);        // t_u + i t_v
+    store_hx(a, ci, col >> 1, ur - vi, ui + vr);        // t_u + i t_v
   else
-    store_hx<R, C>(a, ci + m, col >> 1, -ur - vi, ui - vr);   // -conj(t_u) - i conj(t_v)
+    store_hx(a, ci + m, col >> 1, -ur - vi, ui - vr);   // -conj(t_u) - i conj(t_v)
 }
 
 __device__ __forceinline__ float shfl1(float v) { return __shfl_xor(v, 1); }
-__device__ __forceinline__ double shfl1(double v) { return __shfl_xor(v, 1); }
 
 // ---------------------------------------------------------------- pack
 // Yp (k-pair layout, ldyr reals per row pair, rows >= m zero):
@@ -169,7 +144,6 @@ __device__ __forceinline__ double shfl1(double v) { return __shfl_xor(v, 1); }
 //  K-real:  real column j = coordinates of the top half of x_j (column k,
 //           when k is odd, is zero); the same for the m-row x_j of a TDA
 //           product.
-template <typename R, typename C>
 __global__ __launch_bounds__(256) void pack_kernel(const C* X, int64_t ldx, int64_t m, int k, int kreal, R* Y,
                                                    int64_t ldyr, int64_t rows) {
   // A tile of 64 row pairs p and TJ columns j goes through LDS: the reads
@@ -254,7 +228,6 @@ __device__ __forceinline__ void ring_barrier() {
 
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN>
 struct Cfg {
-  using R = typename Tr::R;
   static constexpr int V = 16 / (int)sizeof(R);          // reals per 16-byte copy
   static constexpr int WTM = BM / WGM, WTN = BN / WGN;   // wave tile
   static constexpr int FM = WTM / Tr::MB, FN = WTN / Tr::NB;
@@ -309,18 +282,16 @@ __device__ __forceinline__ void step_schedule() {
 // product (T tiles, K split `splits` ways, kps slabs each), on the LDS ring
 // at lds (NST stages of the M tile, then NST stages of the Y tile).
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED>
-__device__ __forceinline__ void hx_tile(const ApplyHArgs<typename Tr::R>& a, int splits, int kps,
-                                        typename Tr::R* ws, int bid, typename Tr::R* lds) {
+__device__ __forceinline__ void hx_tile(const ApplyHArgs& a, int splits, int kps,
+                                        R* ws, int bid, R* lds) {
   using CF = Cfg<Tr, BM, BN, BK, NST, WGM, WGN>;
-  using R = typename Tr::R;
-  using C = typename Tr::C;
   constexpr int V = CF::V, FM = CF::FM, FN = CF::FN, BNP = CF::BNP, SA = CF::SA;
   R (*As)[CF::ASTAGE] = reinterpret_cast<R (*)[CF::ASTAGE]>(lds);
   R (*Bs)[CF::BSTAGE] = reinterpret_cast<R (*)[CF::BSTAGE]>(lds + NST * CF::ASTAGE);
 
   const int64_t m = a.m;
   const int M2 = (int)(2 * m);                       // real rows and K
-  const int N = (a.kreal || a.tda) ? a.k : 2 * a.k;  // real columns
+  const int N = a.tda ? a.k : 2 * a.k;  // real columns
   const int Npad = (N + 1) / 2 * 2;                  // packed columns
   const int TM = (M2 + BM - 1) / BM;
   const int TN = (N + BN - 1) / BN;
@@ -425,12 +396,12 @@ __device__ __forceinline__ void hx_tile(const ApplyHArgs<typename Tr::R>& a, int
           // barrier part meanwhile (c64 calls 2.5-5% faster on m = 4000,
           // k = 64..260; the f64 tiles, scheduled by sched_group_barrier,
           // were 5-7% slower with it)
-          if constexpr (sizeof(R) == 4) __builtin_amdgcn_s_setprio(1);
+          __builtin_amdgcn_s_setprio(1);
 #pragma unroll
           for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < NL; ++j) acc[i][j] = Tr::mfma(fa[b][i], fb[b][j], acc[i][j]);
-          if constexpr (sizeof(R) == 4) __builtin_amdgcn_s_setprio(0);
+          __builtin_amdgcn_s_setprio(0);
           step_schedule<SCHED>();
         }
       }
@@ -463,16 +434,15 @@ __device__ __forceinline__ void hx_tile(const ApplyHArgs<typename Tr::R>& a, int
           }
         } else {
           const R pr = shfl1(tr), pi_ = shfl1(ti);
-          if (row < M2 && col < N) finish_pair<R, C>(a, row >> 1, col, tr, ti, pr, pi_);
+          if (row < M2 && col < N) finish_pair(a, row >> 1, col, tr, ti, pr, pi_);
         }
       }
 }
 
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void hx_kernel(
-    const ApplyHArgs<typename Tr::R> a, int splits, int kps, typename Tr::R* ws) {
+    const ApplyHArgs a, int splits, int kps, R* ws) {
   using CF = Cfg<Tr, BM, BN, BK, NST, WGM, WGN>;
-  using R = typename Tr::R;
   __shared__ __attribute__((aligned(16))) R lds[CF::LDS / sizeof(R)];
   hx_tile<Tr, BM, BN, BK, NST, WGM, WGN, SCHED>(a, splits, kps, ws, blockIdx.x, lds);
 }
@@ -488,10 +458,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED, int BMR, int BNR, int BKR,
           int NSTR, int WGMR, int WGNR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void hx_pair_kernel(
-    const ApplyHArgs<typename Tr::R> am, int splits_m, int kps_m, typename Tr::R* ws_m,
-    const ApplyHArgs<typename Tr::R> ar, int splits_r, int kps_r, typename Tr::R* ws_r, int nrem, int nrem_live,
+    const ApplyHArgs am, int splits_m, int kps_m, R* ws_m,
+    const ApplyHArgs ar, int splits_r, int kps_r, R* ws_r, int nrem, int nrem_live,
     int nmain, int nmain_live) {
-  using R = typename Tr::R;
   constexpr size_t LM = Cfg<Tr, BM, BN, BK, NST, WGM, WGN>::LDS;
   constexpr size_t LR = Cfg<Tr, BMR, BNR, BKR, NSTR, WGMR, WGNR>::LDS;
   __shared__ __attribute__((aligned(16))) R lds[(LM > LR ? LM : LR) / sizeof(R)];
@@ -508,23 +477,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // Sum the split-K partials in a fixed order and apply the epilogue: one
 // thread per complex row i and X column j.
-template <typename R, typename C>
-__global__ void hx_reduce(const ApplyHArgs<R> a, int splits, const R* ws) {
+__global__ void hx_reduce(const ApplyHArgs a, int splits, const R* ws) {
   const int64_t m = a.m, M2 = 2 * m;
-  const int N = (a.kreal || a.tda) ? a.k : 2 * a.k;
+  const int N = a.tda ? a.k : 2 * a.k;
   const int64_t total = m * a.k;
   const int64_t split_stride = M2 * N;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(t / m);
     const int64_t i = t % m;
-    if (a.kreal || a.tda) {
+    if (a.tda) {
       R tr = 0, ti = 0;
       for (int s = 0; s < splits; ++s) {
         const R* w = ws + s * split_stride + (int64_t)j * M2 + 2 * i;
         tr += w[0];
         ti += w[1];
       }
-      finish_pair<R, C>(a, i, j, tr, ti, R(0), R(0));
+      finish_pair(a, i, j, tr, ti, R(0), R(0));
       continue;
     }
     R ur = 0, ui = 0, vr = 0, vi = 0;
@@ -535,8 +503,8 @@ __global__ void hx_reduce(const ApplyHArgs<R> a, int splits, const R* ws) {
       vr += w[M2];
       vi += w[M2 + 1];
     }
-    finish_pair<R, C>(a, i, 2 * j, ur, ui, vr, vi);
-    finish_pair<R, C>(a, i, 2 * j + 1, vr, vi, ur, ui);
+    finish_pair(a, i, 2 * j, ur, ui, vr, vi);
+    finish_pair(a, i, 2 * j + 1, vr, vi, ur, ui);
   }
 }
 
@@ -594,34 +562,29 @@ void plan_override(Plan& p, int64_t m2, int64_t n2, const int (&bm)[NCFG], const
   p.tiles = ceil_div(m2, bm[c]) * ceil_div(n2, bn[c]);
 }
 
-template <typename R, typename C>
-Err launch_reduce(const ApplyHArgs<R>& a, int splits, const R* ws, hipStream_t s) {
+Err launch_reduce(const ApplyHArgs& a, int splits, const R* ws, hipStream_t s) {
   if (splits <= 1) return ok();
   const int64_t total = a.m * (int64_t)a.k;
   const int blocks = (int)std::min<int64_t>(ceil_div(total, 256), 8192);
-  hipLaunchKernelGGL((hx_reduce<R, C>), dim3(blocks), dim3(256), 0, s, a, splits, ws);
+  hipLaunchKernelGGL(hx_reduce, dim3(blocks), dim3(256), 0, s, a, splits, ws);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
 
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED = 0>
-Err launch_cfg(const ApplyHArgs<typename Tr::R>& a, const Plan& p, void* ws, hipStream_t s) {
-  using R = typename Tr::R;
-  using C = typename Tr::C;
+Err launch_cfg(const ApplyHArgs& a, const Plan& p, void* ws, hipStream_t s) {
   const int64_t grid = p.tiles * p.splits;
   hipLaunchKernelGGL((hx_kernel<Tr, BM, BN, BK, NST, WGM, WGN, SCHED>), dim3((unsigned)grid), dim3(256), 0, s, a, p.splits,
                      p.kps, (R*)ws);
   CHASE_LAUNCH_CHECK();
-  return launch_reduce<R, C>(a, p.splits, (const R*)ws, s);
+  return launch_reduce(a, p.splits, (const R*)ws, s);
 }
 
 // Main part on tile shape (BM, BN, ...), remainder on (BMR, BNR, ...).
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED, int BMR, int BNR, int BKR,
           int NSTR, int WGMR, int WGNR>
-Err launch_pair_cfg(const ApplyHArgs<typename Tr::R>& am, const Plan& pm, void* wsm,
-                    const ApplyHArgs<typename Tr::R>& ar, const Plan& pr, void* wsr, hipStream_t s) {
-  using R = typename Tr::R;
-  using C = typename Tr::C;
+Err launch_pair_cfg(const ApplyHArgs& am, const Plan& pm, void* wsm,
+                    const ApplyHArgs& ar, const Plan& pr, void* wsr, hipStream_t s) {
   const int live = (int)(pr.tiles * pr.splits);
   const int nrem = (live + 7) / 8 * 8;
   const int main_live = (int)(pm.tiles * pm.splits);
@@ -631,8 +594,8 @@ Err launch_pair_cfg(const ApplyHArgs<typename Tr::R>& am, const Plan& pm, void* 
                      dim3((unsigned)grid), dim3(256), 0, s, am, pm.splits, pm.kps, (R*)wsm, ar, pr.splits, pr.kps,
                      (R*)wsr, nrem, live, nmain, main_live);
   CHASE_LAUNCH_CHECK();
-  CHASE_TRY((launch_reduce<R, C>(am, pm.splits, (const R*)wsm, s)));
-  return launch_reduce<R, C>(ar, pr.splits, (const R*)wsr, s);
+  CHASE_TRY((launch_reduce(am, pm.splits, (const R*)wsm, s)));
+  return launch_reduce(ar, pr.splits, (const R*)wsr, s);
 }
 
 // Tile shapes (BM x BN reals, K slab BK, NST ring stages), two workgroups
@@ -649,18 +612,11 @@ struct F32Tiles {
   static constexpr int occ[3] = {2, 2, 2};
   static constexpr double split_penalty = 0.01;
 };
-struct F64Tiles {
-  static constexpr int bm[3] = {128, 128, 128}, bn[3] = {128, 64, 32}, bk[3] = {8, 8, 8};
-  static constexpr double eff[3] = {1.0, 0.95, 0.8};
-  static constexpr int occ[3] = {2, 2, 2};
-  static constexpr double split_penalty = 0.02;
-};
-
 // Plan over the first ncfg tile shapes (the narrow shape alone: ncfg = 1
 // starting at the last one).
-template <typename T, typename R>
-Plan plan_for(const ApplyHArgs<R>& a, size_t wsb, bool narrow_only) {
-  const int64_t m2 = 2 * a.m, n2 = ((a.kreal || a.tda) ? 1 : 2) * (int64_t)a.k;
+Plan plan_for(const ApplyHArgs& a, size_t wsb, bool narrow_only) {
+  using T = F32Tiles;
+  const int64_t m2 = 2 * a.m, n2 = (a.tda ? 1 : 2) * (int64_t)a.k;
   if (narrow_only) {
     const int bm[1] = {T::bm[2]}, bn[1] = {T::bn[2]}, bk[1] = {T::bk[2]}, occ[1] = {T::occ[2]};
     const double eff[1] = {T::eff[2]};
@@ -673,7 +629,7 @@ Plan plan_for(const ApplyHArgs<R>& a, size_t wsb, bool narrow_only) {
   return p;
 }
 
-Err launch_plan_f32(const ApplyHArgs<float>& a, const Plan& p, void* ws, hipStream_t s) {
+Err launch_plan_f32(const ApplyHArgs& a, const Plan& p, void* ws, hipStream_t s) {
   switch (p.cfg) {
     case 0: return launch_cfg<TF32, 256, 128, 16, 3, 4, 1, 1>(a, p, ws, s);
     case 1: return launch_cfg<TF32, 256, 64, 16, 3, 4, 1, 1>(a, p, ws, s);
@@ -681,16 +637,8 @@ Err launch_plan_f32(const ApplyHArgs<float>& a, const Plan& p, void* ws, hipStre
   }
 }
 
-Err launch_plan_f64(const ApplyHArgs<double>& a, const Plan& p, void* ws, hipStream_t s) {
-  switch (p.cfg) {
-    case 0: return launch_cfg<TF64, 128, 128, 8, 4, 2, 2, 3>(a, p, ws, s);
-    case 1: return launch_cfg<TF64, 128, 64, 8, 4, 2, 2>(a, p, ws, s);
-    default: return launch_cfg<TF64, 128, 32, 8, 4, 4, 1>(a, p, ws, s);
-  }
-}
-
 // the remainder always on the narrow shape (16 x 16 MFMA for c64)
-Err launch_pair_f32(const ApplyHArgs<float>& am, const Plan& pm, void* wsm, const ApplyHArgs<float>& ar,
+Err launch_pair_f32(const ApplyHArgs& am, const Plan& pm, void* wsm, const ApplyHArgs& ar,
                     const Plan& pr, void* wsr, hipStream_t s) {
   switch (pm.cfg) {
     case 0:
@@ -705,57 +653,17 @@ Err launch_pair_f32(const ApplyHArgs<float>& am, const Plan& pm, void* wsm, cons
   }
 }
 
-Err launch_pair_f64(const ApplyHArgs<double>& am, const Plan& pm, void* wsm, const ApplyHArgs<double>& ar,
-                    const Plan& pr, void* wsr, hipStream_t s) {
-  switch (pm.cfg) {
-    case 0:
-      return launch_pair_cfg<TF64, 128, 128, 8, 4, 2, 2, 3, 128, 32, 8, 4, 4, 1>(am, pm, wsm, ar, pr, wsr, s);
-    case 1:
-      return launch_pair_cfg<TF64, 128, 64, 8, 4, 2, 2, 0, 128, 32, 8, 4, 4, 1>(am, pm, wsm, ar, pr, wsr, s);
-    default: {
-      CHASE_TRY((launch_cfg<TF64, 128, 32, 8, 4, 4, 1>(am, pm, wsm, s)));
-      return launch_cfg<TF64, 128, 32, 8, 4, 4, 1>(ar, pr, wsr, s);
-    }
-  }
-}
-
-template <typename R>
-Err pack(const ApplyHArgs<R>& a, hipStream_t s) {
-  using C = typename ApplyHArgs<R>::C;
-  const bool kr = a.kreal || a.tda;
+Err pack(const ApplyHArgs& a, hipStream_t s) {
+  using C = typename ApplyHArgs::C;
+  const bool kr = a.tda != 0;
   const int kc = kr ? (a.k + 1) / 2 * 2 : a.k;
   const int tj = kr ? 32 : 16;
   const dim3 grid((unsigned)ceil_div(a.yrows, 64), (unsigned)ceil_div(kc, tj));
-  hipLaunchKernelGGL((pack_kernel<R, C>), grid, dim3(256), 0, s, a.X, a.ldx, a.m, a.k, kr ? 1 : 0, a.yr, a.ldyr,
+  hipLaunchKernelGGL(pack_kernel, grid, dim3(256), 0, s, a.X, a.ldx, a.m, a.k, kr ? 1 : 0, a.yr, a.ldyr,
                      a.yrows);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
-
-template <typename R>
-struct PrecOps;
-template <>
-struct PrecOps<float> {
-  using Tiles = F32Tiles;
-  static Err one(const ApplyHArgs<float>& a, const Plan& p, void* ws, hipStream_t s) {
-    return launch_plan_f32(a, p, ws, s);
-  }
-  static Err pair(const ApplyHArgs<float>& am, const Plan& pm, void* wsm, const ApplyHArgs<float>& ar,
-                  const Plan& pr, void* wsr, hipStream_t s) {
-    return launch_pair_f32(am, pm, wsm, ar, pr, wsr, s);
-  }
-};
-template <>
-struct PrecOps<double> {
-  using Tiles = F64Tiles;
-  static Err one(const ApplyHArgs<double>& a, const Plan& p, void* ws, hipStream_t s) {
-    return launch_plan_f64(a, p, ws, s);
-  }
-  static Err pair(const ApplyHArgs<double>& am, const Plan& pm, void* wsm, const ApplyHArgs<double>& ar,
-                  const Plan& pr, void* wsr, hipStream_t s) {
-    return launch_pair_f64(am, pm, wsm, ar, pr, wsr, s);
-  }
-};
 
 // c64 products with 64 < k <= 80 (2k = 130 .. 160 real columns) run on one
 // column of wide tiles (256 x 160, 5 MFMA column blocks per wave, K slab 8 so
@@ -768,7 +676,7 @@ struct PrecOps<double> {
 constexpr int WIDE_REM = 16;
 constexpr int WIDE_BN = 160, WIDE_BK = 8;
 
-Err launch_wide_f32(const ApplyHArgs<float>& a, void* ws, size_t ws_bytes, hipStream_t s) {
+Err launch_wide_f32(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   const int bm[1] = {256}, bn[1] = {WIDE_BN}, bk[1] = {WIDE_BK}, occ[1] = {2};
   const double eff[1] = {1.0};
   const Plan p = make_plan<1>(2 * a.m, 2 * (int64_t)a.k, bm, bn, bk, eff, occ, F32Tiles::split_penalty,
@@ -785,19 +693,14 @@ Err launch_wide_f32(const ApplyHArgs<float>& a, void* ws, size_t ws_bytes, hipSt
 // launch (hx_pair_kernel, remainder workgroups first).  Y is packed for all
 // k columns before.  (A main part whose 2(k - r) is not a multiple of 128
 // would keep a padded tile column and pay the remainder on top.)
-template <typename R>
-Err launch_split(const ApplyHArgs<R>& a, void* ws, size_t ws_bytes, hipStream_t s) {
-  using Ops = PrecOps<R>;
+Err launch_split(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   constexpr int gran = 64;
   const int krem = a.k % gran;
   constexpr int rmax = 20;
-  if constexpr (sizeof(R) == 4) {
-    if (a.k > gran && a.k <= gran + WIDE_REM && !a.kreal && !a.tda)
-      return launch_wide_f32(a, ws, ws ? ws_bytes : 0, s);
-  }
-  if (!ws || krem == 0 || krem > rmax || a.k < gran || a.kreal || a.tda)
-    return Ops::one(a, plan_for<typename Ops::Tiles>(a, ws ? ws_bytes : 0, false), ws, s);
-  ApplyHArgs<R> am = a, ar = a;
+  if (a.k > gran && a.k <= gran + WIDE_REM && !a.tda) return launch_wide_f32(a, ws, ws ? ws_bytes : 0, s);
+  if (!ws || krem == 0 || krem > rmax || a.k < gran || a.tda)
+    return launch_plan_f32(a, plan_for(a, ws ? ws_bytes : 0, false), ws, s);
+  ApplyHArgs am = a, ar = a;
   am.k = a.k - krem;
   ar.k = krem;
   const int64_t c0 = am.k;
@@ -812,20 +715,19 @@ Err launch_split(const ApplyHArgs<R>& a, void* ws, size_t ws_bytes, hipStream_t 
   size_t rem_bytes = (size_t)MAX_SPLITS * 2 * a.m * 2 * krem * sizeof(R);
   rem_bytes = std::min(ceil_div((int64_t)rem_bytes, (int64_t)256) * 256, (int64_t)(ws_bytes / 4));
   const size_t main_bytes = (ws_bytes - rem_bytes) / 256 * 256;
-  const Plan pm = plan_for<typename Ops::Tiles>(am, main_bytes, false);
-  const Plan pr = plan_for<typename Ops::Tiles>(ar, rem_bytes, true);
-  return Ops::pair(am, pm, ws, ar, pr, static_cast<char*>(ws) + main_bytes, s);
+  const Plan pm = plan_for(am, main_bytes, false);
+  const Plan pr = plan_for(ar, rem_bytes, true);
+  return launch_pair_f32(am, pm, ws, ar, pr, static_cast<char*>(ws) + main_bytes, s);
 }
 
 // Columns in chunks of at most kcap (the capacity of the packed buffer).
-template <typename R>
-Err launch_any(const ApplyHArgs<R>& a0, void* ws, size_t ws_bytes, hipStream_t s) {
+Err launch_any(const ApplyHArgs& a0, void* ws, size_t ws_bytes, hipStream_t s) {
   if (a0.k <= 0 || a0.m <= 0) return ok();
   if (a0.kcap <= 0 || !a0.yr || !a0.D || a0.ldyr < 4 * (int64_t)a0.kcap + 4 || a0.ldyr % 8 != 0 ||
       a0.yrows < (a0.m + 31) / 32 * 32 || a0.ldd < a0.m || a0.ldd % 8 != 0)
     return fail(CHASE_PH_ERR_ARG, "apply_h: packed buffer or D missing or misaligned");
   for (int c0 = 0; c0 < a0.k; c0 += a0.kcap) {
-    ApplyHArgs<R> a = a0;
+    ApplyHArgs a = a0;
     a.k = std::min(a0.kcap, a0.k - c0);
     a.X = a0.X + (int64_t)c0 * a0.ldx;
     a.Y = a0.Y + (int64_t)c0 * a0.ldy;
@@ -833,8 +735,8 @@ Err launch_any(const ApplyHArgs<R>& a0, void* ws, size_t ws_bytes, hipStream_t s
     if (a0.Q) a.Q = a0.Q + (int64_t)c0 * a0.ldq;
     if (a0.S) a.S = a0.S + (int64_t)c0 * a0.lds;
     if (a0.dcol) a.dcol = a0.dcol + c0;
-    CHASE_TRY(pack<R>(a, s));
-    CHASE_TRY(launch_split<R>(a, ws, ws_bytes, s));
+    CHASE_TRY(pack(a, s));
+    CHASE_TRY(launch_split(a, ws, ws_bytes, s));
   }
   return ok();
 }
@@ -864,13 +766,8 @@ __global__ void make_d_kernel(const c128* A, const c128* B, int64_t ld, int a_co
 
 }  // namespace
 
-Err launch_apply_h_f32(const ApplyHArgs<float>& a, void* ws, size_t ws_bytes, hipStream_t s) {
-  if (a.kreal) return fail(CHASE_PH_ERR_ARG, "apply_h: K-real columns are a c128 mode");
-  return launch_any<float>(a, ws, ws_bytes, s);
-}
-
-Err launch_apply_h_f64(const ApplyHArgs<double>& a, void* ws, size_t ws_bytes, hipStream_t s) {
-  return launch_any<double>(a, ws, ws_bytes, s);
+Err launch_apply_h_f32(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
+  return launch_any(a, ws, ws_bytes, s);
 }
 
 template <typename C>
@@ -883,6 +780,5 @@ Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, C* D, int64_t l
 }
 
 template Err make_d<c64>(const c128*, const c128*, int64_t, int, c64*, int64_t, int64_t, hipStream_t);
-template Err make_d<c128>(const c128*, const c128*, int64_t, int, c128*, int64_t, int64_t, hipStream_t);
 
 }  // namespace chase

@@ -79,9 +79,9 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // per-column real scalars).  Y may alias P or Q (element-wise
 // read-before-write in the same thread), not X.
 // ----------------------------------------------------------------------------
-template <typename R>
 struct ApplyHArgs {
-  using C = typename Cplx<R>::T;
+  using R = float;
+  using C = c64;
   const C* D;       // m x 2m, column-major, ldd (multiple of 8, >= m)
   int64_t ldd;
   int64_t m;
@@ -123,8 +123,7 @@ Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, C* D, int64_t l
 
 // ws: device workspace for split-K partial products (ws_bytes may be 0:
 // then the K range is never split, nor the columns).
-Err launch_apply_h_f32(const ApplyHArgs<float>& a, void* ws, size_t ws_bytes, hipStream_t s);
-Err launch_apply_h_f64(const ApplyHArgs<double>& a, void* ws, size_t ws_bytes, hipStream_t s);
+Err launch_apply_h_f32(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // Generic complex FP64 GEMM (zgemm.hip):

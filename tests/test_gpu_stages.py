@@ -554,3 +554,51 @@ def test_singular_qsq_detected(prob, solver):
     with pytest.raises(ChasePHError) as e:
         solver.oblique_rr(to_dev(Q))
     assert e.value.status == _lib.ERR_SINGULAR_QSQ
+
+
+# c128 products in real coordinates: rows around the 32- and 128-row groups,
+# odd m (a quad of reals half empty), columns around the 16-column fragments,
+# degrees that end in either buffer, a leading dimension above n.  Every value
+# is a sum of at most 2n products and the degrees are small: 1e-11 of the
+# column norm as for the other c128 filters
+@pytest.mark.parametrize("m,k", [(1, 1), (3, 2), (17, 8), (33, 9), (63, 24), (64, 25), (65, 40), (129, 65), (321, 130)])
+def test_filter_fp64_edges(m, k):
+    print_case("filter_fp64_edges", m=m, k=k)
+    p = problem(m=m, seed=m, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, k, 0)
+    rng = np.random.default_rng(m + k)
+    W = complex_normal(rng, (p.n, k))
+    degs = sorted([1, 2, 3, 4, 5][j % 5] for j in range(k))
+    buf = empty_cm(p.n + 3, k)
+    Wd = buf[: p.n]
+    Wd.copy_(to_dev(W))
+    s.filter(Wd, 1.0, 2.5, 6.0, degs=degs, prec=FP64)
+    ref = chebyshev.chebyshev_filter(p.A, p.B, W, np.array(degs), 1.0, 2.5, 6.0)
+    err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.max(err) < 1e-11, err
+    a = complex_normal(rng, (m, k))
+    X = np.concatenate([a, a.conj()], axis=0)
+    Y = to_host(s.apply_h(to_dev(X), prec=_lib.FP64_KREAL))
+    ref = ham.apply_h(p.A, p.B, X)
+    assert np.max(np.abs(Y - ref)) <= 1e-12 * np.max(np.abs(ref))
+
+
+# every tile width (at most 8, 4, 2, 1 column fragments) and parts that end
+# inside a strip, through the epilogue of the recurrence
+@pytest.mark.parametrize("plan", ["0,1", "0,3", "0,7", "1,2", "1,5", "2,3", "3,1", "3,4"])
+def test_filter_fp64_every_tile_plan(prob, plan, monkeypatch):
+    k = 77
+    print_case("filter_fp64_plan", m=prob.m, k=k, plan=plan)
+    monkeypatch.setenv("CHASE_PH_APPLY_PLAN", plan)
+    A, B = dev_blocks(prob)
+    s = PHSolver(A, B, k, 0)
+    mu1, mu_nevex, mu_n = _mus(prob)
+    rng = np.random.default_rng(77)
+    W = complex_normal(rng, (prob.n, k))
+    degs = [2] * 30 + [3] * 30 + [5] * 17
+    Wd = to_dev(W)
+    s.filter(Wd, mu1, mu_nevex, mu_n, degs=degs, prec=FP64)
+    ref = chebyshev.chebyshev_filter(prob.A, prob.B, W, np.array(degs), mu1, mu_nevex, mu_n)
+    err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.max(err) < 1e-11, err
