@@ -152,8 +152,7 @@ Err h2d(chase_ph_t h, void* dst, const void* src, size_t bytes) {
 constexpr int GEMM_LOWER_ONLY = 1, GEMM_A_LOWER = 2, GEMM_B_UPPER = 4, GEMM_REAL = 8;
 
 Err gemm(chase_ph_t h, int ta, int tb, int64_t M, int64_t N, int64_t K, c128 alpha, const c128* A, int64_t lda,
-         const c128* B, int64_t ldb, c128 beta, c128* C, int64_t ldc, int64_t kneg = -1, bool split = true,
-         int flags = 0) {
+         const c128* B, int64_t ldb, c128 beta, c128* C, int64_t ldc, int64_t kneg = -1, int flags = 0) {
   ZgemmArgs g{};
   g.lower_only = (flags & GEMM_LOWER_ONLY) != 0;
   g.a_lower = (flags & GEMM_A_LOWER) != 0;
@@ -165,7 +164,7 @@ Err gemm(chase_ph_t h, int ta, int tb, int64_t M, int64_t N, int64_t K, c128 alp
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.kneg = kneg < 0 ? K : kneg;
   g.batch = 1;
-  return zgemm(g, split ? h->ws : nullptr, split ? h->ws_bytes : 0, h->st);
+  return zgemm(g, h->ws, h->ws_bytes, h->st);
 }
 
 // Block of 2 nevex real columns in X4, all zero: the products write the live
@@ -514,7 +513,7 @@ Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int
 // Lower triangle of the Gram matrix X^H X in Lbuf (padded with I).
 Err gram_lower(chase_ph_t h, int k, int kp, const c128* X, int64_t ldx, c128* Lbuf, bool real, int64_t nr) {
   CHASE_TRY(fill_padded(Lbuf, kp, k, 0.0, 1.0, true, h->st));
-  return gemm(h, 1, 0, k, k, nr, {1, 0}, X, ldx, X, ldx, {0, 0}, Lbuf, kp, -1, true,
+  return gemm(h, 1, 0, k, k, nr, {1, 0}, X, ldx, X, ldx, {0, 0}, Lbuf, kp, -1,
               GEMM_LOWER_ONLY | (real ? GEMM_REAL : 0));
 }
 
@@ -528,7 +527,7 @@ Err cholqr_pass(chase_ph_t h, int k, int kp, const c128* Xin, int64_t ldin, c128
   CHASE_TRY(cholesky_lower(Lbuf, kp, h->dws, h->st, failed));
   if (*failed) return ok();
   CHASE_TRY(tri_inverse_lower(Lbuf, h->Li, kp, h->dws, h->st));
-  return gemm(h, 0, 1, nr, k, k, {1, 0}, Xin, ldin, h->Li, kp, {0, 0}, Xout, ldout, -1, true, GEMM_B_UPPER | rf);
+  return gemm(h, 0, 1, nr, k, k, {1, 0}, Xin, ldin, h->Li, kp, {0, 0}, Xout, ldout, -1, GEMM_B_UPPER | rf);
 }
 
 // Householder QR of X in place; with npre = 2, X is the output of two
@@ -543,8 +542,8 @@ Err householder_fallback(chase_ph_t h, int k, c128* X, int64_t ldx, c128* R, int
                                hipMemcpyDeviceToDevice, h->st));
     return ok();
   }
-  CHASE_TRY(gemm(h, 0, 1, k, k, k, {1, 0}, h->G, kp, h->L2, kp, {0, 0}, h->Tk, kp, -1, false));
-  return gemm(h, 0, 1, k, k, k, {1, 0}, h->Tk, kp, h->L1, kp, {0, 0}, R, ldr, -1, false);
+  CHASE_TRY(gemm(h, 0, 1, k, k, k, {1, 0}, h->G, kp, h->L2, kp, {0, 0}, h->Tk, kp));
+  return gemm(h, 0, 1, k, k, k, {1, 0}, h->Tk, kp, h->L1, kp, {0, 0}, R, ldr);
 }
 
 // CholeskyQR2; shifted CholeskyQR3 when its first factorisation breaks
@@ -594,7 +593,7 @@ Err qr_impl(chase_ph_t h, int k, c128* X, int64_t ldx, c128* R, int64_t ldr, int
     if (used_shift) *used_shift = 1;
     // shifted CholeskyQR3: s = 11 (n k + k (k + 1)) u ||X||_F^2
     CHASE_TRY(fill_padded(h->G, kp, k, 0.0, 1.0, true, h->st));
-    CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, X, ldx, X, ldx, {0, 0}, h->G, kp, -1, true,
+    CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, X, ldx, X, ldx, {0, 0}, h->G, kp, -1,
                    GEMM_LOWER_ONLY | (real ? GEMM_REAL : 0)));
     CHASE_TRY(trace(h->G, kp, k, h->dws.dscalar, h->st));
     double fro2 = 0;
@@ -618,10 +617,10 @@ Err qr_impl(chase_ph_t h, int k, c128* X, int64_t ldx, c128* R, int64_t ldr, int
   if (R) {
     // R = L_nf^H ... L_1^H
     if (nf == 2) {
-      CHASE_TRY(gemm(h, 1, 1, k, k, k, {1, 0}, h->L2, kp, h->L1, kp, {0, 0}, R, ldr, -1, false));
+      CHASE_TRY(gemm(h, 1, 1, k, k, k, {1, 0}, h->L2, kp, h->L1, kp, {0, 0}, R, ldr));
     } else {
-      CHASE_TRY(gemm(h, 1, 1, k, k, k, {1, 0}, h->L3, kp, h->L2, kp, {0, 0}, h->Tk, kp, -1, false));
-      CHASE_TRY(gemm(h, 0, 1, k, k, k, {1, 0}, h->Tk, kp, h->L1, kp, {0, 0}, R, ldr, -1, false));
+      CHASE_TRY(gemm(h, 1, 1, k, k, k, {1, 0}, h->L3, kp, h->L2, kp, {0, 0}, h->Tk, kp));
+      CHASE_TRY(gemm(h, 0, 1, k, k, k, {1, 0}, h->Tk, kp, h->L1, kp, {0, 0}, R, ldr));
     }
   }
   return ok();
@@ -639,14 +638,14 @@ Err rr_backup(chase_ph_t h, int k, const c128* Q, int64_t ldq, const c128* T, in
   CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, T, ldt, {0, 0}, h->Tk, kp));     // Q^H H Q
   CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, Q, ldq, {0, 0}, h->Nb, kp, m));  // N = Q^H S Q
   CHASE_TRY(backup_diag(h->Nb, kp, k, BACKUP_DIAG_MIN, h->dres, h->st));            // D; Nb <- N - D
-  CHASE_TRY(gemm(h, 0, 0, k, k, k, {-1, 0}, h->Nb, kp, h->Tk, kp, {1, 0}, h->G, kp, -1, false));
+  CHASE_TRY(gemm(h, 0, 0, k, k, k, {-1, 0}, h->Nb, kp, h->Tk, kp, {1, 0}, h->G, kp));
   CHASE_TRY(scale_rows_inv(h->G, kp, k, h->dres, h->st));                           // G = D^{-1} [...]
   int qs = 0;
   CHASE_TRY(nonsym_eig(h->G, h->Ev, kp, k, h->Wev, h->L3, h->Li, h->gw, h->st, &qs));
   if (qs != 0)
     return fail(CHASE_PH_ERR_SINGULAR_QSQ, "back-up Rayleigh quotient: QR iteration did not converge for k = " +
                                                std::to_string(k));
-  CHASE_TRY(gemm(h, 0, 0, k, k, k, {1, 0}, h->Ev, kp, h->Li, kp, {0, 0}, h->Ys, kp, -1, false));  // Z Y
+  CHASE_TRY(gemm(h, 0, 0, k, k, k, {1, 0}, h->Ev, kp, h->Li, kp, {0, 0}, h->Ys, kp));  // Z Y
   CHASE_TRY(select_by_real_part(h->Wev, k, h->Ys, kp, h->dperm, h->dlam, Zpos, ldz, h->st));
   if (ritz) {
     CHASE_TRY(d2h_small(ritz, h->dlam, sizeof(double) * (k / 2), h->dws, h->st));
@@ -687,13 +686,13 @@ Err rr_general(chase_ph_t h, int k, const c128* Q, int64_t ldq, const c128* T, i
   CHASE_TRY(fill_padded(h->L1, kp, k, 0.0, 1.0, true, h->st));
   CHASE_TRY(conj_transpose(h->L3, kp, h->L1, kp, k, h->st));                        // R^H (lower)
   CHASE_TRY(tri_inverse_lower(h->L1, h->Li, kp, h->dws, h->st));                    // (R^H)^{-1}
-  CHASE_TRY(gemm(h, 1, 0, k, k, k, {1, 0}, h->Li, kp, h->Tk, kp, {0, 0}, h->G, kp, -1, false));  // G = R^{-1} C
+  CHASE_TRY(gemm(h, 1, 0, k, k, k, {1, 0}, h->Li, kp, h->Tk, kp, {0, 0}, h->G, kp));  // G = R^{-1} C
   int qs = 0;
   CHASE_TRY(nonsym_eig(h->G, h->Ev, kp, k, h->Wev, h->L3, h->Li, h->gw, h->st, &qs));
   if (qs != 0)
     return fail(CHASE_PH_ERR_SINGULAR_QSQ, "general Rayleigh quotient: QR iteration did not converge for k = " +
                                                std::to_string(k));
-  CHASE_TRY(gemm(h, 0, 0, k, k, k, {1, 0}, h->Ev, kp, h->Li, kp, {0, 0}, h->Ys, kp, -1, false));  // Z Y
+  CHASE_TRY(gemm(h, 0, 0, k, k, k, {1, 0}, h->Ev, kp, h->Li, kp, {0, 0}, h->Ys, kp));  // Z Y
   CHASE_TRY(select_by_real_part(h->Wev, k, h->Ys, kp, h->dperm, h->dlam, Zpos, ldz, h->st));
   if (ritz) {
     CHASE_TRY(d2h_small(ritz, h->dlam, sizeof(double) * (k / 2), h->dws, h->st));
@@ -734,7 +733,7 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
     return rr_backup(h, k, Q, ldq, T, ldt, ritz, Zpos, ldz);
   }
   CHASE_TRY(fill_padded(h->G, kp, k, 0.0, 1.0, true, h->st));
-  CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, T, ldt, {0, 0}, h->G, kp, m, true,
+  CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, T, ldt, {0, 0}, h->G, kp, m,
                  GEMM_LOWER_ONLY));  // M = Q^H S T (Hermitian; the Cholesky reads the lower triangle)
   bool failed = false;
   CHASE_TRY(cholesky_lower(h->G, kp, h->dws, h->st, &failed));                // L L^H = M
@@ -742,9 +741,9 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
   CHASE_TRY(tri_inverse_lower(h->G, h->Li, kp, h->dws, h->st));
   CHASE_TRY(fill_padded(h->Nb, kp, k, 1.0, 0.0, true, h->st));              // N = I - 2 Q2^H Q2
   CHASE_TRY(gemm(h, 1, 0, k, k, m, {-2, 0}, Q + m, ldq, Q + m, ldq, {1, 0}, h->Nb, kp));
-  CHASE_TRY(gemm(h, 0, 1, kp, kp, kp, {1, 0}, h->Nb, kp, h->Li, kp, {0, 0}, h->Tk, kp, -1, false,
+  CHASE_TRY(gemm(h, 0, 1, kp, kp, kp, {1, 0}, h->Nb, kp, h->Li, kp, {0, 0}, h->Tk, kp, -1,
                  GEMM_B_UPPER));  // N L^{-H}
-  CHASE_TRY(gemm(h, 0, 0, kp, kp, kp, {1, 0}, h->Li, kp, h->Tk, kp, {0, 0}, h->G, kp, -1, false,
+  CHASE_TRY(gemm(h, 0, 0, kp, kp, kp, {1, 0}, h->Li, kp, h->Tk, kp, {0, 0}, h->G, kp, -1,
                  GEMM_A_LOWER));  // L^{-1} N L^{-H}
   int sweeps = 0;
   CHASE_TRY(jacobi_eigh(h->G, h->Ev, kp, h->dws, h->st, h->p.rr_max_sweeps, &sweeps));
@@ -759,7 +758,7 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
     return fail(CHASE_PH_ERR_SINGULAR_QSQ, "Q^H S Q numerically singular: " + std::to_string(npos) + " positive / " +
                                                std::to_string(nneg) + " negative resolved Ritz values for k = " +
                                                std::to_string(k));
-  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, Zpos, ldz, -1, false));  // Z = L^{-H} Y
+  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, Zpos, ldz));  // Z = L^{-H} Y
   if (ritz) {
     CHASE_TRY(d2h_small(ritz, h->dlam, sizeof(double) * (k / 2), h->dws, h->st));
   }
@@ -770,8 +769,8 @@ Err resid_impl(chase_ph_t h, int k, int kk, const c128* Q, int64_t ldq, const c1
                int64_t ldz, const double* ritz_host, c128* V, int64_t ldv, double* resid, c128* Rout = nullptr) {
   if (kk == 0) return ok();
   const int64_t n = h->n;
-  CHASE_TRY(gemm(h, 0, 0, n, kk, k, {1, 0}, Q, ldq, Zpos, ldz, {0, 0}, V, ldv, -1, false));
-  CHASE_TRY(gemm(h, 0, 0, n, kk, k, {1, 0}, T, ldt, Zpos, ldz, {0, 0}, h->TZ, n, -1, false));
+  CHASE_TRY(gemm(h, 0, 0, n, kk, k, {1, 0}, Q, ldq, Zpos, ldz, {0, 0}, V, ldv));
+  CHASE_TRY(gemm(h, 0, 0, n, kk, k, {1, 0}, T, ldt, Zpos, ldz, {0, 0}, h->TZ, n));
   if (ritz_host) CHASE_TRY(h2d(h, h->dlam, ritz_host, sizeof(double) * kk));
   CHASE_TRY(residual_norms(V, ldv, h->TZ, n, h->dlam, n, kk, h->dres, Rout, n, h->st));
   CHASE_TRY(d2h_small(resid, h->dres, sizeof(double) * kk, h->dws, h->st));
@@ -1213,9 +1212,9 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
     if (lq > 0) {
       CHASE_TRY(kreal_coords(h->Xs, n, m, 2 * lq, h->Xt, n, h->st));
       for (int pass = 0; pass < 2; ++pass) {
-        CHASE_TRY(gemm(h, 1, 0, 2 * lq, kxn, n, {1, 0}, h->Xt, n, h->Tq, n, {0, 0}, h->G, h->kp, -1, true,
+        CHASE_TRY(gemm(h, 1, 0, 2 * lq, kxn, n, {1, 0}, h->Xt, n, h->Tq, n, {0, 0}, h->G, h->kp, -1,
                        GEMM_REAL));  // C = Qp^T X
-        CHASE_TRY(gemm(h, 0, 0, n, kxn, 2 * lq, {-1, 0}, h->Xt, n, h->G, h->kp, {1, 0}, h->Tq, n, -1, true,
+        CHASE_TRY(gemm(h, 0, 0, n, kxn, 2 * lq, {-1, 0}, h->Xt, n, h->G, h->kp, {1, 0}, h->Tq, n, -1,
                        GEMM_REAL));  // X -= Qp C
       }
     }
@@ -1514,8 +1513,8 @@ Err solve_tda_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, i
     inf.rr_flops += hx_flops((double)h->n, kw, true) + 8.0 * m * (double)kw * kw + 16.0 * m * (double)nevex * nevex;
     // residuals ||A w - omega w|| of the unit Ritz vectors w = Q z
     CHASE_TRY(tm.start());
-    CHASE_TRY(gemm(h, 0, 0, m, kw, kw, {1, 0}, Q, m, h->Ys, kt, {0, 0}, h->Vt, m, -1, false));
-    CHASE_TRY(gemm(h, 0, 0, m, kw, kw, {1, 0}, h->Tq, m, h->Ys, kt, {0, 0}, h->TZ, m, -1, false));
+    CHASE_TRY(gemm(h, 0, 0, m, kw, kw, {1, 0}, Q, m, h->Ys, kt, {0, 0}, h->Vt, m));
+    CHASE_TRY(gemm(h, 0, 0, m, kw, kw, {1, 0}, h->Tq, m, h->Ys, kt, {0, 0}, h->TZ, m));
     CHASE_TRY(h2d(h, h->dlam, ritz.data(), sizeof(double) * kw));
     CHASE_TRY(residual_norms(h->Vt, m, h->TZ, m, h->dlam, m, kw, h->dres, nullptr, 0, h->st));
     CHASE_TRY(d2h_small(res.data(), h->dres, sizeof(double) * kw, h->dws, h->st));

@@ -602,3 +602,33 @@ def test_filter_fp64_every_tile_plan(prob, plan, monkeypatch):
     ref = chebyshev.chebyshev_filter(prob.A, prob.B, W, np.array(degs), mu1, mu_nevex, mu_n)
     err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
     assert np.max(err) < 1e-11, err
+
+
+# c128 GEMMs of the QR and Rayleigh-Ritz steps: sizes around the 32-row waves,
+# the 64-row tiles and the 8-row K slabs, with odd m (K and the sign flip of S
+# end inside a slab), against the oracle at the tolerances of the larger cases
+@pytest.mark.parametrize("m,k", [(19, 2), (33, 16), (67, 32), (130, 34), (261, 66), (389, 130)])
+def test_qr_rr_residuals_gemm_edges(m, k):
+    print_case("gemm_edges", m=m, k=k)
+    p = problem(m=m, seed=m, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, k // 2, 0)
+    rng = np.random.default_rng(m)
+    W = complex_normal(rng, (p.n, k // 2))
+    W[m:] *= 1e-3
+    X = np.concatenate([W, ham.apply_k_conj(W)], axis=1)
+    Qd = to_dev(X)
+    Rd, _ = s.qr(Qd)
+    Q, R = to_host(Qd), to_host(Rd)
+    Qr, Rr = np.linalg.qr(X)
+    ph = np.diag(Rr) / np.abs(np.diag(Rr))
+    assert np.max(np.abs(Q - Qr * ph)) < 1e-9
+    assert np.max(np.abs(R - Rr * ph.conj()[:, None])) < 1e-9 * np.max(np.abs(Rr))
+    ritz, Z, T = s.oblique_rr(Qd)
+    ref_ritz = rayleigh_ritz.oblique_rr(p.A, p.B, Q)[0]
+    assert np.max(np.abs(ritz - ref_ritz) / np.abs(ref_ritz)) < 1e-11
+    V, res = s.residuals(Qd, T, Z, ritz)
+    V = to_host(V)
+    assert np.max(np.abs(np.linalg.norm(V, axis=0) - 1)) < 1e-12
+    hv = ham.apply_h(p.A, p.B, V) - V * ritz[None, :]
+    assert np.max(np.abs(np.linalg.norm(hv, axis=0) - res)) < 1e-11
