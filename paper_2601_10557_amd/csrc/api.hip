@@ -524,9 +524,8 @@ Err cholqr_pass(chase_ph_t h, int k, int kp, const c128* Xin, int64_t ldin, c128
   // Gram matrix: the Cholesky reads its lower triangle only
   if (!gram_ready) CHASE_TRY(gram_lower(h, k, kp, Xin, ldin, Lbuf, real, nr));
   if (shift != 0.0) CHASE_TRY(add_diag(Lbuf, kp, k, shift, h->st));
-  CHASE_TRY(cholesky_lower(Lbuf, kp, h->dws, h->st, failed));
+  CHASE_TRY(cholesky_inverse(Lbuf, h->Li, kp, h->dws, h->st, failed));
   if (*failed) return ok();
-  CHASE_TRY(tri_inverse_lower(Lbuf, h->Li, kp, h->dws, h->st));
   return gemm(h, 0, 1, nr, k, k, {1, 0}, Xin, ldin, h->Li, kp, {0, 0}, Xout, ldout, -1, GEMM_B_UPPER | rf);
 }
 
@@ -736,9 +735,8 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
   CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, T, ldt, {0, 0}, h->G, kp, m,
                  GEMM_LOWER_ONLY));  // M = Q^H S T (Hermitian; the Cholesky reads the lower triangle)
   bool failed = false;
-  CHASE_TRY(cholesky_lower(h->G, kp, h->dws, h->st, &failed));                // L L^H = M
+  CHASE_TRY(cholesky_inverse(h->G, h->Li, kp, h->dws, h->st, &failed));      // L L^H = M, and L^{-1}
   if (failed) return fail(CHASE_PH_ERR_NOT_DEFINITE, "Cholesky of Q^H S H Q failed (SH not positive definite on range(Q))");
-  CHASE_TRY(tri_inverse_lower(h->G, h->Li, kp, h->dws, h->st));
   CHASE_TRY(fill_padded(h->Nb, kp, k, 1.0, 0.0, true, h->st));              // N = I - 2 Q2^H Q2
   CHASE_TRY(gemm(h, 1, 0, k, k, m, {-2, 0}, Q + m, ldq, Q + m, ldq, {1, 0}, h->Nb, kp));
   CHASE_TRY(gemm(h, 0, 1, kp, kp, kp, {1, 0}, h->Nb, kp, h->Li, kp, {0, 0}, h->Tk, kp, -1,
@@ -1649,7 +1647,6 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   CHASE_TRY(dalloc(h, &h->lr, (size_t)n * nv));
   CHASE_TRY(dalloc(h, &h->lz, (size_t)n * nv));
   CHASE_TRY(dalloc(h, &h->dab, (size_t)(2 * std::max(1, p->lanczos_steps) + 1) * nv));
-  CHASE_TRY(dalloc(h, &h->dws.small, 64 * 64));
   CHASE_TRY(dalloc(h, &h->dws.panel, (size_t)h->kp * 64));
   CHASE_TRY(dalloc(h, &h->dws.tmp, (size_t)h->kp * 64));
   CHASE_TRY(dalloc(h, &h->dws.U, (size_t)h->kp * 64));

@@ -5,7 +5,6 @@
 namespace chase {
 
 struct DenseWs {
-  c128* small = nullptr;   // 64 x 64
   c128* panel = nullptr;   // kp_max x 64
   c128* tmp = nullptr;     // kp_max x 64 (batched 64 x 64 blocks)
   c128* U = nullptr;       // kp_max x 64 (one rotation block per Jacobi pair)
@@ -27,8 +26,10 @@ int pad64(int k);
 // M = diag(inner) on the first k, pad on the rest; off-diagonals zeroed
 // everywhere when zero_all, else only in the padded rows/columns.
 Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s);
-// In place lower Cholesky of a Hermitian padded matrix; *failed on breakdown.
-Err cholesky_lower(c128* M, int kp, DenseWs& ws, hipStream_t s, bool* failed);
+// In place lower Cholesky of a Hermitian padded matrix (lower triangle given)
+// and X = L^{-1} (chol.hip; both ld kp); *failed on breakdown, both then
+// unspecified.
+Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, bool* failed);
 // X = L^{-1} for lower-triangular L (both kp x kp, ld kp); X must not alias L.
 Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s);
 // Block Jacobi: G (Hermitian, in place) -> diag(theta), V -> eigenvectors.

@@ -2,7 +2,6 @@
 // Cholesky QR; Alg. 2: POTRF, TRSM, HEEVD).  All operate on k x k Hermitian
 // or triangular matrices stored in a padded kp x kp buffer (kp a multiple of
 // 64, leading dimension kp) so that every blocked step has uniform sizes:
-//  * Cholesky  M = L L^H, right-looking, 64-column panels;
 //  * triangular inverse L^{-1}, by block diagonals of batched GEMMs;
 //  * Hermitian eigensolver: block Jacobi with 16-column blocks; each pair of
 //    blocks (a 32 x 32 subproblem) gets one cyclic Jacobi sweep in LDS and
@@ -29,12 +28,9 @@ __device__ __forceinline__ c128 cconj(c128 a) { return {a.re, -a.im}; }
 __device__ __forceinline__ c128 cadd(c128 a, c128 b) { return {a.re + b.re, a.im + b.im}; }
 __device__ __forceinline__ c128 csub(c128 a, c128 b) { return {a.re - b.re, a.im - b.im}; }
 __device__ __forceinline__ c128 cscale(double s, c128 a) { return {s * a.re, s * a.im}; }
-// r - a b and r - a conj(b), as four fused multiply-adds each
+// r - a b as four fused multiply-adds
 __device__ __forceinline__ c128 cfms(c128 r, c128 a, c128 b) {
   return {fma(-a.re, b.re, fma(a.im, b.im, r.re)), fma(-a.re, b.im, fma(-a.im, b.re, r.im))};
-}
-__device__ __forceinline__ c128 cfms_conj(c128 r, c128 a, c128 b) {
-  return {fma(-a.re, b.re, fma(-a.im, b.im, r.re)), fma(a.re, b.im, fma(-a.im, b.re, r.im))};
 }
 
 // ---------------------------------------------------------------- fills
@@ -51,25 +47,14 @@ __global__ void fill_diag_kernel(c128* M, int64_t ld, int kp, int k, double inne
   }
 }
 
-// Zero the strict upper triangle (used after the blocked Cholesky, whose
-// trailing updates also touch the upper part).
-__global__ void zero_upper_kernel(c128* M, int64_t ld, int kp) {
-  const int64_t total = (int64_t)kp * kp;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int j = (int)(t / kp), i = (int)(t % kp);
-    if (i < j) M[(int64_t)j * ld + i] = c128{0.0, 0.0};
-  }
-}
-
-// ------------------------------------------------------- Cholesky block
-// 64 x 64 diagonal blocks, 256 threads.  Lane i of every wave holds row i
-// (Cholesky) or column i (inverse), and wave w the 16 columns (rows)
-// w, w + 4, ..., w + 60 in registers: interleaved, so that the four waves
-// share the shrinking trailing part evenly.  A step publishes one column
-// (row) through LDS, on rotating buffers, so it takes one barrier, and
-// every other operand of the step is a broadcast LDS read.
-constexpr int CT = 256;     // threads of the block kernels
-constexpr int CW = NB / 4;  // columns (rows) per wave
+// --------------------------------------------- triangular inverse blocks
+// Inverse of 64 x 64 triangular blocks, 256 threads.  Lane c of every wave
+// holds column c, and wave w the 16 rows w, w + 4, ..., w + 60 in registers:
+// interleaved, so that the four waves share the shrinking trailing part
+// evenly.  A step publishes one row through LDS, on rotating buffers, so it
+// takes one barrier, and every other operand is a broadcast LDS read.
+constexpr int CT = 256;     // threads of the block kernel
+constexpr int CW = NB / 4;  // rows per wave
 
 // Lane exchange inside a row of 16 lanes by DPP (no LDS round trip).
 template <int CTRL>
@@ -110,86 +95,6 @@ __device__ __forceinline__ double rcp_nr(double d) {
   return q;
 }
 
-// Lower Cholesky A = L L^H of the block and its inverse X = L^{-1}, run as
-// one sweep of 64 column steps with one barrier each.
-//  * Cholesky, right-looking in LDL^H form: step j takes the pivot
-//    d_j = A[j][j] and applies A[i][l] -= A[i][j] conj(A[l][j]) / d_j for
-//    j < l <= i; thread (w, i) holds A[i][4 t + w] in r[t], and the columns
-//    are scaled by 1 / sqrt(d_j) at the end.
-//  * Inverse, forward substitution on the 64 unit right-hand sides one step
-//    behind: step j finishes row j - 1 of X (x = b / L[j-1][j-1], on wave
-//    (j - 1) mod 4) and every wave updates its rows r > j - 1 by
-//    b_r -= L[r][j-1] x with column j - 1 of L (published the step before);
-//    thread (w, c) holds X[4 t + w][c] in b[t].
-// A step publishes column j (and row j - 1 of X) through LDS, the columns
-// triple-buffered since a step reads the last two.  A non-positive or
-// non-finite pivot is replaced by 1 so that the block stays finite (the
-// caller flags it and discards the result).  On return r holds the
-// unscaled columns, b the inverse, dpiv the raw pivots and rsq[j] =
-// 1 / sqrt(d_j) (1 for a replaced pivot).
-__device__ __forceinline__ void chol_inv64(c128 (&r)[CW], c128 (&b)[CW], c128 (*colb)[NB], c128 (*xb)[NB],
-                                           double* dpiv, double* rsq) {
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#pragma unroll
-  for (int t = 0; t < CW; ++t) b[t] = (4 * t + w == lane) ? c128{1.0, 0.0} : c128{0.0, 0.0};
-  double rs_prev = 1.0;  // 1 / sqrt(d_{j-1})
-  // slot tj unrolled (register indices stay static), owner wave wj not
-#pragma unroll
-  for (int tj = 0; tj < CW; ++tj) {
-#pragma unroll 1
-    for (int wj = 0; wj < 4; ++wj) {
-      const int j = 4 * tj + wj;
-      const int k = j - 1;                  // row of X finished in this step
-      const int tk0 = tj > 0 ? tj - 1 : 0;  // its slot: tk0 (wj = 0) or tj
-      c128* col = colb[j % 3];
-      if (w == wj) col[lane] = r[tj];  // column j, final since step j - 1
-      if (k >= 0 && w == (k & 3)) {
-        if (wj == 0) {
-          b[tk0] = cscale(rs_prev, b[tk0]);
-          xb[k & 1][lane] = b[tk0];
-        } else {
-          b[tj] = cscale(rs_prev, b[tj]);
-          xb[k & 1][lane] = b[tj];
-        }
-      }
-      __syncthreads();
-      const double draw = col[j].re;
-      const double d = (draw > 0.0 && isfinite(draw)) ? draw : 1.0;
-      if (threadIdx.x == 0) {
-        dpiv[j] = draw;
-        rsq[j] = rsqrt_nr(d);
-      }
-      const c128 s = cscale(rcp_nr(d), col[lane]);
-      // all reads of the step first, so that their latencies overlap
-      c128 c[CW], l[CW];
-#pragma unroll
-      for (int t = tj; t < CW; ++t) c[t] = col[4 * t + w];
-      c128 x{0.0, 0.0};
-      if (k >= 0) {
-        // x_{j-1} times the column scale of L[:, j-1]
-        x = cscale(rs_prev, xb[k & 1][lane]);
-        const c128* colk = colb[(j + 2) % 3];
-#pragma unroll
-        for (int t = tk0; t < CW; ++t) l[t] = colk[4 * t + w];
-      }
-      // columns l > j, all rows: the entries above the diagonal (l > i) take
-      // updates too but are never read for an entry on or below it
-#pragma unroll
-      for (int t = tj; t < CW; ++t)
-        if (t > tj || w > wj) r[t] = cfms_conj(r[t], s, c[t]);
-      if (k >= 0) {
-#pragma unroll
-        for (int t = tk0; t < CW; ++t)
-          if (4 * t + w > k) b[t] = cfms(b[t], l[t], x);
-      }
-      rs_prev = rsqrt_nr(d);
-    }
-  }
-  // row 63 of X: its last update came with step 63
-  if (w == 3) b[CW - 1] = cscale(rs_prev, b[CW - 1]);
-}
-
 // X = L^{-1} by forward substitution on the 64 unit right-hand sides at
 // once: thread (w, c) holds X[4 t + w][c] in b[t]; step k finishes row k
 // (x_k = b_k / L[k][k]) on wave k mod 4, which publishes it, and every
@@ -220,46 +125,6 @@ __device__ __forceinline__ void trinv64(const c128 (*S)[NB + 1], const double* r
       for (int t = tk; t < CW; ++t)
         if (t > tk || w > wk) b[t] = cfms(b[t], l[t], x);
     }
-  }
-}
-
-// Factor the 64 x 64 diagonal block at (p, p): writes L_pp (lower, upper
-// zeroed) in place and L_pp^{-1} into inv (64 x 64, ld 64).
-__global__ __launch_bounds__(CT) void potrf_diag_kernel(c128* M, int64_t ld, int p, c128* inv, int* fail) {
-  __shared__ c128 S[NB][NB + 1];
-  __shared__ c128 colb[3][NB];
-  __shared__ c128 xb[2][NB];
-  __shared__ double dpiv[NB];
-  __shared__ double rsq[NB];
-  const int lane = threadIdx.x & 63;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  c128 r[CW], b[CW];
-#pragma unroll
-  for (int t = 0; t < CW; ++t) r[t] = M[(int64_t)(p + 4 * t + w) * ld + p + lane];
-  chol_inv64(r, b, colb, xb, dpiv, rsq);
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < CW; ++t) {
-    const int l = 4 * t + w;
-    const double dl = dpiv[l];
-    const bool ok = dl > 0.0 && isfinite(dl);
-    const c128 v = lane > l ? cscale(rsq[l], r[t]) : (lane == l ? c128{ok ? sqrt(dl) : 1.0, 0.0} : c128{0.0, 0.0});
-    M[(int64_t)(p + l) * ld + p + lane] = v;
-    if (lane == l && !ok) atomicOr(fail, 1);
-    S[l][lane] = b[t];
-  }
-  __syncthreads();
-  for (int t = threadIdx.x; t < NB * NB; t += CT) {
-    const int j = t / NB, i = t % NB;
-    inv[(int64_t)j * NB + i] = (i >= j) ? S[i][j] : c128{0.0, 0.0};
-  }
-}
-
-__global__ void copy_block_kernel(const c128* src, int64_t lds, c128* dst, int64_t ldd, int rows, int cols) {
-  const int64_t total = (int64_t)rows * cols;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = t / rows, i = t % rows;
-    dst[j * ldd + i] = src[j * lds + i];
   }
 }
 
@@ -707,46 +572,6 @@ Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all,
   hipLaunchKernelGGL(fill_diag_kernel, dim3(grid_for((int64_t)kp * kp)), dim3(256), 0, s, M, (int64_t)kp, kp, k,
                      inner, pad, zero_all ? 1 : 0);
   CHASE_LAUNCH_CHECK();
-  return ok();
-}
-
-Err cholesky_lower(c128* M, int kp, DenseWs& ws, hipStream_t s, bool* failed) {
-  CHASE_HIP(hipMemsetAsync(ws.flag, 0, sizeof(int), s));
-  const int nblk = kp / NB;
-  for (int b = 0; b < nblk; ++b) {
-    const int p = b * NB;
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(CT), 0, s, M, (int64_t)kp, p, ws.small, ws.flag);
-    CHASE_LAUNCH_CHECK();
-    const int rest = kp - p - NB;
-    if (rest <= 0) break;
-    // panel: L_ip = A_ip * L_pp^{-H}
-    hipLaunchKernelGGL(copy_block_kernel, dim3(grid_for((int64_t)rest * NB)), dim3(256), 0, s,
-                       (const c128*)(M + (int64_t)p * kp + p + NB), (int64_t)kp, ws.panel, (int64_t)rest, rest, NB);
-    CHASE_LAUNCH_CHECK();
-    ZgemmArgs g{};
-    g.transA = 0; g.transB = 1;
-    g.M = rest; g.N = NB; g.K = NB;
-    g.alpha = {1, 0}; g.beta = {0, 0};
-    g.A = ws.panel; g.lda = rest; g.B = ws.small; g.ldb = NB;
-    g.C = M + (int64_t)p * kp + p + NB; g.ldc = kp;
-    g.kneg = NB; g.batch = 1;
-    CHASE_TRY(zgemm(g, nullptr, 0, s));
-    // trailing update: A22 -= L_ip L_ip^H
-    ZgemmArgs u{};
-    u.transA = 0; u.transB = 1;
-    u.M = rest; u.N = rest; u.K = NB;
-    u.alpha = {-1, 0}; u.beta = {1, 0};
-    u.A = M + (int64_t)p * kp + p + NB; u.lda = kp;
-    u.B = M + (int64_t)p * kp + p + NB; u.ldb = kp;
-    u.C = M + (int64_t)(p + NB) * kp + p + NB; u.ldc = kp;
-    u.kneg = NB; u.batch = 1;
-    CHASE_TRY(zgemm(u, nullptr, 0, s));
-  }
-  hipLaunchKernelGGL(zero_upper_kernel, dim3(grid_for((int64_t)kp * kp)), dim3(256), 0, s, M, (int64_t)kp, kp);
-  CHASE_LAUNCH_CHECK();
-  int f = 0;
-  CHASE_TRY(d2h_small(&f, ws.flag, sizeof(int), ws, s));
-  *failed = f != 0;
   return ok();
 }
 

@@ -632,3 +632,25 @@ def test_qr_rr_residuals_gemm_edges(m, k):
     assert np.max(np.abs(np.linalg.norm(V, axis=0) - 1)) < 1e-12
     hv = ham.apply_h(p.A, p.B, V) - V * ritz[None, :]
     assert np.max(np.abs(np.linalg.norm(hv, axis=0) - res)) < 1e-11
+
+
+# Cholesky factor and inverse of the blocked kernel through the QR of 64-column
+# blocks: sizes at, below and above one and two blocks, where R = L^H and
+# Q = X L^{-H}; the unique QR at 1e-11 of its scale (cond(X) below 100)
+@pytest.mark.parametrize("k", [2, 62, 64, 66, 126, 128, 130, 192])
+def test_qr_block_edges(k):
+    print_case("qr_block_edges", k=k)
+    p = problem(m=200, seed=3, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, (k + 1) // 2, 0)
+    rng = np.random.default_rng(k)
+    X = complex_normal(rng, (p.n, k)) * np.linspace(0.1, 1.0, k)[None, :]
+    Qd = to_dev(X)
+    Rd, variant = s.qr(Qd)
+    assert variant == 0
+    Q, R = to_host(Qd), to_host(Rd)
+    Qr, Rr = np.linalg.qr(X)
+    ph = np.diag(Rr) / np.abs(np.diag(Rr))
+    assert np.max(np.abs(Q - Qr * ph)) < 1e-11
+    assert np.max(np.abs(R - Rr * ph.conj()[:, None])) < 1e-11 * np.max(np.abs(Rr))
+    assert np.max(np.abs(np.tril(R, -1))) == 0.0
