@@ -1665,6 +1665,10 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   h->ws32_bytes = h->ws_bytes;
   h->ws_bytes = std::max(h->ws_bytes, std::min<size_t>((size_t)128 << 20, (size_t)h->m << 16));
   CHASE_TRY(dalloc(h, (char**)&h->ws, h->ws_bytes));
+  // free while the projected eigenproblem is solved
+  h->dws.k1 = h->Nb;
+  h->dws.k2 = h->Tk;
+  h->dws.k3 = h->L3;
   h->dws.gemm_ws = h->ws;
   h->dws.gemm_ws_bytes = h->ws_bytes;
   h->hhw.gemm_ws = h->ws;

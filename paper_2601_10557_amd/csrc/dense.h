@@ -8,6 +8,7 @@ struct DenseWs {
   c128* panel = nullptr;   // kp_max x 64
   c128* tmp = nullptr;     // kp_max x 64 (batched 64 x 64 blocks)
   c128* U = nullptr;       // kp_max x 64 (one rotation block per Jacobi pair)
+  c128 *k1 = nullptr, *k2 = nullptr, *k3 = nullptr;  // kp_max x kp_max each (jacobi_eigh)
   int* flag = nullptr;     // 4 ints
   int* pflag = nullptr;    // kp_max / 8 ints (Jacobi pair rotated?)
   double* dscalar = nullptr;  // 4 doubles
@@ -32,7 +33,9 @@ Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all,
 Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, bool* failed);
 // X = L^{-1} for lower-triangular L (both kp x kp, ld kp); X must not alias L.
 Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s);
-// Block Jacobi: G (Hermitian, in place) -> diag(theta), V -> eigenvectors.
+// G (Hermitian, in place) -> eigenvalues theta on the diagonal, V ->
+// eigenvectors, by block Jacobi sweeps and GEMM refinement steps, each counted
+// as a sweep.
 Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out);
 // Positive eigenvalues theta of the first k: Ysel (kp x k/2, ld kp) and
 // dlam[r] = 1/theta for rank r by descending theta.

@@ -207,11 +207,10 @@ __device__ __forceinline__ int rr_player(int pos, int r, int n) {
 // step's rotation one step late, while the next step's operands are read
 // (round 0), or holds it in registers (the cross rounds, below).
 // Writes U (32 x 32, column-major) to Uw[pair] and flags the pair in pflag
-// when it rotated; *count counts the pairs that rotated.  A subproblem whose
-// off-diagonal entries are all at or below thr is left alone (U = I is
-// implied by pflag = 0).
+// when it rotated.  A subproblem whose off-diagonal entries are all at or
+// below thr is left alone (U = I is implied by pflag = 0).
 __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t ld, int nbj, int round, c128* Uw,
-                                                         double thr, int max_sweeps, int* count, int* pflag) {
+                                                         double thr, int max_sweeps, int* pflag) {
   __shared__ c128 S[2][SP][SP + 1];
   __shared__ c128 U[SP][SP + 1];
   const int pair = blockIdx.x;
@@ -334,10 +333,7 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
     if (!__syncthreads_or(did_any)) break;
     ++total;
   }
-  if (tid == 0) {
-    if (total > 0) atomicAdd(count, 1);
-    pflag[pair] = total > 0;
-  }
+  if (tid == 0) pflag[pair] = total > 0;
   if (total == 0) return;
   c128* Uo = Uw + (int64_t)pair * SP * SP;
   if (cross) {
@@ -607,19 +603,128 @@ Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s
   return ok();
 }
 
-// flag[0] = 1 if some off-diagonal entry of the kp x kp G has |g| > thr:
-// the condition under which a further Jacobi sweep would rotate at all.
-__global__ __launch_bounds__(256) void offdiag_above_kernel(const c128* G, int kp, double thr2, int* flag) {
-  const int64_t total = (int64_t)kp * kp;
+// Per column j of the Hermitian G, over the off-diagonal entries o:
+// part[j] = sum |o|^2, part[kp + j] = sum |e|^2 with e = o / (g_ii - g_jj) over
+// those with |o| > thr, part[2 kp + j] = 1 if there is one.
+__global__ __launch_bounds__(256) void offdiag_cols_kernel(const c128* G, int kp, double thr2, double* part) {
+  __shared__ double r1[256], r2[256];
+  const int j = blockIdx.x;
+  const double dj = G[(int64_t)j * kp + j].re;
+  double so = 0, se = 0;
   int big = 0;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t j = t / kp, i = t % kp;
-    const c128 g = G[t];
-    if (i != j && g.re * g.re + g.im * g.im > thr2) big = 1;
+  for (int i = threadIdx.x; i < kp; i += 256) {
+    if (i == j) continue;
+    const c128 g = G[(int64_t)j * kp + i];
+    const double o2 = g.re * g.re + g.im * g.im;
+    so += o2;
+    if (o2 > thr2) {
+      const double gap = G[(int64_t)i * kp + i].re - dj;
+      se += o2 / (gap * gap);
+      big = 1;
+    }
   }
-  if (__syncthreads_or(big) && threadIdx.x == 0) atomicOr(flag, 1);
+  r1[threadIdx.x] = so;
+  r2[threadIdx.x] = se;
+  const int any = __syncthreads_or(big);
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) {
+      r1[threadIdx.x] += r1[threadIdx.x + w];
+      r2[threadIdx.x] += r2[threadIdx.x + w];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    part[j] = r1[0];
+    part[kp + j] = r2[0];
+    part[2 * kp + j] = any;
+  }
 }
 
+// out[b] = sum of part[b kp ... + kp - 1] in a fixed order, b = blockIdx.x.
+__global__ __launch_bounds__(256) void offdiag_sum_kernel(const double* part, int kp, double* out) {
+  __shared__ double red[256];
+  const double* p = part + (int64_t)blockIdx.x * kp;
+  double s = 0;
+  for (int i = threadIdx.x; i < kp; i += 256) s += p[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+}
+
+// The anti-Hermitian E of jacobi_eigh: e_ij = g_ij / (g_jj - g_ii) from the
+// upper triangle, zero where |g_ij| <= thr.
+__global__ void refine_e_kernel(const c128* G, c128* E, int kp, double thr2) {
+  const int64_t total = (int64_t)kp * kp;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t j = t / kp, i = t % kp;
+    c128 e{0.0, 0.0};
+    if (i != j) {
+      const int64_t a = i < j ? i : j, b = i < j ? j : i;
+      const c128 g = G[b * kp + a];
+      if (g.re * g.re + g.im * g.im > thr2) {
+        const double q = 1.0 / (G[b * kp + b].re - G[a * kp + a].re);
+        e = i < j ? c128{q * g.re, q * g.im} : c128{-q * g.re, q * g.im};
+      }
+    }
+    E[t] = e;
+  }
+}
+
+// With T = E^2 and T2 = T^2 (null: the terms past T are below rounding):
+// E <- I + E + T / 2 - T2 / 8 and T <- T / 16 - 5 T2 / 128.
+__global__ void refine_w_kernel(c128* E, c128* T, const c128* T2, int kp) {
+  const int64_t total = (int64_t)kp * kp;
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
+    const c128 f = T[t];
+    c128 w = E[t];
+    w.re += 0.5 * f.re + (t / kp == t % kp ? 1.0 : 0.0);
+    w.im += 0.5 * f.im;
+    if (T2) {
+      const c128 h = T2[t];
+      w.re -= 0.125 * h.re;
+      w.im -= 0.125 * h.im;
+      T[t] = c128{0.0625 * f.re - 0.0390625 * h.re, 0.0625 * f.im - 0.0390625 * h.im};
+    }
+    E[t] = w;
+  }
+}
+
+// C = op(A) B + beta C on kp x kp matrices
+static Err gemm_kp(int ta, int kp, const c128* A, const c128* B, double beta, c128* C, DenseWs& ws,
+                   hipStream_t s) {
+  ZgemmArgs g{};
+  g.transA = ta;
+  g.M = g.N = g.K = kp;
+  g.alpha = {1, 0};
+  g.beta = {beta, 0};
+  g.A = A; g.lda = kp;
+  g.B = B; g.ldb = kp;
+  g.C = C; g.ldc = kp;
+  g.kneg = kp;
+  g.batch = 1;
+  return zgemm(g, ws.gemm_ws, ws.gemm_ws_bytes, s);
+}
+
+// Largest ||E||_F at which a sweep is replaced by a refinement step: there the
+// first term left out of W, 7/256 E^10, is below rounding; and up to which
+// that of the short form I + E + E^2 / 2, E^4 / 8, is.
+constexpr double REFINE_MAX = 0.04, REFINE_SHORT = 1e-4;
+
+// Eigenvectors V and (on the diagonal) eigenvalues of the Hermitian G: block
+// Jacobi sweeps until the off-diagonal entries are small against the gaps of
+// the diagonal, then GEMMs.  With D the diagonal, O the rest and
+// e_ij = o_ij / (d_j - d_i), the unitary W = E + sqrt(I + E^2) =
+// E + I + T / 2 - T^2 / 8 + T^3 / 16 - 5 T^4 / 128 + ... (T = E^2) takes G to
+// W^H G W with off-diagonal part [O, E] / 2 to second order, ||O||_F ||E||_F
+// at most: quadratic like a sweep, which is kp / 16 - 1 rounds of two
+// dependent launches.  At kp = 384 a sweep takes 590 us (26 a round), a step 270,
+// the last one, which leaves G alone, 100; a Rayleigh-Ritz step at m = 4000 and
+// k = 376 went from 5.06 ms to 4.41, one of the converging iterations at k = 500
+// (m = 4000) from 3 sweeps to 1 or 2.
 Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out) {
   const int nbj = kp / JB;  // even since kp % 64 == 0
   const int npair = nbj / 2;
@@ -631,30 +736,51 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   // subproblem solutions needs about as many outer sweeps as with exact ones
   // and a fraction of the inner work.
   const int inner_sweeps = 1;
+  double* part = reinterpret_cast<double*>(ws.panel);  // 3 kp doubles
   int sweep = 0;
   bool converged = false;
-  for (; sweep < max_sweeps; ++sweep) {
-    CHASE_HIP(hipMemsetAsync(ws.flag, 0, 2 * sizeof(int), s));
+  for (;;) {
+    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)G, kp, thr * thr, part);
+    CHASE_LAUNCH_CHECK();
+    hipLaunchKernelGGL(offdiag_sum_kernel, dim3(3), dim3(256), 0, s, (const double*)part, kp, ws.dscalar + 1);
+    CHASE_LAUNCH_CHECK();
+    double st[3] = {0, 0, 0};
+    CHASE_TRY(d2h_small(st, ws.dscalar + 1, sizeof(st), ws, s));
+    const double of = std::sqrt(st[0]), ef = std::sqrt(st[1]);
+    if (st[2] == 0.0) {  // no off-diagonal entry above thr
+      converged = true;
+      break;
+    }
+    if (sweep == max_sweeps) break;
+    ++sweep;
+    if (ef <= REFINE_MAX) {
+      const int blocks = grid_for((int64_t)kp * kp);
+      c128 *W = ws.k1, *T = ws.k2, *T2 = ef > REFINE_SHORT ? ws.k3 : nullptr;
+      hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)G, W, kp, thr * thr);
+      CHASE_LAUNCH_CHECK();
+      CHASE_TRY(gemm_kp(0, kp, W, W, 0.0, T, ws, s));
+      if (T2) CHASE_TRY(gemm_kp(0, kp, T, T, 0.0, T2, ws, s));
+      hipLaunchKernelGGL(refine_w_kernel, dim3(blocks), dim3(256), 0, s, W, T, (const c128*)T2, kp);
+      CHASE_LAUNCH_CHECK();
+      if (T2) CHASE_TRY(gemm_kp(0, kp, T2, T, 1.0, W, ws, s));
+      CHASE_TRY(gemm_kp(0, kp, V, W, 0.0, T, ws, s));
+      CHASE_HIP(hipMemcpyAsync(V, T, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
+      if (of * ef <= 0.5 * thr) {  // what is left off the diagonal, and its shift, is below thr
+        converged = true;
+        break;
+      }
+      CHASE_TRY(gemm_kp(0, kp, G, W, 0.0, T, ws, s));
+      CHASE_TRY(gemm_kp(1, kp, W, T, 0.0, G, ws, s));
+      continue;
+    }
     for (int r = 0; r < nbj - 1; ++r) {
       hipLaunchKernelGGL(jacobi_sub_kernel, dim3(npair), dim3(256), 0, s, (const c128*)G, (int64_t)kp, nbj, r,
-                         ws.U, thr, inner_sweeps, ws.flag, ws.pflag);
+                         ws.U, thr, inner_sweeps, ws.pflag);
       CHASE_LAUNCH_CHECK();
       const int blocks = npair * (npair + 1) / 2 + npair * (kp / SP);
       hipLaunchKernelGGL(jacobi_apply_kernel, dim3(blocks), dim3(256), 0, s, G, V, (int64_t)kp, kp, nbj, r,
                          (const c128*)ws.U, (const int*)ws.pflag);
       CHASE_LAUNCH_CHECK();
-    }
-    // the sweep rotated: stop if no off-diagonal entry is left above thr
-    // (the next sweep would then leave G and V unchanged)
-    hipLaunchKernelGGL(offdiag_above_kernel, dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)kp * kp, 256), 1024)),
-                       dim3(256), 0, s, (const c128*)G, kp, thr * thr, ws.flag + 1);
-    CHASE_LAUNCH_CHECK();
-    int cnt[2] = {0, 0};
-    CHASE_TRY(d2h_small(cnt, ws.flag, 2 * sizeof(int), ws, s));
-    if (cnt[0] == 0 || cnt[1] == 0) {
-      if (cnt[0] != 0) ++sweep;  // count the sweep that rotated
-      converged = true;
-      break;
     }
   }
   if (sweeps_out) *sweeps_out = sweep;

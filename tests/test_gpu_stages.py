@@ -430,6 +430,29 @@ def test_rr_reports_an_unconverged_jacobi_eigensolver(prob):
     s40.close()
 
 
+@pytest.mark.parametrize("kh", [6, 32])
+@pytest.mark.parametrize("eps", [1e-2, 1e-3, 1e-5, 1e-8, 1e-13])
+def test_rr_near_diagonal_quotient(prob, solver80, kh, eps):
+    # a search block eps away from an invariant subspace: the quotient starts
+    # nearly diagonal, so GEMM refinement steps take the place of some or all
+    # of the Jacobi sweeps.  Same bounds as for a random block.
+    print_case("rr_near_diagonal", m=prob.m, k=2 * kh, eps=eps)
+    lam, Vp = dense.dense_ph_eig(prob.A, prob.B)
+    X = np.concatenate([Vp[:, :kh], ham.apply_k_conj(Vp[:, :kh])], axis=1)
+    X = X / np.linalg.norm(X, axis=0)
+    X = X + eps * complex_normal(np.random.default_rng(kh), X.shape) / np.sqrt(prob.n)
+    Q, _, _ = oqr.cholqr2(X)
+    lam_ref, _, _ = rayleigh_ritz.oblique_rr(prob.A, prob.B, Q)
+    ritz, Z, T = solver80.oblique_rr(to_dev(Q))
+    assert np.allclose(ritz, lam_ref, rtol=1e-11, atol=0)
+    Vh = to_host(solver80.residuals(to_dev(Q), T, Z, ritz)[0])
+    R = ham.apply_h(prob.A, prob.B, Vh) - Vh * ritz[None, :]
+    assert np.max(np.abs(Q.conj().T @ ham.apply_s(R))) < 1e-11
+    G = Vh.conj().T @ ham.apply_s(ham.apply_h(prob.A, prob.B, Vh))  # V^H S H V is diagonal
+    d = np.sqrt(np.abs(np.diag(G)))
+    assert np.max(np.abs(G / np.outer(d, d) - np.eye(kh))) < 1e-11
+
+
 def _unit_ritz(Q, Z):
     V = Q @ Z
     return V / np.linalg.norm(V, axis=0)[None, :]
