@@ -33,12 +33,13 @@
 // the team's XCD once.  Two workgroups per CU in all.  A part may start or end
 // inside a strip; the partial sums of such a strip go to a workspace and a
 // second kernel adds them in K order and applies the epilogue, so results do
-// not depend on timing.
+// not depend on timing.  Short products (short_shape) run in one launch of
+// hx_short_kernel instead, where the waves of a workgroup share K.
 //
 // Bound by the FP64 MFMA for N >= 100 or so at m >= 4000 (below that by the
-// read of M), by latency at m <= 1000.  Measured per product of the filter
+// read of M), by latency at m <= 500.  Measured per product of the filter
 // (us; before: a kernel on LDS rings with barriers, packing before every
-// product): m = 500, k = 30: 13.7 (32.8 before); m = 2000, k = 70: 94 (114);
+// product): m = 500, k = 30: 6.5 (32.8 before); m = 2000, k = 70: 85 (114);
 // m = 4000, k = 256: 965 = 67.9 TF/s (1116); k = 376: 1418 (1765);
 // m = 10000, k = 512: 11463 = 71.5 TF/s, as much as MFMAs on registers alone.
 // M read by a team's workgroups in step, rather than by workgroups with parts
@@ -361,13 +362,102 @@ __global__ __launch_bounds__(256) void hx_reduce_kernel(const HxDev a) {
   for (int i = 0; i < FM; ++i) finish(a, row0 + 16 * i + 4 * (lane >> 4), 16 * cf + (lane & 15), v[i]);
 }
 
+// Short products in one launch, without partial sums in memory: a workgroup of
+// NW waves takes 16 FMS rows x 16 NL columns, each wave a share of K, KS slabs
+// a stage, loaded one stage ahead; the waves' sums are added in LDS in K order.
+// Bound by launch and load latency below m = 500 or so, above it by the MFMA
+// and the L1 in turn, at k <= 16 and m >= 3000 by the read of M (5.9 TB/s).
+// Few slabs a stage and many workgroups per CU hide the loads better than
+// long stages (KS = 4 for 2 where two fragments are shared: 3 - 10% slower).
+template <int FMS, int NL, int NW, int KS>
+__global__ __launch_bounds__(64 * NW) void hx_short_kernel(const HxDev a) {
+  __shared__ double red[NW][FMS * NL][2][64][2];
+  const int id = xcd_remap(blockIdx.x, gridDim.x);
+  const int strip = id / a.TN, ct = id - strip * a.TN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = lane >> 4, lc = lane & 15;
+  const int row0 = strip * 16 * FMS, cb = ct * NL;
+  const doublex2* mp = reinterpret_cast<const doublex2*>(a.M + (int64_t)(row0 / WROWS) * a.wstep) +
+                       (row0 / 16 % FM) * 64 + lane;
+  const double* yp = a.y + (g >> 1) * a.ldc4 + 4 * lc + 2 * (g & 1);
+  const int64_t ystep = (BK / 4) * a.ldc4;
+  int yo[NL];  // the last tile's fragments past column N repeat its last one
+#pragma unroll
+  for (int j = 0; j < NL; ++j) yo[j] = 64 * min(cb + j, (a.N - 1) / 16);
+  const int k0 = a.KB * wave / NW, k1 = a.KB * (wave + 1) / NW;  // slabs
+  doublex4 acc[FMS][NL];
+#pragma unroll
+  for (int i = 0; i < FMS; ++i)
+#pragma unroll
+    for (int j = 0; j < NL; ++j) acc[i][j] = doublex4{0, 0, 0, 0};
+  doublex2 fa[2][KS][FMS], fb[2][KS][NL];
+  auto load = [&](int k, doublex2 (&x)[KS][FMS], doublex2 (&y)[KS][NL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+      const int64_t kk = min(k + q, k1 - 1);
+#pragma unroll
+      for (int i = 0; i < FMS; ++i) x[q][i] = mp[kk * (FM * 64) + i * 64];
+#pragma unroll
+      for (int j = 0; j < NL; ++j) y[q][j] = *reinterpret_cast<const doublex2*>(yp + kk * ystep + yo[j]);
+    }
+  };
+  auto mul = [&](int k, const doublex2 (&x)[KS][FMS], const doublex2 (&y)[KS][NL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < KS; ++q)
+      if (k + q < k1) {
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+#pragma unroll
+          for (int i = 0; i < FMS; ++i)
+#pragma unroll
+            for (int j = 0; j < NL; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[q][i][v], y[q][j][v], acc[i][j], 0, 0, 0);
+      }
+  };
+  if (k0 < k1) {
+    load(k0, fa[0], fb[0]);
+#pragma unroll 1
+    for (int k = k0; k < k1; k += 2 * KS) {
+      load(k + KS, fa[1], fb[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(k, fa[0], fb[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      load(k + 2 * KS, fa[0], fb[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      mul(k + KS, fa[1], fb[1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < FMS; ++i)
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<doublex2*>(red[wave][i * NL + j][h][lane]) = doublex2{acc[i][j][2 * h], acc[i][j][2 * h + 1]};
+  __syncthreads();
+#pragma unroll 1
+  for (int f = wave; f < FMS * NL; f += NW) {
+    doublex4 v{0, 0, 0, 0};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const doublex2 x = *reinterpret_cast<const doublex2*>(red[w][f][0][lane]),
+                     y = *reinterpret_cast<const doublex2*>(red[w][f][1][lane]);
+      v += doublex4{x[0], x[1], y[0], y[1]};
+    }
+    finish(a, row0 + 16 * (f / NL) + 4 * g, 16 * (cb + f % NL) + lc, v);
+  }
+}
+
 // ---------------------------------------------------------------- plan
 // CHASE_PH_APPLY_PLAN="w,splits" forces tiles of at most 8 >> w column
-// fragments and about `splits` parts per tile, so that every tile width and
-// split can be checked for parity on one problem.
+// fragments and about `splits` parts per tile, w = 4 .. 9 the short product's
+// shape w - 4, so that every tile width, split and shape can be checked for
+// parity on one problem.
 bool plan_override(int* w, int* splits) {
   const char* e = std::getenv("CHASE_PH_APPLY_PLAN");
-  return e && std::sscanf(e, "%d,%d", w, splits) == 2 && *w >= 0 && *w <= 3 && *splits >= 1;
+  return e && std::sscanf(e, "%d,%d", w, splits) == 2 && *w >= 0 && *w <= 9 && *splits >= 1;
 }
 
 // Cuts NB column fragments into TN tiles and the strips' K range into parts
@@ -381,50 +471,82 @@ void set_tiles(HxDev& a, int NB, int TN) {
   a.slot = (int64_t)BM * 16 * a.wmax;
 }
 
+// Column tiles of a long product and the estimate of its time: a team's widest
+// tile, where the padding of unequal tiles shows, plus the partial sums (at
+// 12 TB/s, mostly from the Infinity Cache).  Tiles of fewer than 5 fragments
+// read more per MFMA.  m = 4000: k = 130 (17 fragments) 549 us on 3 tiles, 573
+// on 5, 597 on 4; k = 260 (33) 1037 on 5, 1071 on 6.
+double long_plan(const HxDev& a, int* tn) {
+  const int NB = (int)ceil_div(a.N, (int64_t)16);
+  const int64_t slabs = ceil_div(a.rows2, (int64_t)BM) * ceil_div(a.rows2, (int64_t)BK);
+  const double frag_us = FM * V * 64 / 2400.0;  // MFMA time of one slab and column fragment
+  static const double narrow[5] = {0, 1.2, 1.12, 1.06, 1.05};
+  const int t0 = (int)ceil_div(NB, (int64_t)MAX_NL);
+  double best = 1e300;
+  for (int t = t0; t <= std::min(NB, 3 * t0); ++t) {
+    const int w = (int)ceil_div(NB, (int64_t)t), teams = std::max(1, MAX_WG / t);
+    const double us = slabs * frag_us * w * (w < 5 ? narrow[w] : 1.0) / teams +
+                      2.0 * BM * 16 * w * t * teams * sizeof(double) / 12e6;
+    if (us < best) {
+      best = us;
+      *tn = t;
+    }
+  }
+  return best;
+}
+
+// Shapes (FMS, NL) of hx_short_kernel.
+constexpr int SHORT_SHAPES = 6;
+constexpr int short_f[SHORT_SHAPES] = {1, 1, 2, 2, 2, 2}, short_n[SHORT_SHAPES] = {1, 2, 1, 2, 3, 4};
+
+// The shape that computes a short product soonest, or -1 if teams on long
+// parts do.  A CU's workgroups each cost 10.6 ns per slab and fragment pair
+// (MFMA) and 5.8 per fragment loaded (L1), on top of 3.6 us; M comes from the
+// caches at 10 TB/s or so, from HBM at 6 (4.5 where a workgroup reads only
+// half of a 32-row group).  Whole workgroups per CU count: that is what the
+// teams' equal parts avoid, at the price of a second launch and of partial
+// sums (5 us and 2.3 times the estimate of long_plan, M at 4.8 TB/s).  Measured
+// (us a product; teams / this): m = 100, k = 30 11.9 / 4.0; m = 500, k = 30
+// 15.1 / 6.5; m = 1000, k = 120 46.2 / 35.4; m = 2000, k = 35 61.0 / 53.2, k = 70
+// 85.2 / 91; m = 3000, k = 35 111 / 128; m = 4000, k = 4 107 / 91, k = 32
+// 158 / 136.
+int short_shape(const HxDev& a) {
+  int w = 0, splits = 0;
+  if (plan_override(&w, &splits)) return w < 4 ? -1 : w - 4;
+  const double slabs = (double)ceil_div(a.rows2, (int64_t)BK);
+  const double bytes = 8.0 * a.rows2 * a.rows2 * 1e-6;
+  const bool cached = bytes < 256;
+  int tn = 0, shape = -1;
+  auto overlap = [](double x, double y) { return std::max(x, y) + 0.2 * std::min(x, y); };
+  double best = overlap(5.0 + 2.3 * long_plan(a, &tn), bytes / 4.8);
+  for (int c = 0; c < SHORT_SHAPES; ++c) {
+    const int f = short_f[c], n = short_n[c];
+    const int64_t rounds = ceil_div(ceil_div(a.rows2, (int64_t)(16 * f)) * ceil_div(a.N, (int64_t)(16 * n)),
+                                    (int64_t)(MAX_WG / 2));
+    if (rounds > 4) continue;
+    const double comp = 3.6 + slabs * rounds * (f * n * 0.0106 + (f + n) * 0.0058);
+    const double mem = bytes / (cached ? 10.0 : f == 1 ? 4.5 : 6.0);
+    const double us = overlap(comp, mem);
+    if (us < best) {
+      best = us;
+      shape = c;
+    }
+  }
+  return shape;
+}
+
 void make_plan(HxDev& a, size_t ws_bytes) {
   const int NB = (int)ceil_div(a.N, (int64_t)16);
   a.TM = (int)ceil_div(a.rows2, (int64_t)BM);
-  const int64_t slabs = (int64_t)a.TM * ceil_div(a.rows2, (int64_t)BK);
-  const double frag_us = FM * V * 64 / 2400.0;  // MFMA time of one slab and column fragment
   auto most = [](int TN) { return std::max<int64_t>(1, MAX_WG / TN); };
   int force_w = 0, force_s = 0;
   int64_t teams;
   if (plan_override(&force_w, &force_s)) {
     set_tiles(a, NB, (int)ceil_div(NB, (int64_t)(MAX_NL >> force_w)));
     teams = std::min((int64_t)a.TM * force_s, most(a.TN));
-  } else if (slabs * NB * frag_us < 12.0 * MAX_WG) {
-    // Short products (MFMA time below 12 us on the whole chip), bound by
-    // latency and by the partial sums: tiles of one fragment, and 2^p parts
-    // per strip so that all of them have the same length.  A part costs t / n
-    // of MFMA time and b of partial-sum traffic (at 4 TB/s), least at
-    // n = sqrt(t / b); 0.6 of that measured best.  m = 500, k = 30: 12.6 us a
-    // product, 17.4 on one tile of four fragments; m = 1000, k = 60: 30.0
-    // against 38.3 (8 fragments).
-    set_tiles(a, NB, NB);
-    const double t = slabs * frag_us, b = 2.0 * a.slot * NB * sizeof(double) / 4e6;
-    const double per_strip = 0.6 * std::sqrt(t / b) / a.TM;
-    const int p = std::max(0, (int)std::lround(std::log2(per_strip)));
-    teams = std::min((int64_t)a.TM << std::min(p, 10), most(NB));
   } else {
-    // Long products: all workgroups, and the tile count with the least time
-    // of a team: its widest tile, where the padding of unequal tiles shows,
-    // plus the partial sums (at 12 TB/s, mostly from the Infinity Cache).
-    // Tiles of fewer than 5 fragments read more per MFMA.  m = 4000: k = 130
-    // (17 fragments) 549 us on 3 tiles, 573 on 5, 597 on 4; k = 260 (33)
-    // 1037 on 5, 1071 on 6.
-    static const double narrow[5] = {0, 1.2, 1.12, 1.06, 1.05};
-    const int t0 = (int)ceil_div(NB, (int64_t)MAX_NL);
-    double best = 1e300;
-    int tn = t0;
-    for (int t = t0; t <= std::min(NB, 3 * t0); ++t) {
-      const int w = (int)ceil_div(NB, (int64_t)t);
-      const double us = slabs * frag_us * w * (w < 5 ? narrow[w] : 1.0) / most(t) +
-                        2.0 * BM * 16 * w * t * most(t) * sizeof(double) / 12e6;
-      if (us < best) {
-        best = us;
-        tn = t;
-      }
-    }
+    int tn = 1;
+    long_plan(a, &tn);
     set_tiles(a, NB, tn);
     teams = most(tn);
   }
@@ -445,6 +567,31 @@ void make_plan(HxDev& a, size_t ws_bytes) {
 }
 
 Err launch(HxDev& a, void* ws, size_t ws_bytes, hipStream_t s) {
+  const int shape = short_shape(a);
+  if (shape >= 0) {
+    auto go = [&](auto F, auto NL, auto NW, auto KS) {
+      constexpr int f = decltype(F)::value, nl = decltype(NL)::value, nw = decltype(NW)::value;
+      a.TN = (int)ceil_div(a.N, (int64_t)(16 * nl));
+      a.KB = (int)ceil_div(a.rows2, (int64_t)BK);
+      const unsigned blocks = (unsigned)(ceil_div(a.rows2, (int64_t)(16 * f)) * a.TN);
+      hipLaunchKernelGGL((hx_short_kernel<f, nl, nw, decltype(KS)::value>), dim3(blocks), dim3(64 * nw), 0, s, a);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using I4 = std::integral_constant<int, 4>;
+    using I8 = std::integral_constant<int, 8>;
+    switch (shape) {
+      case 0: go(I1{}, I1{}, I4{}, I4{}); break;
+      case 1: go(I1{}, I2{}, I4{}, I2{}); break;
+      case 2: go(I2{}, I1{}, I4{}, I2{}); break;
+      case 3: go(I2{}, I2{}, I4{}, I2{}); break;
+      case 4: go(I2{}, I3{}, I4{}, I2{}); break;
+      default: go(I2{}, I4{}, I8{}, I1{}); break;
+    }
+    CHASE_LAUNCH_CHECK();
+    return ok();
+  }
   a.ws = (double*)ws;
   make_plan(a, ws ? ws_bytes : 0);
   const dim3 grid((unsigned)(a.teams * a.TN)), block(256);

@@ -627,6 +627,38 @@ def test_filter_fp64_every_tile_plan(prob, plan, monkeypatch):
     assert np.max(err) < 1e-11, err
 
 
+# every shape of the short products, at sizes with fewer K slabs of 8 than a
+# workgroup has waves (m = 5), a last strip and a last column tile that are cut
+# off (m = 13, 75) and full ones (m = 64, 2 k = 64), general and K-real
+# columns, through the plain and the recurrence's epilogue
+@pytest.mark.parametrize("plan", ["4,1", "5,1", "6,1", "7,1", "8,1", "9,1"])
+@pytest.mark.parametrize("m,k", [(5, 2), (13, 9), (64, 32), (75, 41), (75, 57)])
+def test_short_products_every_shape(m, k, plan, monkeypatch):
+    print_case("short_products", m=m, k=k, plan=plan)
+    monkeypatch.setenv("CHASE_PH_APPLY_PLAN", plan)
+    p = problem(m=m, seed=m, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, k, 0)
+    rng = np.random.default_rng(m + k)
+    X = complex_normal(rng, (p.n, k))
+    ref = ham.apply_h(p.A, p.B, X)
+    assert np.max(np.abs(to_host(s.apply_h(to_dev(X))) - ref)) <= 1e-12 * np.max(np.abs(ref))
+    a = complex_normal(rng, (m, k))
+    X = np.concatenate([a, a.conj()], axis=0)
+    ref = ham.apply_h(p.A, p.B, X)
+    Y = to_host(s.apply_h(to_dev(X), prec=_lib.FP64_KREAL))
+    assert np.max(np.abs(Y - ref)) <= 1e-12 * np.max(np.abs(ref))
+    mu1, mu_nevex, mu_n = 0.9, 2.0, 1.2 * np.max(np.linalg.eigvalsh(ham.assemble_sh(p.A, p.B)))
+    W = complex_normal(rng, (p.n, k))
+    degs = [2] * (k // 2) + [5] * (k - k // 2)
+    Wd = to_dev(W)
+    s.filter(Wd, mu1, mu_nevex, mu_n, degs=degs, prec=FP64)
+    ref = chebyshev.chebyshev_filter(p.A, p.B, W, np.array(degs), mu1, mu_nevex, mu_n)
+    err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.max(err) < 1e-11, err
+    s.close()
+
+
 # c128 GEMMs of the QR and Rayleigh-Ritz steps: sizes around the 32-row waves,
 # the 64-row tiles and the 8-row K slabs, with odd m (K and the sign flip of S
 # end inside a slab), against the oracle at the tolerances of the larger cases
