@@ -140,13 +140,8 @@ Err dalloc(chase_ph_t h, T** p, size_t count) {
   return ok();
 }
 
-// Small host-to-device copy from pageable host memory; waits for it so the
-// host buffer may be released right after.
-Err h2d(chase_ph_t h, void* dst, const void* src, size_t bytes) {
-  CHASE_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, h->st));
-  CHASE_HIP(hipStreamSynchronize(h->st));
-  return ok();
-}
+// Small host-to-device copy; the host buffer may be released right after.
+Err h2d(chase_ph_t h, void* dst, const void* src, size_t bytes) { return h2d_small(dst, src, bytes, h->st); }
 
 // Structure flags of gemm(): see ZgemmArgs.
 constexpr int GEMM_LOWER_ONLY = 1, GEMM_A_LOWER = 2, GEMM_B_UPPER = 4, GEMM_REAL = 8;
@@ -486,8 +481,18 @@ Err check_filter_args(chase_ph_t h, int k, int64_t ldw, const int32_t* degs, dou
   return ok();
 }
 
+// e0 .. e1 of the last filter_any as chase_ph_last_timing's time; waits for e1.
+Err read_timing(chase_ph_t h) {
+  CHASE_HIP(hipEventSynchronize(h->e1));
+  float ms = 0;
+  CHASE_HIP(hipEventElapsedTime(&ms, h->e0, h->e1));
+  h->last_ms = ms;
+  return ok();
+}
+
+// wait = false: the caller reads the timing later (read_timing).
 Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
-               double mu_n, int prec, double* flops) {
+               double mu_n, int prec, double* flops, bool wait = true) {
   if (k == 0) return ok();
   int launches = 0;
   double fl = 0;
@@ -499,13 +504,9 @@ Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int
     CHASE_TRY(filter64(h, k, (c128*)dW, ldw, d, mu1, mu_nevex, mu_n, &launches, &fl));
   }
   CHASE_HIP(hipEventRecord(h->e1, h->st));
-  CHASE_HIP(hipEventSynchronize(h->e1));
-  float ms = 0;
-  CHASE_HIP(hipEventElapsedTime(&ms, h->e0, h->e1));
-  h->last_ms = ms;
   h->last_launches = launches;
   if (flops) *flops = fl;
-  return ok();
+  return wait ? read_timing(h) : ok();
 }
 
 // One Cholesky-QR pass: Xout = Xin L^{-H} with L L^H = Xin^H Xin + shift I.
@@ -517,15 +518,25 @@ Err gram_lower(chase_ph_t h, int k, int kp, const c128* X, int64_t ldx, c128* Lb
               GEMM_LOWER_ONLY | (real ? GEMM_REAL : 0));
 }
 
+// Breakdown of the factorisation: *failed, and Xout untouched.  With
+// failed = null the pass does not wait to see it: it is in flag CHOL, and
+// Xout unspecified then; a later call's failed_first reads it.
 Err cholqr_pass(chase_ph_t h, int k, int kp, const c128* Xin, int64_t ldin, c128* Xout, int64_t ldout, c128* Lbuf,
-                double shift, bool* failed, bool real = false, int64_t rows = 0, bool gram_ready = false) {
+                double shift, bool* failed, bool real = false, int64_t rows = 0, bool gram_ready = false,
+                bool* failed_first = nullptr) {
   const int rf = real ? GEMM_REAL : 0;
   const int64_t nr = rows > 0 ? rows : h->n;
   // Gram matrix: the Cholesky reads its lower triangle only
   if (!gram_ready) CHASE_TRY(gram_lower(h, k, kp, Xin, ldin, Lbuf, real, nr));
   if (shift != 0.0) CHASE_TRY(add_diag(Lbuf, kp, k, shift, h->st));
-  CHASE_TRY(cholesky_inverse(Lbuf, h->Li, kp, h->dws, h->st, failed));
-  if (*failed) return ok();
+  CHASE_TRY(cholesky_inverse(Lbuf, h->Li, kp, h->dws, h->st, failed ? DenseWs::CHOL2 : DenseWs::CHOL));
+  if (failed) {
+    int f[2] = {0, 0};
+    CHASE_TRY(d2h_small(f, h->dws.flag + DenseWs::CHOL, sizeof(f), h->dws, h->st));
+    if (failed_first) *failed_first = f[0] != 0;
+    *failed = f[1] != 0;
+    if (*failed || (failed_first && *failed_first)) return ok();
+  }
   return gemm(h, 0, 1, nr, k, k, {1, 0}, Xin, ldin, h->Li, kp, {0, 0}, Xout, ldout, -1, GEMM_B_UPPER | rf);
 }
 
@@ -552,43 +563,51 @@ Err householder_fallback(chase_ph_t h, int k, c128* X, int64_t ldx, c128* R, int
 // passes of the shifted variant, on their output (same leading spans).
 // With householder = false the breakdown is only reported (*used_shift = 2,
 // X unspecified): the solver then orthonormalises the K-real form instead.
-// rows: rows of X (0: n).
+// rows: rows of X (0: n).  result: the caller takes Q from *result (X, or Xt
+// with that many rows as pitch) and X is then unspecified.
 Err qr_impl(chase_ph_t h, int k, c128* X, int64_t ldx, c128* R, int64_t ldr, int* used_shift,
-            bool householder = true, bool real = false, int64_t rows = 0) {
+            bool householder = true, bool real = false, int64_t rows = 0, const c128** result = nullptr) {
   if (used_shift) *used_shift = 0;
   h->qr_one_pass = false;
+  if (result) *result = X;
   if (k == 0) return ok();
   const int kp = pad64(k);
   const int64_t n = rows > 0 ? rows : h->n;
-  bool failed = false;
-  CHASE_TRY(cholqr_pass(h, k, kp, X, ldx, h->Xt, n, h->L1, 0.0, &failed, real, n));
+  // The first pass leaves X as it is, so whether it broke down is read with
+  // the next number that the host waits for.
+  bool failed = false, failed1 = false;
+  CHASE_TRY(cholqr_pass(h, k, kp, X, ldx, h->Xt, n, h->L1, 0.0, nullptr, real, n));
   int nf = 2;
-  if (!failed && !R) {
+  if (!R) {
     // Section 2 chooses the orthonormalisation by condition number: when
     // the first pass already left Q^H Q within QR_ONE_PASS of I (a
     // well-conditioned block), the second pass is skipped
     CHASE_TRY(gram_lower(h, k, kp, h->Xt, n, h->L2, real, n));
     CHASE_TRY(gram_deviation(h->L2, kp, k, h->dres, h->dws.dscalar, h->st));
     double dev = 0;
-    CHASE_TRY(d2h_small(&dev, h->dws.dscalar, sizeof(double), h->dws, h->st));
-    if (dev <= QR_ONE_PASS) {
+    int f = 0;
+    CHASE_TRY(d2h_small(&dev, h->dws.dscalar, sizeof(double), h->dws, h->st, &f, h->dws.flag + DenseWs::CHOL,
+                        sizeof(int)));
+    failed1 = f != 0;
+    if (!failed1 && dev <= QR_ONE_PASS) {
       h->qr_one_pass = true;
+      if (result) {
+        *result = h->Xt;
+        return ok();
+      }
       CHASE_HIP(hipMemcpy2DAsync(X, ldx * sizeof(c128), h->Xt, n * sizeof(c128), n * sizeof(c128), k,
                                  hipMemcpyDeviceToDevice, h->st));
       return ok();
     }
-    CHASE_TRY(cholqr_pass(h, k, kp, h->Xt, n, X, ldx, h->L2, 0.0, &failed, real, n, true));
-    if (failed) {
-      if (used_shift) *used_shift = 2;
-      return householder ? householder_fallback(h, k, X, ldx, R, ldr, 0, n) : ok();
-    }
-  } else if (!failed) {
-    CHASE_TRY(cholqr_pass(h, k, kp, h->Xt, n, X, ldx, h->L2, 0.0, &failed, real, n));
-    if (failed) {
-      if (used_shift) *used_shift = 2;
-      return householder ? householder_fallback(h, k, X, ldx, R, ldr, 0, n) : ok();
-    }
+    if (!failed1) CHASE_TRY(cholqr_pass(h, k, kp, h->Xt, n, X, ldx, h->L2, 0.0, &failed, real, n, true));
   } else {
+    CHASE_TRY(cholqr_pass(h, k, kp, h->Xt, n, X, ldx, h->L2, 0.0, &failed, real, n, false, &failed1));
+  }
+  if (!failed1 && failed) {
+    if (used_shift) *used_shift = 2;
+    return householder ? householder_fallback(h, k, X, ldx, R, ldr, 0, n) : ok();
+  }
+  if (failed1) {
     if (used_shift) *used_shift = 1;
     // shifted CholeskyQR3: s = 11 (n k + k (k + 1)) u ||X||_F^2
     CHASE_TRY(fill_padded(h->G, kp, k, 0.0, 1.0, true, h->st));
@@ -734,9 +753,7 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
   CHASE_TRY(fill_padded(h->G, kp, k, 0.0, 1.0, true, h->st));
   CHASE_TRY(gemm(h, 1, 0, k, k, n, {1, 0}, Q, ldq, T, ldt, {0, 0}, h->G, kp, m,
                  GEMM_LOWER_ONLY));  // M = Q^H S T (Hermitian; the Cholesky reads the lower triangle)
-  bool failed = false;
-  CHASE_TRY(cholesky_inverse(h->G, h->Li, kp, h->dws, h->st, &failed));      // L L^H = M, and L^{-1}
-  if (failed) return fail(CHASE_PH_ERR_NOT_DEFINITE, "Cholesky of Q^H S H Q failed (SH not positive definite on range(Q))");
+  CHASE_TRY(cholesky_inverse(h->G, h->Li, kp, h->dws, h->st, DenseWs::CHOL));  // L L^H = M, and L^{-1}
   CHASE_TRY(fill_padded(h->Nb, kp, k, 1.0, 0.0, true, h->st));              // N = I - 2 Q2^H Q2
   CHASE_TRY(gemm(h, 1, 0, k, k, m, {-2, 0}, Q + m, ldq, Q + m, ldq, {1, 0}, h->Nb, kp));
   CHASE_TRY(gemm(h, 0, 1, kp, kp, kp, {1, 0}, h->Nb, kp, h->Li, kp, {0, 0}, h->Tk, kp, -1,
@@ -744,10 +761,17 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
   CHASE_TRY(gemm(h, 0, 0, kp, kp, kp, {1, 0}, h->Li, kp, h->Tk, kp, {0, 0}, h->G, kp, -1,
                  GEMM_A_LOWER));  // L^{-1} N L^{-H}
   int sweeps = 0;
-  CHASE_TRY(jacobi_eigh(h->G, h->Ev, kp, h->dws, h->st, h->p.rr_max_sweeps, &sweeps));
+  bool failed = false;  // the factorisation above, read with the eigensolver's first check
+  CHASE_TRY(jacobi_eigh(h->G, h->Ev, kp, h->dws, h->st, h->p.rr_max_sweeps, &sweeps, DenseWs::CHOL, &failed));
+  if (failed) return fail(CHASE_PH_ERR_NOT_DEFINITE, "Cholesky of Q^H S H Q failed (SH not positive definite on range(Q))");
   h->last_sweeps = sweeps;
-  int npos = 0, nneg = 0;
-  CHASE_TRY(select_positive(h->G, h->Ev, k, kp, h->Ys, h->dlam, h->dws, h->st, &npos, &nneg));
+  CHASE_TRY(select_positive(h->G, h->Ev, k, kp, h->Ys, h->dlam, h->dws, h->st));
+  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, Zpos, ldz));  // Z = L^{-H} Y
+  int cnt[2] = {0, 0};
+  std::vector<double> lam(ritz ? k / 2 : 0);
+  CHASE_TRY(d2h_small(lam.data(), h->dlam, sizeof(double) * lam.size(), h->dws, h->st, cnt,
+                      h->dws.flag + DenseWs::COUNTS, sizeof(cnt)));
+  const int npos = cnt[0], nneg = cnt[1];
   if ((npos != k / 2 || nneg != k / 2) && backup == 0) {
     if (used_backup) *used_backup = true;
     return rr_backup(h, k, Q, ldq, T, ldt, ritz, Zpos, ldz);
@@ -756,10 +780,7 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
     return fail(CHASE_PH_ERR_SINGULAR_QSQ, "Q^H S Q numerically singular: " + std::to_string(npos) + " positive / " +
                                                std::to_string(nneg) + " negative resolved Ritz values for k = " +
                                                std::to_string(k));
-  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, Zpos, ldz));  // Z = L^{-H} Y
-  if (ritz) {
-    CHASE_TRY(d2h_small(ritz, h->dlam, sizeof(double) * (k / 2), h->dws, h->st));
-  }
+  std::copy(lam.begin(), lam.end(), ritz);
   return ok();
 }
 
@@ -1077,27 +1098,44 @@ Err filter_tda(chase_ph_t h, int k, c128* W, int64_t ldw, int deg, double mu1, d
 // Phase timer on its own event pair (the stage calls it brackets record
 // the handle's e0/e1 for chase_ph_last_timing).
 struct Timer {
+  struct Span {
+    hipEvent_t a, b;
+    double* acc;
+  };
   chase_ph_t h;
-  hipEvent_t a = nullptr, b = nullptr;
+  std::vector<Span> spans;  // the first `used` hold times not yet added
+  size_t used = 0;
   explicit Timer(chase_ph_t hh) : h(hh) {}
   ~Timer() {
-    if (a) (void)hipEventDestroy(a);
-    if (b) (void)hipEventDestroy(b);
+    for (Span& s : spans) {
+      if (s.a) (void)hipEventDestroy(s.a);
+      if (s.b) (void)hipEventDestroy(s.b);
+    }
   }
   Err start() {
-    if (!a) {
-      CHASE_HIP(hipEventCreate(&a));
-      CHASE_HIP(hipEventCreate(&b));
+    if (used == spans.size()) {
+      spans.push_back(Span{nullptr, nullptr, nullptr});
+      CHASE_HIP(hipEventCreate(&spans.back().a));
+      CHASE_HIP(hipEventCreate(&spans.back().b));
     }
-    CHASE_HIP(hipEventRecord(a, h->st));
+    CHASE_HIP(hipEventRecord(spans[used].a, h->st));
     return ok();
   }
+  // The time is added to *acc by collect(): a wait here would keep the next
+  // stage's launches from being queued.
   Err stop(double* acc) {
-    CHASE_HIP(hipEventRecord(b, h->st));
-    CHASE_HIP(hipEventSynchronize(b));
-    float ms = 0;
-    CHASE_HIP(hipEventElapsedTime(&ms, a, b));
-    *acc += ms * 1e-3;
+    CHASE_HIP(hipEventRecord(spans[used].b, h->st));
+    spans[used++].acc = acc;
+    return used < 64 ? ok() : collect();
+  }
+  Err collect() {
+    if (used > 0) CHASE_HIP(hipEventSynchronize(spans[used - 1].b));
+    for (size_t i = 0; i < used; ++i) {
+      float ms = 0;
+      CHASE_HIP(hipEventElapsedTime(&ms, spans[i].a, spans[i].b));
+      *spans[i].acc += ms * 1e-3;
+    }
+    used = 0;
     return ok();
   }
 };
@@ -1153,13 +1191,15 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
   int g0 = mixed ? 0 : nevex, g1 = 0;  // W columns: [mode 0 | mode 1 | mode 2]
   int hist_pos = 0;
   *converged = false;
+  bool filtered = false;
   for (int it = 0; it < p.max_iter; ++it) {
     const int kw = nevex - locked;
     double fl = 0;
     CHASE_TRY(tm.start());
     if (g0 > 0) {
       std::vector<int> d0(degs.begin(), degs.begin() + g0);
-      CHASE_TRY(filter_any(h, g0, h->Wk, n, d0, mu1, mu_nevex, mu_n, CHASE_PH_FP64, &fl));
+      CHASE_TRY(filter_any(h, g0, h->Wk, n, d0, mu1, mu_nevex, mu_n, CHASE_PH_FP64, &fl, false));
+      filtered = true;
       inf.filter_flops += fl;
       if (inf.switch_iter < 0 && mixed) inf.switch_iter = it;
     }
@@ -1177,7 +1217,8 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
       fl = 0;
       std::vector<int> d2(degs.begin() + c0, degs.begin() + kw);
       CHASE_TRY(convert_to_c64(h->Wk + (int64_t)c0 * n, n, h->W32, n, n, k32, h->st));
-      CHASE_TRY(filter_any(h, k32, h->W32, n, d2, mu1, mu_nevex, mu_n, CHASE_PH_FP32, &fl));
+      CHASE_TRY(filter_any(h, k32, h->W32, n, d2, mu1, mu_nevex, mu_n, CHASE_PH_FP32, &fl, false));
+      filtered = true;
       CHASE_TRY(convert_to_c128(h->W32, n, h->Wk + (int64_t)c0 * n, n, n, k32, h->st));
       inf.filter_flops_fp32 += fl;
       inf.filter_flops += fl;
@@ -1217,12 +1258,9 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
       }
     }
     int used = 0;
-    CHASE_TRY(qr_impl(h, kxn, h->Tq, n, nullptr, 0, &used, false, true));
-    if (used != 2) {
-      CHASE_TRY(kreal_unpack(h->Tq, n, m, kxn, h->st));
-      CHASE_HIP(hipMemcpy2DAsync(Xn, n * sizeof(c128), h->Tq, n * sizeof(c128), n * sizeof(c128), kxn,
-                                 hipMemcpyDeviceToDevice, h->st));
-    }
+    const c128* Qr = nullptr;
+    CHASE_TRY(qr_impl(h, kxn, h->Tq, n, nullptr, 0, &used, false, true, 0, &Qr));
+    if (used != 2) CHASE_TRY(kreal_unpack(Qr, n, Xn, n, m, kxn, h->st));
     if (used == 2) {
       // Numerically rank-deficient block: Householder QR of the real
       // coordinates of the K-real parts of all pairs, locked ones first, so
@@ -1255,7 +1293,7 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
         }
         CHASE_TRY(householder_qr(h->Xs, n, n, kall, nullptr, 0, h->hhw, h->st));
       }
-      CHASE_TRY(kreal_unpack(h->Xs, n, m, kall, h->st));
+      CHASE_TRY(kreal_unpack(h->Xs, n, h->Xs, n, m, kall, h->st));
     }
     lq = locked;
     inf.shifted_qr_used += used == 1;
@@ -1394,6 +1432,8 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
   CHASE_HIP(hipEventRecord(t1, h->st));
   CHASE_HIP(hipEventSynchronize(t1));
   float ms = 0;
+  CHASE_TRY(tm.collect());
+  if (filtered) CHASE_TRY(read_timing(h));
   CHASE_HIP(hipEventElapsedTime(&ms, t0, t1));
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
@@ -1548,6 +1588,7 @@ Err solve_tda_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, i
   CHASE_HIP(hipEventRecord(t1, h->st));
   CHASE_HIP(hipEventSynchronize(t1));
   float ms = 0;
+  CHASE_TRY(tm.collect());
   CHASE_HIP(hipEventElapsedTime(&ms, t0, t1));
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
@@ -1655,7 +1696,7 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   CHASE_TRY(dalloc(h, &h->dws.dscalar, 4));
   // pinned host staging for the small reads of every iteration (flags,
   // counts, Ritz values, residuals: at most kmax doubles)
-  h->dws.hpin_bytes = std::max<size_t>(4096, sizeof(double) * (size_t)h->kmax);
+  h->dws.hpin_bytes = std::max<size_t>(4096, sizeof(double) * (size_t)h->kmax) + 64;
   CHASE_HIP(hipHostMalloc(&h->dws.hpin, h->dws.hpin_bytes, hipHostMallocDefault));
   // zgemm split-K partials (up to 8 k x k blocks) and the partial tiles of
   // the H X products (two per workgroup: 128 MiB when all 512 take part,

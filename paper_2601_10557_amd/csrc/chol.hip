@@ -331,14 +331,13 @@ __global__ __launch_bounds__(NT) void chol_finish_kernel(c128* M, int64_t ld, in
 
 }  // namespace
 
-Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, bool* failed) {
-  CHASE_HIP(hipMemsetAsync(ws.flag, 0, sizeof(int), s));
-  CHASE_TRY(fill_padded(X, kp, kp, 0.0, 0.0, true, s));
+Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, int slot) {
+  CHASE_TRY(fill_padded(X, kp, kp, 0.0, 0.0, true, s, ws.flag + slot));
   for (int p = 0; p < kp; p += NB) {
     const int rest = kp - p - NB;
     const int nrow = rest / PB, ncol = p / PB;
     hipLaunchKernelGGL(chol_panel_kernel, dim3((unsigned)(1 + nrow + ncol)), dim3(NTP), 0, s, M, X, (int64_t)kp, p,
-                       nrow, ws.panel + (int64_t)p * NB, ws.flag);
+                       nrow, ws.panel + (int64_t)p * NB, ws.flag + slot);
     CHASE_LAUNCH_CHECK();
     if (rest <= 0) break;
     const int tiles = nrow * (nrow + 1) / 2 + nrow * (ncol + 4);
@@ -349,9 +348,6 @@ Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, bool*
   hipLaunchKernelGGL(chol_finish_kernel, dim3((unsigned)std::min<int64_t>(ceil_div((int64_t)kp * kp, NT), 2048)),
                      dim3(NT), 0, s, M, (int64_t)kp, kp, (const c128*)ws.panel);
   CHASE_LAUNCH_CHECK();
-  int f = 0;
-  CHASE_TRY(d2h_small(&f, ws.flag, sizeof(int), ws, s));
-  *failed = f != 0;
   return ok();
 }
 

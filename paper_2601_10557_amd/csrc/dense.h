@@ -9,38 +9,47 @@ struct DenseWs {
   c128* tmp = nullptr;     // kp_max x 64 (batched 64 x 64 blocks)
   c128* U = nullptr;       // kp_max x 64 (one rotation block per Jacobi pair)
   c128 *k1 = nullptr, *k2 = nullptr, *k3 = nullptr;  // kp_max x kp_max each (jacobi_eigh)
-  int* flag = nullptr;     // 4 ints
+  int* flag = nullptr;     // 4 ints: positives, negatives (select_positive), two Cholesky breakdowns
   int* pflag = nullptr;    // kp_max / 8 ints (Jacobi pair rotated?)
   double* dscalar = nullptr;  // 4 doubles
   void* gemm_ws = nullptr;     // split-K partials of the batched GEMMs (may be null)
   size_t gemm_ws_bytes = 0;
   void* hpin = nullptr;        // pinned host staging for small device-to-host reads (may be null)
   size_t hpin_bytes = 0;
+  enum { COUNTS = 0, CHOL = 2, CHOL2 = 3 };  // places in flag
 };
 
-// Copy bytes from device memory to host memory and wait for it: through the
-// pinned staging buffer of ws when it is large enough (a direct transfer,
-// no pageable staging on the runtime's side), else straight to host.
-Err d2h_small(void* host, const void* dev, size_t bytes, const DenseWs& ws, hipStream_t s);
+// Copy bytes (and bytes2) from device memory to host memory and wait for it:
+// a kernel stores them in the pinned staging buffer of ws when they fit there
+// (a runtime copy costs several times its launch), else by runtime copies.
+Err d2h_small(void* host, const void* dev, size_t bytes, const DenseWs& ws, hipStream_t s, void* host2 = nullptr,
+              const void* dev2 = nullptr, size_t bytes2 = 0);
+// Copy bytes of host memory to device memory; the host buffer is free on
+// return.  Up to 14 kB travel as kernel arguments, which needs no wait.
+Err h2d_small(void* dev, const void* host, size_t bytes, hipStream_t s);
 
 int pad64(int k);
 // M = diag(inner) on the first k, pad on the rest; off-diagonals zeroed
 // everywhere when zero_all, else only in the padded rows/columns.
-Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s);
+Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s,
+                int* clear = nullptr);  // *clear = 0 too
 // In place lower Cholesky of a Hermitian padded matrix (lower triangle given)
-// and X = L^{-1} (chol.hip; both ld kp); *failed on breakdown, both then
-// unspecified.
-Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, bool* failed);
+// and X = L^{-1} (chol.hip; both ld kp); ws.flag[slot] != 0 on breakdown, both
+// then unspecified.
+Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, int slot);
 // X = L^{-1} for lower-triangular L (both kp x kp, ld kp); X must not alias L.
 Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s);
 // G (Hermitian, in place) -> eigenvalues theta on the diagonal, V ->
 // eigenvectors, by block Jacobi sweeps and GEMM refinement steps, each counted
-// as a sweep.
-Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out);
+// as a sweep.  guard >= 0: if ws.flag[guard] is set, *tripped and nothing else.
+Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out,
+                int guard = -1, bool* tripped = nullptr);
 // Positive eigenvalues theta of the first k: Ysel (kp x k/2, ld kp) and
-// dlam[r] = 1/theta for rank r by descending theta.
+// dlam[r] = 1/theta for rank r by descending theta; the numbers of positive
+// and negative ones in ws.flag[COUNTS] and the next (columns of Ysel past the
+// first are unspecified).
 Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, double* dlam, DenseWs& ws,
-                    hipStream_t s, int* npos, int* nneg);
+                    hipStream_t s);
 
 // Householder QR (householder.hip): panels of HH_PANEL columns, row-parallel
 // launches of HH_PARTS one-wave workgroups.

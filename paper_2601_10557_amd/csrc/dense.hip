@@ -34,8 +34,10 @@ __device__ __forceinline__ c128 cfms(c128 r, c128 a, c128 b) {
 }
 
 // ---------------------------------------------------------------- fills
-__global__ void fill_diag_kernel(c128* M, int64_t ld, int kp, int k, double inner, double pad, int zero_all) {
+__global__ void fill_diag_kernel(c128* M, int64_t ld, int kp, int k, double inner, double pad, int zero_all,
+                                 int* clear) {
   const int64_t total = (int64_t)kp * kp;
+  if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(t / kp), i = (int)(t % kp);
     c128* p = M + (int64_t)j * ld + i;
@@ -480,7 +482,7 @@ __global__ __launch_bounds__(256) void jacobi_apply_kernel(c128* G, c128* V, int
 
 // Frobenius norm in two deterministic stages: one block per column writes the
 // column's sum of squares, then one block adds the kp column sums in a fixed
-// order.
+// order (and clears two counters).
 __global__ __launch_bounds__(256) void frob_cols_kernel(const c128* G, int64_t ld, int kp, double* part) {
   __shared__ double red[256];
   const int64_t col = blockIdx.x;
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(256) void frob_cols_kernel(const c128* G, int64_t l
   if (threadIdx.x == 0) part[col] = red[0];
 }
 
-__global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int kp, double* out) {
+__global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int kp, double* out, int* clear2) {
   __shared__ double red[256];
   double s = 0;
   for (int i = threadIdx.x; i < kp; i += 256) s += part[i];
@@ -509,14 +511,17 @@ __global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int k
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = sqrt(red[0]);
+  if (clear2 && threadIdx.x < 2) clear2[threadIdx.x] = 0;
 }
 
 // Select eigenvalues theta > 0 of the first k diagonal entries, order them
 // descending (ascending 1/theta), gather the matching eigenvector columns
 // (first kp rows) into Ysel and write lambda = 1/theta.  Counts positives and
 // negatives that are resolved away from zero.
-__global__ void select_kernel(const c128* G, const c128* V, int64_t ld, int k, int kp, double tiny,
+__global__ void select_kernel(const c128* G, const c128* V, int64_t ld, int k, int kp, const double* fro,
                               c128* Ysel, double* lam, int* npos, int* nneg) {
+  // 1e3 * u * max|theta| bounded by the Frobenius norm
+  const double tiny = 1e3 * 1.1102230246251565e-16 * *fro;
   const int i = blockIdx.x;
   if (i >= k) return;
   const double ti = G[(int64_t)i * ld + i].re;
@@ -544,29 +549,70 @@ __global__ void select_kernel(const c128* G, const c128* V, int64_t ld, int k, i
 }  // namespace
 
 // ---------------------------------------------------------------------------
-Err d2h_small(void* host, const void* dev, size_t bytes, const DenseWs& ws, hipStream_t s) {
-  if (bytes == 0) return ok();
-  void* dst = (ws.hpin && bytes <= ws.hpin_bytes) ? ws.hpin : host;
-  CHASE_HIP(hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, s));
+// Words of two device buffers into pinned host memory.
+__global__ __launch_bounds__(256) void to_host_kernel(const uint32_t* a, int na, const uint32_t* b, int nb,
+                                                      uint32_t* out) {
+  for (int i = threadIdx.x; i < na; i += 256) out[i] = a[i];
+  for (int i = threadIdx.x; i < nb; i += 256) out[na + i] = b[i];
+}
+
+struct HostWords {
+  uint32_t w[896];
+};
+__global__ __launch_bounds__(256) void from_host_kernel(uint32_t* dst, int n, const HostWords v) {
+  for (int i = threadIdx.x; i < n; i += 256) dst[i] = v.w[i];
+}
+
+Err d2h_small(void* host, const void* dev, size_t bytes, const DenseWs& ws, hipStream_t s, void* host2,
+              const void* dev2, size_t bytes2) {
+  if (bytes + bytes2 == 0) return ok();
+  if (ws.hpin && bytes + bytes2 <= ws.hpin_bytes && bytes % 4 == 0 && bytes2 % 4 == 0) {
+    hipLaunchKernelGGL(to_host_kernel, dim3(1), dim3(256), 0, s, (const uint32_t*)dev, (int)(bytes / 4),
+                       (const uint32_t*)dev2, (int)(bytes2 / 4), (uint32_t*)ws.hpin);
+    CHASE_LAUNCH_CHECK();
+    CHASE_HIP(hipStreamSynchronize(s));
+    if (bytes) std::memcpy(host, ws.hpin, bytes);
+    if (bytes2) std::memcpy(host2, (const char*)ws.hpin + bytes, bytes2);
+    return ok();
+  }
+  if (bytes) CHASE_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, s));
+  if (bytes2) CHASE_HIP(hipMemcpyAsync(host2, dev2, bytes2, hipMemcpyDeviceToHost, s));
   CHASE_HIP(hipStreamSynchronize(s));
-  if (dst != host) std::memcpy(host, dst, bytes);
+  return ok();
+}
+
+Err h2d_small(void* dev, const void* host, size_t bytes, hipStream_t s) {
+  HostWords v;
+  if (bytes % 4 || bytes > 4 * sizeof(v)) {
+    CHASE_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, s));
+    CHASE_HIP(hipStreamSynchronize(s));
+    return ok();
+  }
+  for (size_t o = 0; o < bytes; o += sizeof(v)) {
+    const size_t n = std::min(bytes - o, sizeof(v));
+    std::memcpy(v.w, (const char*)host + o, n);
+    hipLaunchKernelGGL(from_host_kernel, dim3(1), dim3(256), 0, s, (uint32_t*)((char*)dev + o), (int)(n / 4), v);
+    CHASE_LAUNCH_CHECK();
+  }
   return ok();
 }
 
 static int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 2048)); }
 
-static Err frob_norm(const c128* G, int kp, DenseWs& ws, hipStream_t s, double* host_out) {
+// dscalar[0] = ||G||_F
+static Err frob_norm(const c128* G, int kp, DenseWs& ws, hipStream_t s, int* clear2) {
   double* part = reinterpret_cast<double*>(ws.panel);  // kp doubles (panel holds kp x 64 c128)
   hipLaunchKernelGGL(frob_cols_kernel, dim3(kp), dim3(256), 0, s, G, (int64_t)kp, kp, part);
   CHASE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(frob_sum_kernel, dim3(1), dim3(256), 0, s, (const double*)part, kp, ws.dscalar);
+  hipLaunchKernelGGL(frob_sum_kernel, dim3(1), dim3(256), 0, s, (const double*)part, kp, ws.dscalar,
+                     clear2);
   CHASE_LAUNCH_CHECK();
-  return d2h_small(host_out, ws.dscalar, sizeof(double), ws, s);
+  return ok();
 }
 
-Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s) {
+Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s, int* clear) {
   hipLaunchKernelGGL(fill_diag_kernel, dim3(grid_for((int64_t)kp * kp)), dim3(256), 0, s, M, (int64_t)kp, kp, k,
-                     inner, pad, zero_all ? 1 : 0);
+                     inner, pad, zero_all ? 1 : 0, clear);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
@@ -605,11 +651,12 @@ Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s
 
 // Per column j of the Hermitian G, over the off-diagonal entries o:
 // part[j] = sum |o|^2, part[kp + j] = sum |e|^2 with e = o / (g_ii - g_jj) over
-// those with |o| > thr, part[2 kp + j] = 1 if there is one.
-__global__ __launch_bounds__(256) void offdiag_cols_kernel(const c128* G, int kp, double thr2, double* part) {
+// those with |o| > thr, part[2 kp + j] = 1 if there is one; thr = thr_of(*fro).
+__host__ __device__ inline double thr_of(double fro) { return 1e-16 * (fro < 1e-300 ? 1e-300 : fro); }
+__global__ __launch_bounds__(256) void offdiag_cols_kernel(const c128* G, int kp, const double* fro, double* part) {
   __shared__ double r1[256], r2[256];
   const int j = blockIdx.x;
-  const double dj = G[(int64_t)j * kp + j].re;
+  const double dj = G[(int64_t)j * kp + j].re, thr2 = thr_of(*fro) * thr_of(*fro);
   double so = 0, se = 0;
   int big = 0;
   for (int i = threadIdx.x; i < kp; i += 256) {
@@ -725,13 +772,12 @@ constexpr double REFINE_MAX = 0.04, REFINE_SHORT = 1e-4;
 // the last one, which leaves G alone, 100; a Rayleigh-Ritz step at m = 4000 and
 // k = 376 went from 5.06 ms to 4.41, one of the converging iterations at k = 500
 // (m = 4000) from 3 sweeps to 1 or 2.
-Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out) {
+Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out, int guard,
+                bool* tripped) {
   const int nbj = kp / JB;  // even since kp % 64 == 0
   const int npair = nbj / 2;
   CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s));
-  double fro = 0;
-  CHASE_TRY(frob_norm(G, kp, ws, s, &fro));
-  const double thr = 1e-16 * std::max(fro, 1e-300);
+  CHASE_TRY(frob_norm(G, kp, ws, s, nullptr));
   // One cyclic sweep per subproblem: block Jacobi with approximate
   // subproblem solutions needs about as many outer sweeps as with exact ones
   // and a fraction of the inner work.
@@ -740,14 +786,20 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   int sweep = 0;
   bool converged = false;
   for (;;) {
-    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)G, kp, thr * thr, part);
+    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)G, kp, (const double*)ws.dscalar,
+                       part);
     CHASE_LAUNCH_CHECK();
     hipLaunchKernelGGL(offdiag_sum_kernel, dim3(3), dim3(256), 0, s, (const double*)part, kp, ws.dscalar + 1);
     CHASE_LAUNCH_CHECK();
-    double st[3] = {0, 0, 0};
-    CHASE_TRY(d2h_small(st, ws.dscalar + 1, sizeof(st), ws, s));
-    const double of = std::sqrt(st[0]), ef = std::sqrt(st[1]);
-    if (st[2] == 0.0) {  // no off-diagonal entry above thr
+    double st[4] = {0, 0, 0, 0};
+    int bad = 0;
+    CHASE_TRY(d2h_small(st, ws.dscalar, sizeof(st), ws, s, &bad, ws.flag + guard, guard < 0 ? 0 : sizeof(int)));
+    if (bad) {
+      *tripped = true;
+      return ok();
+    }
+    const double thr = thr_of(st[0]), of = std::sqrt(st[1]), ef = std::sqrt(st[2]);
+    if (st[3] == 0.0) {  // no off-diagonal entry above thr
       converged = true;
       break;
     }
@@ -791,20 +843,12 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
 }
 
 Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, double* dlam, DenseWs& ws,
-                    hipStream_t s, int* npos, int* nneg) {
-  // tiny: 1e3 * u * max|theta| bounded by the Frobenius norm
-  double fro = 0;
-  CHASE_TRY(frob_norm(G, kp, ws, s, &fro));
-  const double tiny = 1e3 * 1.1102230246251565e-16 * fro;
-  CHASE_HIP(hipMemsetAsync(ws.flag, 0, 2 * sizeof(int), s));
-  CHASE_HIP(hipMemsetAsync(Ysel, 0, (size_t)kp * (k / 2) * sizeof(c128), s));
-  hipLaunchKernelGGL(select_kernel, dim3(k), dim3(256), 0, s, G, V, (int64_t)kp, k, kp, tiny, Ysel, dlam, ws.flag,
-                     ws.flag + 1);
+                    hipStream_t s) {
+  int* counts = ws.flag + DenseWs::COUNTS;
+  CHASE_TRY(frob_norm(G, kp, ws, s, counts));
+  hipLaunchKernelGGL(select_kernel, dim3(k), dim3(256), 0, s, G, V, (int64_t)kp, k, kp, (const double*)ws.dscalar, Ysel,
+                     dlam, counts, counts + 1);
   CHASE_LAUNCH_CHECK();
-  int h[2] = {0, 0};
-  CHASE_TRY(d2h_small(h, ws.flag, 2 * sizeof(int), ws, s));
-  *npos = h[0];
-  *nneg = h[1];
   return ok();
 }
 

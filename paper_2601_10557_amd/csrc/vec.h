@@ -15,8 +15,8 @@ Err kreal_coords(const c128* Q, int64_t ldq, int64_t m, int k, c128* D, int64_t 
 Err unit_column(c128* x, int64_t n, int64_t r, hipStream_t s);
 // In place, columns 2j and 2j + 1: (x, y) -> (x + i y, x - i y) / sqrt(2).
 Err pair_mix(c128* X, int64_t ldx, int64_t n, int npair, hipStream_t s);
-// In place: orthonormal real coordinates -> orthonormal K-real vectors.
-Err kreal_unpack(c128* X, int64_t ldx, int64_t m, int k, hipStream_t s);
+// Orthonormal real coordinates X -> orthonormal K-real vectors Y (may be X).
+Err kreal_unpack(const c128* X, int64_t ldx, c128* Y, int64_t ldy, int64_t m, int k, hipStream_t s);
 Err convert_to_c64(const c128* src, int64_t lds, c64* dst, int64_t ldd, int64_t rows, int cols, hipStream_t s);
 Err convert_to_c128(const c64* src, int64_t lds, c128* dst, int64_t ldd, int64_t rows, int cols, hipStream_t s);
 Err scale_lower_half(const c128* src, int64_t lds, c128* dst, int64_t ldd, int64_t m, int cols, double g,

@@ -291,16 +291,16 @@ __global__ void unit_column_kernel(c128* x, int64_t n, int64_t r) {
     x[i] = c128{i == r ? 1.0 : 0.0, 0.0};
 }
 
-// In place: real coordinates [r1; r2] of unit length -> the unit K-real
-// vector [a; conj(a)] / sqrt(2) with a = r1 + i r2.
-__global__ void kreal_unpack_kernel(c128* X, int64_t ldx, int64_t m, int k) {
+// Real coordinates [r1; r2] of unit length -> the unit K-real vector
+// [a; conj(a)] / sqrt(2) with a = r1 + i r2; Y may be X.
+__global__ void kreal_unpack_kernel(const c128* X, int64_t ldx, c128* Y, int64_t ldy, int64_t m, int k) {
   const int64_t total = m * k;
   const double h = 0.70710678118654752440;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
     const int64_t c = t / m, i = t % m;
     const double r1 = X[c * ldx + i].re, r2 = X[c * ldx + m + i].re;
-    X[c * ldx + i] = c128{h * r1, h * r2};
-    X[c * ldx + m + i] = c128{h * r1, -h * r2};
+    Y[c * ldy + i] = c128{h * r1, h * r2};
+    Y[c * ldy + m + i] = c128{h * r1, -h * r2};
   }
 }
 
@@ -335,9 +335,9 @@ Err pair_mix(c128* X, int64_t ldx, int64_t n, int npair, hipStream_t s) {
   return ok();
 }
 
-Err kreal_unpack(c128* X, int64_t ldx, int64_t m, int k, hipStream_t s) {
+Err kreal_unpack(const c128* X, int64_t ldx, c128* Y, int64_t ldy, int64_t m, int k, hipStream_t s) {
   if (m * k == 0) return ok();
-  hipLaunchKernelGGL(kreal_unpack_kernel, dim3(grid_for(m * k)), dim3(256), 0, s, X, ldx, m, k);
+  hipLaunchKernelGGL(kreal_unpack_kernel, dim3(grid_for(m * k)), dim3(256), 0, s, X, ldx, Y, ldy, m, k);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
