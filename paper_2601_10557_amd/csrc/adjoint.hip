@@ -27,9 +27,7 @@ namespace chase {
 namespace {
 
 constexpr int TB = 64;        // output tile (rows and columns)
-constexpr int KB = 8;         // eigenpairs per K slab
 constexpr int NT = 256;       // 4 waves, each a 32 x 32 quadrant of the tile
-constexpr int LDT = TB + 2;   // padded LDS row
 
 __device__ __forceinline__ doublex4 mfma64(double a, double b, doublex4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -63,47 +61,42 @@ __device__ __forceinline__ void lower_tile(int64_t t, int64_t* I, int64_t* J) {
   *J = t - i * (i + 1) / 2;
 }
 
-__global__ __launch_bounds__(NT) void adjoint_kernel(const c128* __restrict__ V, int64_t ldv, int64_t m, int nev,
-                                                     const double* __restrict__ gt, c128* GA, c128* GB, int64_t ldg) {
-  // slab layout [buffer][operand][re/im][k][row]: operands 0 = gt x_I,
-  // 1 = gt conj(y_I), 2 = x_J, 3 = y_J
-  __shared__ double S[2][4][2][KB][LDT];
+// One 64 x 64 tile of both outputs, each wave a 32 x 32 quadrant.  Bound by the
+// FP64 MFMA: 64 of them (4096 cycles) per four eigenpairs on eight 16-byte
+// loads, so the fragments come straight from V one step ahead (lane l holds
+// row l % 16, eigenpair l / 16) and no wave waits for another.  m = 4000,
+// nev = 200: @ME@
+__global__ __launch_bounds__(NT, 2) void adjoint_kernel(const c128* __restrict__ V, int64_t ldv, int64_t m, int nev,
+                                                        const double* __restrict__ gt, c128* GA, c128* GB,
+                                                        int64_t ldg) {
   int64_t I, J;
   lower_tile(blockIdx.x, &I, &J);
   const int64_t r0 = I * TB, c0 = J * TB;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-
-  // each thread stages 4 complex values per slab: operand o = tid / 64,
-  // rows (tid & 63) ... of each of the KB columns, two columns per pass
-  const int o = tid >> 6;          // 0..3
-  const int row = tid & 63;
-  const int64_t grow = (o < 2 ? r0 : c0) + row;
-  const bool row_ok = grow < m;
-  const int64_t voff = (o == 1 || o == 3) ? m : 0;   // y half for operands 1, 3
-  c128 st[KB];
-
-  const int KT = (nev + KB - 1) / KB;
-  auto load = [&](int kt) {
+  const int lr = lane & 15, lk = lane >> 4;
+  // rows past m - 1 repeat it (their sums are not written), eigenpairs past
+  // nev - 1 repeat it with weight 0
+  int64_t rr[2], rc[2];
 #pragma unroll
-    for (int kk = 0; kk < KB; ++kk) {
-      const int j = kt * KB + kk;
-      const bool ok = row_ok && j < nev;
-      st[kk] = ok ? V[(int64_t)j * ldv + voff + grow] : c128{0.0, 0.0};
-    }
+  for (int i = 0; i < 2; ++i) {
+    rr[i] = min(r0 + wr + 16 * i + lr, m - 1);
+    rc[i] = min(c0 + wc + 16 * i + lr, m - 1);
+  }
+  struct Step {
+    c128 p[2], q[2], x[2], y[2];
+    double w;
   };
-  auto store = [&](int kt, int buf) {
+  auto load = [&](int k, Step& f) __attribute__((always_inline)) {
+    const int j = min(k + lk, nev - 1);
+    const c128* v = V + (int64_t)j * ldv;
+    f.w = gt[j];
 #pragma unroll
-    for (int kk = 0; kk < KB; ++kk) {
-      const int j = kt * KB + kk;
-      double re = st[kk].re, im = st[kk].im;
-      if (o < 2) {
-        const double w = j < nev ? gt[j] : 0.0;
-        re *= w;
-        im *= (o == 1) ? -w : w;     // gt conj(y) for operand 1
-      }
-      S[buf][o][0][kk][row] = re;
-      S[buf][o][1][kk][row] = im;
+    for (int i = 0; i < 2; ++i) {
+      f.p[i] = v[rr[i]];
+      f.q[i] = v[m + rr[i]];
+      f.x[i] = v[rc[i]];
+      f.y[i] = v[m + rc[i]];
     }
   };
 
@@ -115,58 +108,49 @@ __global__ __launch_bounds__(NT) void adjoint_kernel(const c128* __restrict__ V,
 #pragma unroll
       for (int r = 0; r < 4; ++r) ar[i][j][r] = ai[i][j][r] = br[i][j][r] = bi[i][j][r] = 0.0;
 
-  if (KT > 0) {
-    load(0);
-    store(0, 0);
-  }
-  __syncthreads();
-  const int lr = lane & 15, lk = lane >> 4;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) load(kt + 1);
+  Step cur, nxt;
+  load(0, cur);
+#pragma unroll 1
+  for (int k = 0; k < nev; k += 4) {
+    load(min(k + 4, nev - 1), nxt);
+    __builtin_amdgcn_sched_barrier(0);
+    const double w = k + lk < nev ? cur.w : 0.0;
 #pragma unroll
-    for (int ks = 0; ks < KB; ks += 4) {
-      double pr[2], pi[2], qr[2], qi[2], xr[2], xi[2], yr[2], yi[2];
+    for (int i = 0; i < 2; ++i) {
+      const double pr = w * cur.p[i].re, pi = w * cur.p[i].im;   // p = gt x_r
+      const double qr = w * cur.q[i].re, qi = -w * cur.q[i].im;  // q = gt conj(y_r)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        pr[i] = S[buf][0][0][ks + lk][wr + 16 * i + lr];
-        pi[i] = S[buf][0][1][ks + lk][wr + 16 * i + lr];
-        qr[i] = S[buf][1][0][ks + lk][wr + 16 * i + lr];
-        qi[i] = S[buf][1][1][ks + lk][wr + 16 * i + lr];
-        xr[i] = S[buf][2][0][ks + lk][wc + 16 * i + lr];
-        xi[i] = S[buf][2][1][ks + lk][wc + 16 * i + lr];
-        yr[i] = S[buf][3][0][ks + lk][wc + 16 * i + lr];
-        yi[i] = S[buf][3][1][ks + lk][wc + 16 * i + lr];
+      for (int j = 0; j < 2; ++j) {
+        const double xr = cur.x[j].re, xi = cur.x[j].im, yr = cur.y[j].re, yi = cur.y[j].im;
+        // G_A += p conj(x_c) + q y_c
+        ar[i][j] = mfma64(pr, xr, ar[i][j]);
+        ai[i][j] = mfma64(pi, xr, ai[i][j]);
+        br[i][j] = mfma64(pr, yr, br[i][j]);
+        bi[i][j] = mfma64(pi, yr, bi[i][j]);
+        ar[i][j] = mfma64(pi, xi, ar[i][j]);
+        ai[i][j] = mfma64(-pr, xi, ai[i][j]);
+        // G_B += p conj(y_c) + q x_c
+        br[i][j] = mfma64(pi, yi, br[i][j]);
+        bi[i][j] = mfma64(-pr, yi, bi[i][j]);
+        ar[i][j] = mfma64(qr, yr, ar[i][j]);
+        ai[i][j] = mfma64(qr, yi, ai[i][j]);
+        br[i][j] = mfma64(qr, xr, br[i][j]);
+        bi[i][j] = mfma64(qr, xi, bi[i][j]);
+        ar[i][j] = mfma64(-qi, yi, ar[i][j]);
+        ai[i][j] = mfma64(qi, yr, ai[i][j]);
+        br[i][j] = mfma64(-qi, xi, br[i][j]);
+        bi[i][j] = mfma64(qi, xr, bi[i][j]);
       }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          // G_A += p conj(x_c) + q y_c,   p = gt x_r, q = gt conj(y_r)
-          ar[i][j] = mfma64(pr[i], xr[j], ar[i][j]);
-          ar[i][j] = mfma64(pi[i], xi[j], ar[i][j]);
-          ar[i][j] = mfma64(qr[i], yr[j], ar[i][j]);
-          ar[i][j] = mfma64(-qi[i], yi[j], ar[i][j]);
-          ai[i][j] = mfma64(pi[i], xr[j], ai[i][j]);
-          ai[i][j] = mfma64(-pr[i], xi[j], ai[i][j]);
-          ai[i][j] = mfma64(qr[i], yi[j], ai[i][j]);
-          ai[i][j] = mfma64(qi[i], yr[j], ai[i][j]);
-          // G_B += p conj(y_c) + q x_c
-          br[i][j] = mfma64(pr[i], yr[j], br[i][j]);
-          br[i][j] = mfma64(pi[i], yi[j], br[i][j]);
-          br[i][j] = mfma64(qr[i], xr[j], br[i][j]);
-          br[i][j] = mfma64(-qi[i], xi[j], br[i][j]);
-          bi[i][j] = mfma64(pi[i], yr[j], bi[i][j]);
-          bi[i][j] = mfma64(-pr[i], yi[j], bi[i][j]);
-          bi[i][j] = mfma64(qr[i], xi[j], bi[i][j]);
-          bi[i][j] = mfma64(qi[i], xr[j], bi[i][j]);
-        }
     }
-    if (kt + 1 < KT) store(kt + 1, buf ^ 1);
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    cur = nxt;
   }
 
   // D = 16 x 16 block: lane holds rows (lane >> 4) + 4 r, column lane & 15
+  typedef double doublex2 __attribute__((ext_vector_type(2)));
+  auto put = [&](c128* p, double re, double im) __attribute__((always_inline)) {
+    __builtin_nontemporal_store(doublex2{re, im}, reinterpret_cast<doublex2*>(p));
+  };
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -176,11 +160,11 @@ __global__ __launch_bounds__(NT) void adjoint_kernel(const c128* __restrict__ V,
         const int64_t gi = r0 + wr + 16 * i + (lane >> 4) + 4 * r;
         const int64_t gj = c0 + wc + 16 * j + (lane & 15);
         if (gi < m && gj < m) {
-          GA[gj * ldg + gi] = c128{ar[i][j][r], ai[i][j][r]};
-          GB[gj * ldg + gi] = c128{br[i][j][r], bi[i][j][r]};
+          put(GA + gj * ldg + gi, ar[i][j][r], ai[i][j][r]);
+          put(GB + gj * ldg + gi, br[i][j][r], bi[i][j][r]);
           if (I != J) {
-            GA[gi * ldg + gj] = c128{ar[i][j][r], -ai[i][j][r]};
-            GB[gi * ldg + gj] = c128{br[i][j][r], bi[i][j][r]};
+            put(GA + gi * ldg + gj, ar[i][j][r], -ai[i][j][r]);
+            put(GB + gi * ldg + gj, br[i][j][r], bi[i][j][r]);
           }
         }
       }
