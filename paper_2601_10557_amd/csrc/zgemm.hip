@@ -20,7 +20,7 @@ namespace {
 
 constexpr int BK = 16, NT = 256;  // small products: K slab
 constexpr int RK = 8;             // large products: K slab
-constexpr int RT = 64;            // and tile of a workgroup, 2 x 2 waves of 32 x 32
+constexpr int RT = 64;            // and RT x RT outputs of a workgroup, 32 x 32 a wave
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 
@@ -42,8 +42,8 @@ struct ZgemmDev {
   int lower_only, a_lower, b_upper;
   int real_data;
   int splits;
-  int TM, TN;      // tiles of a large product
-  int tiles;       // of them, those that are computed
+  int TM, TN;      // workgroup tiles of a large product (not lower_only)
+  int tiles;
   int64_t kchunk;  // K range per split
   c128* ws;        // split-K partials: one RT x RT tile per (split, batch, tile)
 };
@@ -219,28 +219,37 @@ __device__ __forceinline__ int xcd_remap(int w, int T) {
   return xcd * q + (xcd < r ? xcd : r) + slot;
 }
 
-// Tile t of the computed ones: of the lower triangle row by row (lower_only),
-// else row strip by row strip; with a triangular operand the tiles with the
-// longest K ranges first (8000 x 520 x 520 upper: 270 us strip by strip, 198 us
-// longest first).
-__device__ __forceinline__ void tile_of(const ZgemmDev& g, int t, int* I, int* J) {
+// First row and column of a wave's 32 x 32 outputs in workgroup tile t, false
+// if it has none.  lower_only: the tiles of the lower triangle row by row, four
+// neighbours a workgroup (no wave above the diagonal).  With a triangular
+// operand the four waves have the same K range, 128 rows of a column (b_upper)
+// or 128 columns of a row (a_lower), the longest ranges first.  Else 2 x 2.
+// 8000 x 520 x 520 upper: 270 us strip by strip, 198 us longest first in 64 x 64 tiles, 183 so;
+// 520 x 520 x 8000 lower: 200 us on 2 x 2, 171 so.
+__device__ __forceinline__ bool wave_tile(const ZgemmDev& g, int t, int wave, int64_t* m0, int64_t* n0) {
+  int i, j;
   if (g.lower_only) {
-    int i = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-    while (i * (i + 1) / 2 > t) --i;
-    while ((i + 1) * (i + 2) / 2 <= t) ++i;
-    *I = i;
-    *J = t - i * (i + 1) / 2;
-    return;
+    const int u = 4 * t + wave;
+    i = (int)((sqrt(8.0 * (double)u + 1.0) - 1.0) * 0.5);
+    while (i * (i + 1) / 2 > u) --i;
+    while ((i + 1) * (i + 2) / 2 <= u) ++i;
+    j = u - i * (i + 1) / 2;
+  } else if (g.b_upper) {
+    j = t / g.TM;
+    i = 4 * (t - j * g.TM) + wave;
+    j = g.TN - 1 - j;
+  } else if (g.a_lower) {
+    i = t / g.TN;
+    j = 4 * (t - i * g.TN) + wave;
+    i = g.TM - 1 - i;
+  } else {
+    i = t / g.TN;
+    j = 2 * (t - i * g.TN) + (wave & 1);
+    i = 2 * i + (wave >> 1);
   }
-  if (g.b_upper) {  // column by column, the longest K ranges first
-    const int j = t / g.TM;
-    *I = t - j * g.TM;
-    *J = g.TN - 1 - j;
-    return;
-  }
-  const int i = t / g.TN;
-  *I = g.a_lower ? g.TM - 1 - i : i;
-  *J = t - i * g.TN;
+  *m0 = 32 * (int64_t)i;
+  *n0 = 32 * (int64_t)j;
+  return *m0 < g.M && *n0 < g.N;
 }
 
 __device__ __forceinline__ double flip(double x, unsigned mask) {  // mask: 0 or 0x80000000
@@ -275,10 +284,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int id = g.b_upper || g.a_lower ? blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
   const int sp = id / g.tiles, bt = blockIdx.y, t = id - sp * g.tiles;
-  int I, J;
-  tile_of(g, t, &I, &J);
-  const int64_t m0 = (int64_t)I * RT + (wave >> 1) * 32, n0 = (int64_t)J * RT + (wave & 1) * 32;
-  if (m0 >= g.M || n0 >= g.N || (g.lower_only && m0 + 32 <= n0)) return;
+  int64_t m0, n0;
+  if (!wave_tile(g, t, wave, &m0, &n0)) return;
   const c128* A = g.A + (int64_t)bt * g.strideA;
   const c128* B = g.B + (int64_t)bt * g.strideB;
   int64_t klim = g.K;
@@ -402,11 +409,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void
 // wave.
 __global__ __launch_bounds__(NT) void zgemm_reduce_kernel(const ZgemmDev g) {
   const int t = blockIdx.x, bt = blockIdx.y, f = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int I, J;
-  tile_of(g, t, &I, &J);
-  const int64_t m0 = (int64_t)I * RT + (wave >> 1) * 32, n0 = (int64_t)J * RT + (wave & 1) * 32;
-  if (m0 >= g.M || n0 >= g.N || (g.lower_only && m0 + 32 <= n0)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t m0, n0;
+  if (!wave_tile(g, t, wave, &m0, &n0)) return;
   const doublex2* p = reinterpret_cast<const doublex2*>(g.ws + ((int64_t)bt * g.tiles + t) * RT * RT) +
                       (wave * 4 + f) * 256 + lane;
   const int64_t step = (int64_t)gridDim.y * g.tiles * RT * RT;
@@ -466,9 +472,11 @@ Err zgemm(const ZgemmArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
     CHASE_LAUNCH_CHECK();
     return ok();
   }
-  g.TM = (int)ceil_div(a.M, (int64_t)RT);
-  g.TN = (int)ceil_div(a.N, (int64_t)RT);
-  g.tiles = a.lower_only ? g.TM * (g.TM + 1) / 2 : g.TM * g.TN;
+  const bool col = a.b_upper && !a.lower_only, row = a.a_lower && !a.lower_only && !a.b_upper;
+  g.TM = (int)ceil_div(a.M, (int64_t)(col ? 128 : row ? 32 : RT));
+  g.TN = (int)ceil_div(a.N, (int64_t)(col ? 32 : row ? 128 : RT));
+  const int64_t t32 = ceil_div(a.M, (int64_t)32);
+  g.tiles = a.lower_only ? (int)ceil_div(t32 * (t32 + 1) / 2, (int64_t)4) : g.TM * g.TN;
   // K splits while the tiles leave workgroup slots empty, at least 8 slabs
   // each: to two workgroups per CU, and two splits where that leaves one tile
   // on most CUs (three fit: 8000 x 188 x 376, 375 tiles: 113 us whole, 89 + 17
