@@ -449,23 +449,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // A split product in one launch: the last few columns on their own tile
 // shape and K split, next to the main columns, without a second stream.
-// The f32 remainder workgroups come first (0 .. nrem - 1) and spread over the
-// CUs while the main tiles fill the rest; the f64 ones come after the main
-// tiles, where they fill the CUs the last main tiles leave idle (2-3% faster
-// f64 calls at k = 260, no change in f32).  Each part starts at a multiple of
-// 8 (nrem and nmain rounded up, the padding workgroups exit at once) so that
-// the XCD of a workgroup stays blockIdx mod 8 in both.
+// The remainder workgroups are short and bound by the read of M.  Where the
+// main tiles leave some of the 512 places empty (two a CU) they come after
+// those and fill them (m = 4000, two products, first / last: k = 200 1006 / 967
+// us, k = 330 1544 / 1487; m = 8000, k = 260 4404 / 4349); where the main tiles
+// take every place they come first (k = 145 792 / 799, k = 260 1202 / 1201; mixed
+// orders put two main tiles on some CUs and none on others).  Each part starts
+// at a multiple of 8 (nrem and nmain rounded up, the padding workgroups exit at
+// once) so that the XCD of a workgroup stays blockIdx mod 8 in both.
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED, int BMR, int BNR, int BKR,
           int NSTR, int WGMR, int WGNR>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void hx_pair_kernel(
     const ApplyHArgs am, int splits_m, int kps_m, R* ws_m,
     const ApplyHArgs ar, int splits_r, int kps_r, R* ws_r, int nrem, int nrem_live,
-    int nmain, int nmain_live) {
+    int nmain, int nmain_live, bool rem_first) {
   constexpr size_t LM = Cfg<Tr, BM, BN, BK, NST, WGM, WGN>::LDS;
   constexpr size_t LR = Cfg<Tr, BMR, BNR, BKR, NSTR, WGMR, WGNR>::LDS;
   __shared__ __attribute__((aligned(16))) R lds[(LM > LR ? LM : LR) / sizeof(R)];
   const int bid = blockIdx.x;
-  constexpr bool rem_first = sizeof(R) == 4;
   const int rb = rem_first ? bid : bid - nmain;  // remainder workgroup, if >= 0
   const int mb = rem_first ? bid - nrem : bid;   // main workgroup, if >= 0
   if (rem_first ? bid < nrem : bid >= nmain) {
@@ -476,13 +477,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Sum the split-K partials in a fixed order and apply the epilogue: one
-// thread per complex row i and X column j.
-__global__ void hx_reduce(const ApplyHArgs a, int splits, const R* ws) {
+// thread per complex row i and X column j.  Blocks from na on take part b.
+__global__ void hx_reduce(const ApplyHArgs aa, int splits_a, const R* ws_a, int na, const ApplyHArgs ab, int splits_b,
+                          const R* ws_b) {
+  const bool first = (int)blockIdx.x < na;
+  const ApplyHArgs& a = first ? aa : ab;
+  const int splits = first ? splits_a : splits_b;
+  const R* ws = first ? ws_a : ws_b;
+  const int64_t block = first ? blockIdx.x : blockIdx.x - na, blocks = first ? na : gridDim.x - na;
   const int64_t m = a.m, M2 = 2 * m;
   const int N = a.tda ? a.k : 2 * a.k;
   const int64_t total = m * a.k;
   const int64_t split_stride = M2 * N;
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t t = block * blockDim.x + threadIdx.x; t < total; t += blocks * blockDim.x) {
     const int j = (int)(t / m);
     const int64_t i = t % m;
     if (a.tda) {
@@ -562,11 +569,16 @@ void plan_override(Plan& p, int64_t m2, int64_t n2, const int (&bm)[NCFG], const
   p.tiles = ceil_div(m2, bm[c]) * ceil_div(n2, bn[c]);
 }
 
-Err launch_reduce(const ApplyHArgs& a, int splits, const R* ws, hipStream_t s) {
-  if (splits <= 1) return ok();
-  const int64_t total = a.m * (int64_t)a.k;
-  const int blocks = (int)std::min<int64_t>(ceil_div(total, 256), 8192);
-  hipLaunchKernelGGL(hx_reduce, dim3(blocks), dim3(256), 0, s, a, splits, ws);
+// Part b (null: none) in the same launch: at 8 columns it is latency, 8 us in a
+// launch of its own.
+Err launch_reduce(const ApplyHArgs& a, int splits, const R* ws, const ApplyHArgs* b, int splits_b, const R* ws_b,
+                  hipStream_t s) {
+  auto blocks = [](const ApplyHArgs& x, int sp) {
+    return sp <= 1 ? 0 : (int)std::min<int64_t>(ceil_div(x.m * (int64_t)x.k, 256), 8192);
+  };
+  const int na = blocks(a, splits), nb = b ? blocks(*b, splits_b) : 0;
+  if (na + nb == 0) return ok();
+  hipLaunchKernelGGL(hx_reduce, dim3(na + nb), dim3(256), 0, s, a, splits, ws, na, b ? *b : a, splits_b, ws_b);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
@@ -577,7 +589,7 @@ Err launch_cfg(const ApplyHArgs& a, const Plan& p, void* ws, hipStream_t s) {
   hipLaunchKernelGGL((hx_kernel<Tr, BM, BN, BK, NST, WGM, WGN, SCHED>), dim3((unsigned)grid), dim3(256), 0, s, a, p.splits,
                      p.kps, (R*)ws);
   CHASE_LAUNCH_CHECK();
-  return launch_reduce(a, p.splits, (const R*)ws, s);
+  return launch_reduce(a, p.splits, (const R*)ws, nullptr, 1, nullptr, s);
 }
 
 // Main part on tile shape (BM, BN, ...), remainder on (BMR, BNR, ...).
@@ -592,10 +604,9 @@ Err launch_pair_cfg(const ApplyHArgs& am, const Plan& pm, void* wsm,
   const int64_t grid = (int64_t)nrem + nmain;
   hipLaunchKernelGGL((hx_pair_kernel<Tr, BM, BN, BK, NST, WGM, WGN, SCHED, BMR, BNR, BKR, NSTR, WGMR, WGNR>),
                      dim3((unsigned)grid), dim3(256), 0, s, am, pm.splits, pm.kps, (R*)wsm, ar, pr.splits, pr.kps,
-                     (R*)wsr, nrem, live, nmain, main_live);
+                     (R*)wsr, nrem, live, nmain, main_live, main_live % 512 == 0);
   CHASE_LAUNCH_CHECK();
-  CHASE_TRY((launch_reduce(am, pm.splits, (const R*)wsm, s)));
-  return launch_reduce(ar, pr.splits, (const R*)wsr, s);
+  return launch_reduce(am, pm.splits, (const R*)wsm, &ar, pr.splits, (const R*)wsr, s);
 }
 
 // Tile shapes (BM x BN reals, K slab BK, NST ring stages), two workgroups
