@@ -8,19 +8,22 @@
 // and reduced in a fixed order (deterministic).  Real matrices held in c128
 // (real_data) take only the real-by-real MFMA of each step.
 //
-// Two kernels.  Large products run without LDS and barriers: the FP64 MFMA
-// takes 64 cycles, so a wave of 32 x 32 outputs loads its fragments straight
-// into registers (8 16-byte loads per lane and slab of 8 k for 32 MFMAs,
-// 2048 cycles), one slab ahead.  Small ones (few tiles, K <= 256) are bound
-// by latency and run on 32 x 32 tiles of a workgroup, staged through LDS.
+// The FP64 MFMA takes 64 cycles, so a wave loads its fragments straight into
+// registers (32 x 32 outputs: 8 16-byte loads per lane and slab of 8 k for 32
+// MFMAs, 2048 cycles), one slab ahead, without LDS and barriers.  Large
+// products: waves of 32 x 32, four a workgroup, K split over workgroups where
+// the tiles leave CUs idle.  Small ones, bound by latency: the waves of a
+// workgroup share K.
+#include <type_traits>
+
 #include "common.h"
 
 namespace chase {
 namespace {
 
-constexpr int BK = 16, NT = 256;  // small products: K slab
-constexpr int RK = 8;             // large products: K slab
-constexpr int RT = 64;            // and RT x RT outputs of a workgroup, 32 x 32 a wave
+constexpr int NT = 256;
+constexpr int RK = 8;   // K slab
+constexpr int RT = 64;  // large products: RT x RT outputs of a workgroup, 32 x 32 a wave
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 
@@ -48,168 +51,7 @@ struct ZgemmDev {
   c128* ws;        // split-K partials: one RT x RT tile per (split, batch, tile)
 };
 
-// Small products: 32 x 32 output tiles, a 16 x 16 MFMA tile per wave.
-template <bool REAL>
-__global__ __launch_bounds__(NT) void zgemm_small_kernel(const ZgemmDev g) {
-  constexpr int TB = 32, BM = TB, BN = TB, FR = TB / 32;
-  constexpr int LDS_A = BM + 2, LDS_B = BN + 2;
-  __shared__ double As[2][2][BK][LDS_A];
-  __shared__ double Bs[2][2][BK][LDS_B];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int TN = (int)((g.N + BN - 1) / BN);
-  const int64_t m0 = (int64_t)(blockIdx.x / TN) * BM;
-  const int64_t n0 = (int64_t)(blockIdx.x % TN) * BN;
-  const int bt = blockIdx.y;
-  if (g.lower_only && m0 + BM <= n0) return;  // strictly above the diagonal
-  const c128* A = g.A + (int64_t)bt * g.strideA;
-  const c128* B = g.B + (int64_t)bt * g.strideB;
-  // triangular operands: products with k beyond the last row of this tile
-  // (lower op(A)) or the last column (upper op(B)) vanish
-  int64_t klim = g.K;
-  if (g.a_lower) klim = min(klim, m0 + BM);
-  if (g.b_upper) klim = min(klim, n0 + BN);
-  const int64_t kbeg = 0, kend = klim;
-  const int KT = (int)((kend - kbeg + BK - 1) / BK);
-  const int wm0 = (wave >> 1) * (TB / 2), wn0 = (wave & 1) * (TB / 2);
-
-  constexpr int PER = BM * BK / NT;  // elements of each operand per thread
-  // raw loads (clamped addresses) plus validity bits; conj / sign are applied
-  // when the tile is written to LDS, after the MFMAs of the previous slab
-  doublex2 ra[PER], rb[PER];
-  unsigned okA = 0, okB = 0, negB = 0;
-
-  auto load = [&](int kt) {
-    const int64_t k0 = kbeg + (int64_t)kt * BK;
-    okA = okB = negB = 0;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int el = tid + e * NT;
-      int i, kk;
-      if (g.transA == 0) { kk = el / BM; i = el % BM; } else { i = el / BK; kk = el % BK; }
-      const int64_t gi = m0 + i, gk = k0 + kk;
-      const bool ok = gi < g.M && gk < kend;
-      const int64_t idx = ok ? (g.transA == 0 ? gk * g.lda + gi : gi * g.lda + gk) : 0;
-      ra[e] = *reinterpret_cast<const doublex2*>(A + idx);
-      if (ok) okA |= 1u << e;
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int el = tid + e * NT;
-      int j, kk;
-      if (g.transB == 0) { j = el / BK; kk = el % BK; } else { kk = el / BN; j = el % BN; }
-      const int64_t gj = n0 + j, gk = k0 + kk;
-      const bool ok = gj < g.N && gk < kend;
-      const int64_t idx = ok ? (g.transB == 0 ? gj * g.ldb + gk : gk * g.ldb + gj) : 0;
-      rb[e] = *reinterpret_cast<const doublex2*>(B + idx);
-      if (ok) okB |= 1u << e;
-      if (gk >= g.kneg) negB |= 1u << e;
-    }
-  };
-  auto store = [&](int buf) {
-    const double ca = g.transA ? -1.0 : 1.0, cb = g.transB ? -1.0 : 1.0;
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int el = tid + e * NT;
-      int i, kk;
-      if (g.transA == 0) { kk = el / BM; i = el % BM; } else { i = el / BK; kk = el % BK; }
-      const bool ok = (okA >> e) & 1u;
-      As[buf][0][kk][i] = ok ? ra[e][0] : 0.0;
-      As[buf][1][kk][i] = ok ? ra[e][1] * ca : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int el = tid + e * NT;
-      int j, kk;
-      if (g.transB == 0) { j = el / BK; kk = el % BK; } else { kk = el / BN; j = el % BN; }
-      const bool ok = (okB >> e) & 1u;
-      const double sg = ((negB >> e) & 1u) ? -1.0 : 1.0;
-      Bs[buf][0][kk][j] = ok ? rb[e][0] * sg : 0.0;
-      Bs[buf][1][kk][j] = ok ? rb[e][1] * cb * sg : 0.0;
-    }
-  };
-
-  doublex4 cr[FR][FR], ci[FR][FR];
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FR; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) { cr[i][j][r] = 0; ci[i][j][r] = 0; }
-
-  if (KT > 0) {
-    load(0);
-    store(0);
-  }
-  __syncthreads();
-  const int lr = lane & 15, lk = lane >> 4;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) load(kt + 1);
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 4) {
-      double fa_r[FR], fa_i[FR], fb_r[FR], fb_i[FR], fb_n[FR];
-#pragma unroll
-      for (int i = 0; i < FR; ++i) {
-        fa_r[i] = As[buf][0][ks + lk][wm0 + 16 * i + lr];
-        fa_i[i] = As[buf][1][ks + lk][wm0 + 16 * i + lr];
-      }
-#pragma unroll
-      for (int j = 0; j < FR; ++j) {
-        fb_r[j] = Bs[buf][0][ks + lk][wn0 + 16 * j + lr];
-        fb_i[j] = Bs[buf][1][ks + lk][wn0 + 16 * j + lr];
-        fb_n[j] = -fb_i[j];
-      }
-      if constexpr (REAL) {
-#pragma unroll
-        for (int i = 0; i < FR; ++i)
-#pragma unroll
-          for (int j = 0; j < FR; ++j) cr[i][j] = mfma64(fa_r[i], fb_r[j], cr[i][j]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < FR; ++i)
-#pragma unroll
-          for (int j = 0; j < FR; ++j) {
-            cr[i][j] = mfma64(fa_r[i], fb_r[j], cr[i][j]);
-            ci[i][j] = mfma64(fa_r[i], fb_i[j], ci[i][j]);
-          }
-#pragma unroll
-        for (int i = 0; i < FR; ++i)
-#pragma unroll
-          for (int j = 0; j < FR; ++j) {
-            cr[i][j] = mfma64(fa_i[i], fb_n[j], cr[i][j]);
-            ci[i][j] = mfma64(fa_i[i], fb_r[j], ci[i][j]);
-          }
-      }
-    }
-    if (kt + 1 < KT) store(buf ^ 1);
-    __syncthreads();
-  }
-
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FR; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t gi = m0 + wm0 + 16 * i + (lane >> 4) + 4 * r;
-        const int64_t gj = n0 + wn0 + 16 * j + (lane & 15);
-        if (gi < g.M && gj < g.N) {
-          const double xr = cr[i][j][r], xi = ci[i][j][r];
-          const double yr = g.ar * xr - g.ai * xi, yi = g.ar * xi + g.ai * xr;
-          c128* Cp = g.C + (int64_t)bt * g.strideC + gj * g.ldc + gi;
-          double outr = yr, outi = yi;
-          if (g.br != 0.0 || g.bi != 0.0) {
-            c128 c = *Cp;
-            outr += g.br * c.re - g.bi * c.im;
-            outi += g.br * c.im + g.bi * c.re;
-          }
-          *Cp = c128{outr, outi};
-        }
-      }
-}
-
-// Large products.  Lane l of a fragment of 16 rows (columns) and 8 k holds row
-// l % 16 at k = 2 (l / 16) + s, s = 0, 1: two loads of one c128, 128 contiguous
+// Lane l of a fragment of 16 rows (columns) and 8 k holds row l % 16 at k = 2 (l / 16) + s, s = 0, 1: two loads of one c128, 128 contiguous
 // bytes per row where k runs along memory, 256 per k where the rows do.
 __device__ __forceinline__ int xcd_remap(int w, int T) {
   // workgroup w runs on XCD w % 8: give each XCD a contiguous range, so that
@@ -277,24 +119,14 @@ __device__ __forceinline__ void put4(const ZgemmDev& g, int bt, int64_t gi, int6
   }
 }
 
-template <bool REAL, int TA, int TBT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void zgemm_kernel(const ZgemmDev g) {
-  constexpr int F = 2;  // fragments per wave and operand
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int id = g.b_upper || g.a_lower ? blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
-  const int sp = id / g.tiles, bt = blockIdx.y, t = id - sp * g.tiles;
-  int64_t m0, n0;
-  if (!wave_tile(g, t, wave, &m0, &n0)) return;
+// cr + i ci = op(A) S op(B) over k in [kbeg, kend) for the 16 F x 16 F outputs
+// at (m0, n0), a slab of 8 loaded ahead of its use.
+template <bool REAL, int TA, int TBT, int F>
+__device__ __forceinline__ void accumulate(const ZgemmDev& g, int bt, int64_t m0, int64_t n0, int64_t kbeg, int64_t kend,
+                                           doublex4 (&cr)[F][F], doublex4 (&ci)[F][F]) {
   const c128* A = g.A + (int64_t)bt * g.strideA;
   const c128* B = g.B + (int64_t)bt * g.strideB;
-  int64_t klim = g.K;
-  if (g.a_lower) klim = min(klim, m0 + 32);
-  if (g.b_upper) klim = min(klim, n0 + 32);
-  const int64_t kbeg = (int64_t)sp * g.kchunk;
-  const int64_t kend = min(klim, kbeg + g.kchunk);
-  const int lk = 2 * (lane >> 4);
-
+  const int lane = threadIdx.x & 63, lk = 2 * (lane >> 4);
   // addresses of the lane's first k of each fragment (rows past the end read
   // the last one: never stored)
   const doublex2 *pa[F], *pb[F];
@@ -306,7 +138,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void
   }
   const int64_t ka = TA ? 1 : g.lda, kb = TBT ? g.ldb : 1;  // step of one k
   doublex2 fa[2][F][2], fb[2][F][2];
-  doublex4 cr[F][F], ci[F][F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
@@ -384,6 +215,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void
     load_tail(kfull, fa[0], fb[0]);
     mul(kfull, fa[0], fb[0]);
   }
+}
+
+template <bool REAL, int TA, int TBT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void zgemm_kernel(const ZgemmDev g) {
+  constexpr int F = 2;  // fragments per wave and operand
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int id = g.b_upper || g.a_lower ? blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
+  const int sp = id / g.tiles, bt = blockIdx.y, t = id - sp * g.tiles;
+  int64_t m0, n0;
+  if (!wave_tile(g, t, wave, &m0, &n0)) return;
+  int64_t klim = g.K;
+  if (g.a_lower) klim = min(klim, m0 + 32);
+  if (g.b_upper) klim = min(klim, n0 + 32);
+  const int64_t kbeg = (int64_t)sp * g.kchunk;
+  doublex4 cr[F][F], ci[F][F];
+  accumulate<REAL, TA, TBT, F>(g, bt, m0, n0, kbeg, min(klim, kbeg + g.kchunk), cr, ci);
 
   double* w = g.splits > 1 ? reinterpret_cast<double*>(g.ws + (((int64_t)sp * gridDim.y + bt) * g.tiles + t) * RT * RT) +
                                  wave * (F * F * 512)
@@ -403,6 +251,56 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void
         put4(g, bt, m0 + 16 * i + 4 * (lane >> 4), n0 + 16 * j + (lane & 15), vr, vi);
       }
     }
+}
+
+// Small products: a workgroup of NW waves takes 16 F x 16 F outputs, every wave
+// a share of K, and adds the waves' sums in LDS in K order.  Bound by the
+// latency of a slab's loads; one launch, no partial sums in memory.
+template <bool REAL, int TA, int TBT, int F, int NW>
+__global__ __launch_bounds__(64 * NW) void zgemm_short_kernel(const ZgemmDev g) {
+  constexpr int PARTS = REAL ? 1 : 2;
+  __shared__ double red[NW][F * F][PARTS][4][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int bt = blockIdx.y, ti = blockIdx.x / g.TN;
+  const int64_t m0 = (int64_t)ti * 16 * F, n0 = ((int64_t)blockIdx.x - (int64_t)ti * g.TN) * 16 * F;
+  if (g.lower_only && m0 + 16 * F <= n0) return;  // strictly above the diagonal
+  int64_t klim = g.K;
+  if (g.a_lower) klim = min(klim, m0 + 16 * F);
+  if (g.b_upper) klim = min(klim, n0 + 16 * F);
+  const int64_t S = (klim + RK - 1) / RK;
+  doublex4 cr[F][F], ci[F][F];
+  accumulate<REAL, TA, TBT, F>(g, bt, m0, n0, S * wave / NW * RK, min(klim, S * (wave + 1) / NW * RK), cr, ci);
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        red[wave][i * F + j][0][r][lane] = cr[i][j][r];
+        if constexpr (!REAL) red[wave][i * F + j][PARTS - 1][r][lane] = ci[i][j][r];
+      }
+  __syncthreads();
+#pragma unroll 1
+  for (int e = wave; e < F * F * 4; e += NW) {
+    const int f = e >> 2, r = e & 3;
+    double xr = 0, xi = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      xr += red[w][f][0][r][lane];
+      if constexpr (!REAL) xi += red[w][f][PARTS - 1][r][lane];
+    }
+    const int64_t gi = m0 + 16 * (f / F) + 4 * (lane >> 4) + r, gj = n0 + 16 * (f % F) + (lane & 15);
+    if (gi >= g.M || gj >= g.N) continue;
+    c128* Cp = g.C + (int64_t)bt * g.strideC + gj * g.ldc + gi;
+    double outr = g.ar * xr - g.ai * xi, outi = g.ar * xi + g.ai * xr;
+    if (g.br != 0.0 || g.bi != 0.0) {
+      const c128 c = *Cp;
+      outr += g.br * c.re - g.bi * c.im;
+      outi += g.br * c.im + g.bi * c.re;
+    }
+    *Cp = c128{outr, outi};
+  }
 }
 
 // Sums the K splits of tile blockIdx.x in order; fragment blockIdx.z of each
@@ -447,6 +345,22 @@ void launch_large(const ZgemmDev& g, dim3 grid, hipStream_t s) {
   }
 }
 
+template <int F, int NW>
+void launch_short(ZgemmDev g, int batch, hipStream_t s) {
+  g.TN = (int)ceil_div(g.N, (int64_t)(16 * F));
+  const dim3 grid((unsigned)(ceil_div(g.M, (int64_t)(16 * F)) * g.TN), (unsigned)batch), block(64 * NW);
+  auto go = [&](auto REAL, auto TA, auto TB) {
+    hipLaunchKernelGGL((zgemm_short_kernel<decltype(REAL)::value != 0, decltype(TA)::value, decltype(TB)::value,
+                                           F, NW>),
+                       grid, block, 0, s, g);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  auto tb = [&](auto REAL, auto TA) { g.transB ? go(REAL, TA, I1{}) : go(REAL, TA, I0{}); };
+  auto ta = [&](auto REAL) { g.transA ? tb(REAL, I1{}) : tb(REAL, I0{}); };
+  g.real_data ? ta(I1{}) : ta(I0{});
+}
+
 }  // namespace
 
 Err zgemm(const ZgemmArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
@@ -461,14 +375,18 @@ Err zgemm(const ZgemmArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   g.kneg = a.kneg;
   g.lower_only = a.lower_only; g.a_lower = a.a_lower; g.b_upper = a.b_upper;
   g.real_data = a.real_data;
-  // 32 x 32 tiles when 64 x 64 ones would leave most CUs idle and K is too
-  // short for a split: a 64 x 64 x 64 complex tile is about 7 us of one CU's
-  // FP64 MFMA, a 32 x 32 one a quarter of that
-  const int64_t t64 = ceil_div(a.M, (int64_t)64) * ceil_div(a.N, (int64_t)64) * a.batch;
-  if (t64 < 128 && a.K <= 256) {
-    const dim3 grid((unsigned)(ceil_div(a.M, (int64_t)32) * ceil_div(a.N, (int64_t)32)), (unsigned)a.batch);
-    if (a.real_data) hipLaunchKernelGGL((zgemm_small_kernel<true>), grid, dim3(NT), 0, s, g);
-    else hipLaunchKernelGGL((zgemm_small_kernel<false>), grid, dim3(NT), 0, s, g);
+  // Small products in one launch of workgroups whose waves share K.  us, here
+  // against tiles of 64 x 64 with split K (or, before, of 32 x 32 through LDS):
+  // 64^3 3.8 / 7.4, 192^3 5.8 / 17.5, 384^3 17.0 / 24.0, 512^3 23.2 / 38.2,
+  // 4000 x 260 x 260 57 / 71, 200 x 200 x 640 11.9 / 19.1; past the line
+  // 576^3 45.9 / 44.0, 8000 x 200 x 200 75 / 66, 140 x 140 x 4000 58 / 40 (few
+  // workgroups, each waiting for its loads).  32 x 32 outputs on eight waves
+  // instead of 16 x 16 on four halve the loads where K gives every wave enough to
+  // do: 448^3 20.5 / 25.4, 384^3 17.7 / 17.0.
+  const double mnk = (double)a.M * a.N * a.K * a.batch;
+  if (a.K <= 640 && mnk <= (a.K <= 512 ? 2.8e8 : 1e8)) {
+    if (a.K >= 384 && mnk >= 8e7) launch_short<2, 8>(g, a.batch, s);
+    else launch_short<1, 4>(g, a.batch, s);
     CHASE_LAUNCH_CHECK();
     return ok();
   }

@@ -709,3 +709,26 @@ def test_qr_block_edges(k):
     assert np.max(np.abs(Q - Qr * ph)) < 1e-11
     assert np.max(np.abs(R - Rr * ph.conj()[:, None])) < 1e-11 * np.max(np.abs(Rr))
     assert np.max(np.abs(np.tril(R, -1))) == 0.0
+
+
+# k x k x k products around the sizes where the small-product kernel changes
+# its tile (386: 16 x 16 outputs, 434 and 450: 32 x 32) and gives way to the
+# large one (514), all with cut-off tiles and K slabs; bounds as above
+@pytest.mark.parametrize("k", [386, 434, 450, 514])
+def test_qr_product_shapes(k):
+    print_case("qr_product_shapes", k=k)
+    p = problem(m=600, seed=4, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, (k + 1) // 2, 0)
+    rng = np.random.default_rng(k)
+    X = complex_normal(rng, (p.n, k)) * np.linspace(0.1, 1.0, k)[None, :]
+    Qd = to_dev(X)
+    Rd, variant = s.qr(Qd)
+    assert variant == 0
+    Q, R = to_host(Qd), to_host(Rd)
+    Qr, Rr = np.linalg.qr(X)
+    ph = np.diag(Rr) / np.abs(np.diag(Rr))
+    assert np.max(np.abs(Q - Qr * ph)) < 1e-11
+    assert np.max(np.abs(R - Rr * ph.conj()[:, None])) < 1e-11 * np.max(np.abs(Rr))
+    assert np.max(np.abs(np.tril(R, -1))) == 0.0
+    s.close()
