@@ -192,12 +192,12 @@ __device__ __forceinline__ int rr_player(int pos, int r, int n) {
   return ((pos - 1 + r) % (n - 1)) + 1;
 }
 
-// One Jacobi sweep on the 32 x 32 subproblem [[G_pp, G_pq], [G_qp, G_qq]]
-// of pair `pair` in round `round`, in steps of 16 disjoint rotations.
+// One Jacobi sweep on the 32 x 32 subproblem S[0] = [[G_pp, G_pq], [G_qp, G_qq]]
+// of a pair of blocks, in steps of 16 disjoint rotations.
 // Round 0 of an outer sweep holds every block of G in exactly one pair, so
 // there the subproblem gets a full cyclic sweep (31 steps, round-robin
 // pairing) and every index pair inside a block is rotated once; the later
-// rounds (cross = 1) rotate only the 256 index pairs across the two blocks
+// rounds (CROSS) rotate only the 256 index pairs across the two blocks
 // (16 steps; step r pairs row i of block p with row (i + r) mod 16 of block
 // q).  The outer sweep thus meets every index pair of G once, as a cyclic
 // Jacobi sweep does.  Thread (a, b) = (tid % 16, tid / 16) owns the 2 x 2
@@ -208,32 +208,16 @@ __device__ __forceinline__ int rr_player(int pos, int r, int n) {
 // double-buffered in LDS, so a step needs one barrier.  The unitary takes a
 // step's rotation one step late, while the next step's operands are read
 // (round 0), or holds it in registers (the cross rounds, below).
-// Writes U (32 x 32, column-major) to Uw[pair] and flags the pair in pflag
-// when it rotated.  A subproblem whose off-diagonal entries are all at or
-// below thr is left alone (U = I is implied by pflag = 0).
-__global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t ld, int nbj, int round, c128* Uw,
-                                                         double thr, int max_sweeps, int* pflag) {
-  __shared__ c128 S[2][SP][SP + 1];
-  __shared__ c128 U[SP][SP + 1];
-  const int pair = blockIdx.x;
+// Writes U (32 x 32, column-major) to Uo and sets *flag when it rotated.  A
+// subproblem whose off-diagonal entries are all at or below thr (not needed) is
+// left alone (U = I is implied by *flag = 0).  U: LDS, the identity, only used
+// in round 0.
+template <bool CROSS>
+__device__ __forceinline__ void jacobi_block(c128 (*S)[SP][SP + 1], c128 (*U)[SP + 1], double thr, bool needed, c128* Uo,
+                                             int* flag) {
   const int tid = threadIdx.x;
-  const int bp = rr_player(pair, round, nbj), bq = rr_player(nbj - 1 - pair, round, nbj);
-  const int P = min(bp, bq) * JB, Q = max(bp, bq) * JB;
-  int big = 0;
-  for (int t = tid; t < SP * SP; t += 256) {
-    const int j = t / SP, i = t % SP;
-    const int gi = i < JB ? P + i : Q + i - JB;
-    const int gj = j < JB ? P + j : Q + j - JB;
-    const c128 g = G[(int64_t)gj * ld + gi];
-    S[0][i][j] = g;
-    U[i][j] = (i == j) ? c128{1.0, 0.0} : c128{0.0, 0.0};
-    if (i != j && g.re * g.re + g.im * g.im > thr * thr) big = 1;
-  }
-  const bool needed = __syncthreads_or(big);
   const int a = tid % (SP / 2), b = tid / (SP / 2);
-  const bool cross = round > 0;
-  const int nsteps = cross ? JB : SP - 1;
-  int total = 0;
+  constexpr int nsteps = CROSS ? JB : SP - 1;
   // U <- U J on the columns (up, uq) of a rotation (c, s), rows b and b + 16
   auto rotate_u = [&](int up_col, int uq_col, double c, c128 sr) {
 #pragma unroll
@@ -250,8 +234,8 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
   // lane down the row of 16 lanes (DPP row rotation) after each step; after
   // the 16 steps q is 16 + a again.
   c128 up0{a == b ? 1.0 : 0.0, 0.0}, up1{0.0, 0.0}, uq0{0.0, 0.0}, uq1{a == b ? 1.0 : 0.0, 0.0};
-  for (int sweep = 0; needed && sweep < max_sweeps; ++sweep) {
-    int did_any = 0;
+  int did_any = 0;
+  if (needed) {
     int lp = 0, lq = 0;  // the previous step's rotation a, not yet applied to U
     double lc = 1.0;
     c128 ls{0.0, 0.0};
@@ -259,7 +243,7 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
       const c128 (*cur)[SP + 1] = S[r & 1];
       c128 (*nxt)[SP + 1] = S[(r + 1) & 1];
       int pa, qa, pb, qb;
-      if (cross) {
+      if constexpr (CROSS) {
         pa = a;
         qa = JB + ((a + r) & (JB - 1));
         pb = b;
@@ -275,7 +259,7 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
       const double app = cur[pa][pa].re, aqq = cur[qa][qa].re;
       const c128 apq = cur[pa][qa];
       const c128 x00 = cur[pa][pb], x01 = cur[pa][qb], x10 = cur[qa][pb], x11 = cur[qa][qb];
-      if (!cross && r > 0) rotate_u(lp, lq, lc, ls);
+      if (!CROSS && r > 0) rotate_u(lp, lq, lc, ls);
       double ca, ta;
       c128 sa;
       int da;
@@ -309,7 +293,7 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
       nxt[pa][qb] = z01;
       nxt[qa][pb] = z10;
       nxt[qa][qb] = z11;
-      if (cross) {
+      if constexpr (CROSS) {
         // U <- U J on columns a and q: col_a' = c col_a - conj(s) col_q,
         // col_q' = s col_a + c col_q; then q moves on (lane a takes lane a + 1's)
         const c128 n0 = csub(cscale(ca, up0), cmul(cconj(sa), uq0));
@@ -327,28 +311,41 @@ __global__ __launch_bounds__(256) void jacobi_sub_kernel(const c128* G, int64_t 
       ls = sa;
       __syncthreads();
     }
-    if (!cross) rotate_u(lp, lq, lc, ls);
-    // the sweep's result is in S[nsteps & 1]; a further sweep starts from S[0]
-    if ((nsteps & 1) && sweep + 1 < max_sweeps) {
-      for (int t = tid; t < SP * SP; t += 256) S[0][t % SP][t / SP] = S[1][t % SP][t / SP];
-    }
-    if (!__syncthreads_or(did_any)) break;
-    ++total;
+    if (!CROSS) rotate_u(lp, lq, lc, ls);
   }
-  if (tid == 0) pflag[pair] = total > 0;
-  if (total == 0) return;
-  c128* Uo = Uw + (int64_t)pair * SP * SP;
-  if (cross) {
+  const bool rotated = __syncthreads_or(did_any);
+  if (tid == 0) *flag = rotated;
+  if (!rotated) return;
+  if constexpr (CROSS) {
     Uo[a * SP + b] = up0;
     Uo[a * SP + b + JB] = up1;
     Uo[(JB + a) * SP + b] = uq0;
     Uo[(JB + a) * SP + b + JB] = uq1;
-    return;
+  } else {
+    for (int t = tid; t < SP * SP; t += 256) Uo[t] = U[t % SP][t / SP];
   }
-  for (int t = tid; t < SP * SP; t += 256) {
+}
+
+// Round 0 of a sweep, workgroup = pair.
+__global__ __launch_bounds__(256) void jacobi_first_kernel(const c128* G, int64_t ld, int nbj, c128* Uw, double thr,
+                                                           int* pflag) {
+  __shared__ c128 S[2][SP][SP + 1];
+  __shared__ c128 U[SP][SP + 1];
+  const int pair = blockIdx.x;
+  const int bp = rr_player(pair, 0, nbj), bq = rr_player(nbj - 1 - pair, 0, nbj);
+  const int P = min(bp, bq) * JB, Q = max(bp, bq) * JB;
+  int big = 0;
+  for (int t = threadIdx.x; t < SP * SP; t += 256) {
     const int j = t / SP, i = t % SP;
-    Uo[(int64_t)j * SP + i] = U[i][j];
+    const int gi = i < JB ? P + i : Q + i - JB;
+    const int gj = j < JB ? P + j : Q + j - JB;
+    const c128 g = G[(int64_t)gj * ld + gi];
+    S[0][i][j] = g;
+    U[i][j] = (i == j) ? c128{1.0, 0.0} : c128{0.0, 0.0};
+    if (i != j && g.re * g.re + g.im * g.im > thr * thr) big = 1;
   }
+  const bool needed = __syncthreads_or(big);
+  jacobi_block<false>(S, U, thr, needed, Uw + (int64_t)pair * SP * SP, pflag + pair);
 }
 
 // Index of row/col i (0..2*JB-1) of the subproblem of pair `pair` in round `round`.
@@ -379,24 +376,109 @@ __device__ __forceinline__ void cgemm_tile32(int lane, FA a, FB b, doublex4& cr,
   }
 }
 
-// G <- J^H G J with J block-diagonal (one 32 x 32 U per pair, in the pair's
-// index set); block (a, b) of pairs is U_a^H G_ab U_b.  G stays Hermitian,
-// so only the blocks a <= b are formed and each is also written, conjugate
-// transposed, to (b, a) (a diagonal block from its upper triangle).  Also
-// V <- V J on row chunks of 32.  blockIdx.x < npair (npair + 1) / 2: G
-// blocks; the rest: V blocks.  The data block and the rotation blocks are
-// staged in LDS; each of the four waves computes one 16 x 16 quarter of each
-// 32 x 32 product on MFMA.
-__global__ __launch_bounds__(256) void jacobi_apply_kernel(c128* G, c128* V, int64_t ld, int kp, int nbj, int round,
-                                                           const c128* Uw, const int* pflag) {
-  __shared__ c128 X[SP][SP + 1];
-  __shared__ c128 Y[SP][SP + 1];
-  __shared__ c128 UA[SP][SP + 1];
-  __shared__ c128 UB[SP][SP + 1];
+// The same tile, operands given: v[q], z[q] at k = 4 q + lane / 16.
+__device__ __forceinline__ void cgemm_k32(const c128 (&v)[8], const c128 (&z)[8], doublex4& cr, doublex4& ci) {
+  cr = doublex4{0, 0, 0, 0};
+  ci = doublex4{0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q].re, z[q].re, cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q].re, z[q].im, ci, 0, 0, 0);
+    cr = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q].im, -z[q].im, cr, 0, 0, 0);
+    ci = __builtin_amdgcn_mfma_f64_16x16x4f64(v[q].im, z[q].re, ci, 0, 0, 0);
+  }
+}
+
+// The pair that block p plays in round r, and whether p is its upper half.
+__device__ __forceinline__ int pair_of(int p, int r, int n, int* half) {
+  const int pos = p == 0 ? 0 : (p - 1 - r + (n - 1)) % (n - 1) + 1;
+  *half = p > rr_player(n - 1 - pos, r, n);
+  return min(pos, n - 1 - pos);
+}
+
+// The rotations of pair `pair` of round `round` + 1 from G as it is before the
+// rotations Uw of round `round`: the three 16 x 16 blocks of the subproblem are
+// taken through those first (T = X U, S = U^H T, on the MFMA).
+__device__ __forceinline__ void next_rotations(c128* lds, const c128* G, int64_t ld, int nbj, int round, int pair,
+                                               const c128* Uw, const int* pflag, c128* Uo, int* flag, double thr) {
+  c128 (*S)[SP][SP + 1] = reinterpret_cast<c128 (*)[SP][SP + 1]>(lds);
+  c128 (*T)[SP][JB + 1] = reinterpret_cast<c128 (*)[SP][JB + 1]>(lds + 2 * SP * (SP + 1));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lk = lane >> 4;
+  const int x = rr_player(pair, round + 1, nbj), y = rr_player(nbj - 1 - pair, round + 1, nbj);
+  int hp, hq;
+  const int a = pair_of(min(x, y), round, nbj, &hp), b = pair_of(max(x, y), round, nbj, &hq);
+  // column 16 h + li of the rotation of pair c, row k
+  auto u = [&](int c, int h, int k) __attribute__((always_inline)) {
+    return pflag[c] ? Uw[(int64_t)c * SP * SP + (JB * h + li) * SP + k] : c128{k == JB * h + li ? 1.0 : 0.0, 0.0};
+  };
+  // T[0] = X_aa U_a, T[1] = X_bb U_b, T[2] = X_ab U_b: 16 columns each
+  for (int t = wave; t < 6; t += 4) {
+    const int w = t >> 1, row = w == 1 ? b : a, col = w == 0 ? a : b, h = w == 0 ? hp : hq;
+    const int gi = sub_index(row, round, nbj, JB * (t & 1) + li);
+    c128 v[8], z[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      v[q] = G[(int64_t)sub_index(col, round, nbj, 4 * q + lk) * ld + gi];
+      z[q] = u(col, h, 4 * q + lk);
+    }
+    doublex4 cr, ci;
+    cgemm_k32(v, z, cr, ci);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) T[w][JB * (t & 1) + lk + 4 * r][li] = c128{cr[r], ci[r]};
+  }
+  __syncthreads();
+  int big = 0;
+  if (wave < 3) {  // blocks pp, qq, pq
+    const int c = wave == 1 ? b : a, h = wave == 1 ? hq : hp;
+    c128 v[8], z[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      v[q] = cconj(u(c, h, 4 * q + lk));
+      z[q] = T[wave][4 * q + lk][li];
+    }
+    doublex4 cr, ci;
+    cgemm_k32(v, z, cr, ci);
+    const int i0 = wave == 1 ? JB : 0, j0 = wave == 0 ? 0 : JB;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + lk + 4 * r, j = j0 + li;
+      const c128 g{cr[r], i == j ? 0.0 : ci[r]};
+      S[0][i][j] = g;
+      if (wave == 2) S[0][j][i] = cconj(g);
+      if (i != j && g.re * g.re + g.im * g.im > thr * thr) big = 1;
+    }
+  }
+  const bool needed = __syncthreads_or(big);
+  jacobi_block<true>(S, nullptr, thr, needed, Uo, flag);
+}
+
+// Round `round`: Gn = J^H G J with J block-diagonal (one 32 x 32 U per pair, in
+// the pair's index set); block (a, b) of pairs is U_a^H G_ab U_b.  G stays
+// Hermitian, so only the blocks a <= b are formed and each is also written,
+// conjugate transposed, to (b, a) (a diagonal block from its upper triangle).
+// Also V <- V J on row chunks of 32.  The first nspec = npair workgroups
+// compute the next round's rotations meanwhile (none in the last round); then
+// npair (npair + 1) / 2 G blocks; the rest: V blocks.  The data block and the
+// rotation blocks are staged in LDS; each of the four waves computes one
+// 16 x 16 quarter of each 32 x 32 product on MFMA.  Bound by the chain of a
+// round's 16 rotation steps (0.65 us each); kp = 384: 20.9 us a
+// round, with rotations and update in launches of their own 25.5
+__global__ __launch_bounds__(256) void jacobi_round_kernel(const c128* G, c128* Gn, c128* V, int64_t ld, int kp, int nbj,
+                                                           int round, const c128* Uw, const int* pflag, c128* Un,
+                                                           int* pflagn, double thr, int nspec) {
+  __shared__ c128 lds[4 * SP * (SP + 1)];
+  if ((int)blockIdx.x < nspec) {
+    next_rotations(lds, G, ld, nbj, round, blockIdx.x, Uw, pflag, Un + (int64_t)blockIdx.x * SP * SP,
+                   pflagn + blockIdx.x, thr);
+    return;
+  }
+  c128 (*X)[SP + 1] = reinterpret_cast<c128 (*)[SP + 1]>(lds);
+  c128 (*Y)[SP + 1] = X + SP, (*UA)[SP + 1] = X + 2 * SP, (*UB)[SP + 1] = X + 3 * SP;
   const int npair = nbj / 2;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r0 = (wave >> 1) * 16, c0 = (wave & 1) * 16;  // this wave's quarter
-  int blk = blockIdx.x;
+  int blk = blockIdx.x - nspec;
   doublex4 cr, ci;
   const int ntri = npair * (npair + 1) / 2;
   if (blk < ntri) {
@@ -408,7 +490,6 @@ __global__ __launch_bounds__(256) void jacobi_apply_kernel(c128* G, c128* V, int
     }
     const int b = a + rest;
     const bool ua = pflag[a], ub = pflag[b];
-    if (!ua && !ub) return;  // both rotations are the identity
     const c128* Ua = Uw + (int64_t)a * SP * SP;
     const c128* Ub = Uw + (int64_t)b * SP * SP;
     for (int t = tid; t < SP * SP; t += 256) {
@@ -449,13 +530,13 @@ __global__ __launch_bounds__(256) void jacobi_apply_kernel(c128* G, c128* V, int
       const int i = r0 + (lane >> 4) + 4 * r, j = c0 + (lane & 15);
       const int gi = sub_index(a, round, nbj, i), gj = sub_index(b, round, nbj, j);
       if (a != b) {
-        G[(int64_t)gj * ld + gi] = c128{cr[r], ci[r]};
-        G[(int64_t)gi * ld + gj] = c128{cr[r], -ci[r]};
+        Gn[(int64_t)gj * ld + gi] = c128{cr[r], ci[r]};
+        Gn[(int64_t)gi * ld + gj] = c128{cr[r], -ci[r]};
       } else if (i < j) {
-        G[(int64_t)gj * ld + gi] = c128{cr[r], ci[r]};
-        G[(int64_t)gi * ld + gj] = c128{cr[r], -ci[r]};
+        Gn[(int64_t)gj * ld + gi] = c128{cr[r], ci[r]};
+        Gn[(int64_t)gi * ld + gj] = c128{cr[r], -ci[r]};
       } else if (i == j) {
-        G[(int64_t)gj * ld + gi] = c128{cr[r], 0.0};
+        Gn[(int64_t)gj * ld + gi] = c128{cr[r], 0.0};
       }
     }
   } else {
@@ -767,9 +848,9 @@ constexpr double REFINE_MAX = 0.04, REFINE_SHORT = 1e-4;
 // e_ij = o_ij / (d_j - d_i), the unitary W = E + sqrt(I + E^2) =
 // E + I + T / 2 - T^2 / 8 + T^3 / 16 - 5 T^4 / 128 + ... (T = E^2) takes G to
 // W^H G W with off-diagonal part [O, E] / 2 to second order, ||O||_F ||E||_F
-// at most: quadratic like a sweep, which is kp / 16 - 1 rounds of two
-// dependent launches.  At kp = 384 a sweep takes 590 us (26 a round), a step 270,
-// the last one, which leaves G alone, 100; a Rayleigh-Ritz step at m = 4000 and
+// at most: quadratic like a sweep, which is kp / 16 - 1 dependent
+// launches.  At kp = 384 a sweep takes 500 us (21 a round), a step 150,
+// the last one, which leaves G alone, 60; a Rayleigh-Ritz step at m = 4000 and
 // k = 376 went from 5.06 ms to 4.41, one of the converging iterations at k = 500
 // (m = 4000) from 3 sweeps to 1 or 2.
 Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out, int guard,
@@ -778,15 +859,13 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   const int npair = nbj / 2;
   CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s));
   CHASE_TRY(frob_norm(G, kp, ws, s, nullptr));
-  // One cyclic sweep per subproblem: block Jacobi with approximate
-  // subproblem solutions needs about as many outer sweeps as with exact ones
-  // and a fraction of the inner work.
-  const int inner_sweeps = 1;
+  // G is in cur; every round writes it to o[0] and the two change places.
+  c128 *cur = G, *o[3] = {ws.k1, ws.k2, ws.k3};
   double* part = reinterpret_cast<double*>(ws.panel);  // 3 kp doubles
   int sweep = 0;
   bool converged = false;
   for (;;) {
-    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)G, kp, (const double*)ws.dscalar,
+    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)cur, kp, (const double*)ws.dscalar,
                        part);
     CHASE_LAUNCH_CHECK();
     hipLaunchKernelGGL(offdiag_sum_kernel, dim3(3), dim3(256), 0, s, (const double*)part, kp, ws.dscalar + 1);
@@ -807,8 +886,8 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     ++sweep;
     if (ef <= REFINE_MAX) {
       const int blocks = grid_for((int64_t)kp * kp);
-      c128 *W = ws.k1, *T = ws.k2, *T2 = ef > REFINE_SHORT ? ws.k3 : nullptr;
-      hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)G, W, kp, thr * thr);
+      c128 *W = o[0], *T = o[1], *T2 = ef > REFINE_SHORT ? o[2] : nullptr;
+      hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, W, kp, thr * thr);
       CHASE_LAUNCH_CHECK();
       CHASE_TRY(gemm_kp(0, kp, W, W, 0.0, T, ws, s));
       if (T2) CHASE_TRY(gemm_kp(0, kp, T, T, 0.0, T2, ws, s));
@@ -821,20 +900,27 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
         converged = true;
         break;
       }
-      CHASE_TRY(gemm_kp(0, kp, G, W, 0.0, T, ws, s));
-      CHASE_TRY(gemm_kp(1, kp, W, T, 0.0, G, ws, s));
+      CHASE_TRY(gemm_kp(0, kp, cur, W, 0.0, T, ws, s));
+      CHASE_TRY(gemm_kp(1, kp, W, T, 0.0, cur, ws, s));
       continue;
     }
+    // U and flags of a round and of the next
+    c128* U[2] = {ws.U, ws.U + (int64_t)npair * SP * SP};
+    int* fl[2] = {ws.pflag, ws.pflag + npair};
+    hipLaunchKernelGGL(jacobi_first_kernel, dim3(npair), dim3(256), 0, s, (const c128*)cur, (int64_t)kp, nbj, U[0], thr,
+                       fl[0]);
+    CHASE_LAUNCH_CHECK();
     for (int r = 0; r < nbj - 1; ++r) {
-      hipLaunchKernelGGL(jacobi_sub_kernel, dim3(npair), dim3(256), 0, s, (const c128*)G, (int64_t)kp, nbj, r,
-                         ws.U, thr, inner_sweeps, ws.pflag);
+      const int nspec = r < nbj - 2 ? npair : 0;
+      const int blocks = nspec + npair * (npair + 1) / 2 + npair * (kp / SP);
+      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, o[0], V, (int64_t)kp, kp,
+                         nbj, r, (const c128*)U[r & 1], (const int*)fl[r & 1], U[(r + 1) & 1], fl[(r + 1) & 1], thr,
+                         nspec);
       CHASE_LAUNCH_CHECK();
-      const int blocks = npair * (npair + 1) / 2 + npair * (kp / SP);
-      hipLaunchKernelGGL(jacobi_apply_kernel, dim3(blocks), dim3(256), 0, s, G, V, (int64_t)kp, kp, nbj, r,
-                         (const c128*)ws.U, (const int*)ws.pflag);
-      CHASE_LAUNCH_CHECK();
+      std::swap(cur, o[0]);
     }
   }
+  if (cur != G) CHASE_HIP(hipMemcpyAsync(G, cur, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
   if (sweeps_out) *sweeps_out = sweep;
   if (!converged)
     return fail(CHASE_PH_ERR_EIG, "Jacobi eigensolver: off-diagonal entries above 1e-16 ||G||_F after " +
