@@ -24,7 +24,7 @@
 //  * GEMM: both operand tiles copied HBM -> LDS by the gfx950
 //    direct-to-LDS load (global_load_lds_dwordx4: lane l's 16 bytes land at
 //    the wave's LDS base + 16 l) into a ring of LDS stages, NST - 1 slabs
-//    ahead; real MFMAs (f32 32x32x2 or 16x16x4, f64 16x16x4);
+//    ahead; real MFMAs (f32 32x32x2 or 16x16x4);
 //  * epilogue: a lane holds the real and imaginary part of t for one
 //    column of the pair (u_j or v_j) and takes the other from its
 //    neighbour lane (l ^ 1); the u lane writes row i of H x_j, the v lane
@@ -53,8 +53,7 @@ using C = c64;
 // MFMA shapes.  phys_row(r, l): the real row (within a fragment of MB rows)
 // of accumulator r of lane l; the accumulators 2t, 2t + 1 hold the real rows
 // 2i, 2i + 1 of one complex row i.  a_row(l): the fragment row whose A
-// operand lane l supplies (a permutation for the f64 shape, so that the
-// output rows land as stated).
+// operand lane l supplies.
 struct TF32 {  // v_mfma_f32_32x32x2f32
   using Acc = floatx16;
   static constexpr int MB = 32, NB = 32, KB = 2, NACC = 16;
@@ -234,9 +233,9 @@ struct Cfg {
   static constexpr int CW = 64 * V / 2;                  // Y columns per copy (one row pair)
   static constexpr int BNP = (BN + CW - 1) / CW * CW;     // Y columns per LDS row pair
   // k-row pitch of the M stage: a 32-lane half of a wave reads 32 words of
-  // one k row and the other half the next k row (f32); half a pitch of 32
-  // words puts the two halves on disjoint banks (f64: 16 doubles)
-  static constexpr int SA = BM + (sizeof(R) == 4 ? 32 : 16);
+  // one k row and the other half the next k row; half a pitch of 32
+  // words puts the two halves on disjoint banks
+  static constexpr int SA = BM + 32;
   static constexpr int PARTS = BM / (64 * V);             // copies per k column of M
   static constexpr int ACOP = BK * PARTS;                 // copies of the M tile per slab
   static constexpr int BCOP = (BK / 2) * (BNP / CW);     // copies of the Y tile per slab
@@ -262,20 +261,10 @@ struct Cfg {
 // Scheduling of one K step (measured on the m = 4000 shapes): SCHED 1 lets
 // the compiler interleave the fragment reads of the slab with its MFMAs
 // (iglp_opt(0): 72-77% of the FP32 peak on the 256 x 128 tile against
-// 69-73% without); SCHED 3 places one read after every two MFMAs (c128
-// 128 x 128 tile: 76% against 74%).
+// 69-73% without).
 template <int SCHED>
 __device__ __forceinline__ void step_schedule() {
   if constexpr (SCHED == 1) __builtin_amdgcn_iglp_opt(0);
-  if constexpr (SCHED == 3) {
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);  // 2 MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // 1 DS read
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
-  }
 }
 
 // One tile of the GEMM: workgroup bid of the T * splits workgroups of a
@@ -391,11 +380,9 @@ __device__ __forceinline__ void hx_tile(const ApplyHArgs& a, int splits, int kps
         for (int ks = 0; ks < BK; ks += Tr::KB) {
           const int b = (ks / Tr::KB) & 1;
           if (ks + Tr::KB < BK) load(ks + Tr::KB, b ^ 1);
-          // f32: raised issue priority while this wave feeds the matrix
-          // core, so that the other wave on the SIMD takes its copy / wait /
-          // barrier part meanwhile (c64 calls 2.5-5% faster on m = 4000,
-          // k = 64..260; the f64 tiles, scheduled by sched_group_barrier,
-          // were 5-7% slower with it)
+          // raised issue priority while this wave feeds the matrix core, so
+          // that the other wave on the SIMD takes its copy / wait / barrier
+          // part meanwhile (2.5-5% faster calls on m = 4000, k = 64..260)
           __builtin_amdgcn_s_setprio(1);
 #pragma unroll
           for (int i = 0; i < FM; ++i)
@@ -611,12 +598,9 @@ Err launch_pair_cfg(const ApplyHArgs& am, const Plan& pm, void* wsm,
 
 // Tile shapes (BM x BN reals, K slab BK, NST ring stages), two workgroups
 // per CU (at most 80 KB of LDS):
-//  c64:  0  256 x 128, BK 16, 3 stages, 32x32x2 (wave tile 64 x 128), SCHED 1
-//        1  256 x 64,  BK 16, 3 stages, 32x32x2 (64 x 64), SCHED 1
-//        2  256 x 32,  BK 16, 3 stages, 16x16x4 (64 x 32; narrow launches)
-//  c128: 0  128 x 128, BK 8,  4 stages, 16x16x4 f64 (2 x 2 waves of 64 x 64), SCHED 3
-//        1  128 x 64,  BK 8,  4 stages (64 x 32)
-//        2  128 x 32,  BK 8,  4 stages, 4 x 1 waves (32 x 32; narrow launches)
+//  0  256 x 128, BK 16, 3 stages, 32x32x2 (wave tile 64 x 128), SCHED 1
+//  1  256 x 64,  BK 16, 3 stages, 32x32x2 (64 x 64), SCHED 1
+//  2  256 x 32,  BK 16, 3 stages, 16x16x4 (64 x 32; narrow launches)
 struct F32Tiles {
   static constexpr int bm[3] = {256, 256, 256}, bn[3] = {128, 64, 32}, bk[3] = {16, 16, 16};
   static constexpr double eff[3] = {1.0, 0.95, 0.8};
