@@ -1710,6 +1710,7 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   h->dws.k1 = h->Nb;
   h->dws.k2 = h->Tk;
   h->dws.k3 = h->L3;
+  h->dws.k4 = h->L2;
   h->dws.gemm_ws = h->ws;
   h->dws.gemm_ws_bytes = h->ws_bytes;
   h->hhw.gemm_ws = h->ws;

@@ -8,7 +8,7 @@ struct DenseWs {
   c128* panel = nullptr;   // kp_max x 64
   c128* tmp = nullptr;     // kp_max x 64 (batched 64 x 64 blocks)
   c128* U = nullptr;       // kp_max x 64 (one rotation block per Jacobi pair)
-  c128 *k1 = nullptr, *k2 = nullptr, *k3 = nullptr;  // kp_max x kp_max each (jacobi_eigh)
+  c128 *k1 = nullptr, *k2 = nullptr, *k3 = nullptr, *k4 = nullptr;  // kp_max x kp_max each (jacobi_eigh)
   int* flag = nullptr;     // 4 ints: positives, negatives (select_positive), two Cholesky breakdowns
   int* pflag = nullptr;    // kp_max / 8 ints (Jacobi pair rotated?)
   double* dscalar = nullptr;  // 4 doubles

@@ -803,8 +803,9 @@ __global__ void refine_e_kernel(const c128* G, c128* E, int kp, double thr2) {
 }
 
 // With T = E^2 and T2 = T^2 (null: the terms past T are below rounding):
-// E <- I + E + T / 2 - T2 / 8 and T <- T / 16 - 5 T2 / 128.
-__global__ void refine_w_kernel(c128* E, c128* T, const c128* T2, int kp) {
+// E <- I + E + T / 2 - T2 / 8, T <- T / 16 - 5 T2 / 128 and, where given,
+// Z = 7 T / 256 - 21 T2 / 1024.
+__global__ void refine_w_kernel(c128* E, c128* T, const c128* T2, c128* Z, int kp) {
   const int64_t total = (int64_t)kp * kp;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
     const c128 f = T[t];
@@ -816,6 +817,7 @@ __global__ void refine_w_kernel(c128* E, c128* T, const c128* T2, int kp) {
       w.re -= 0.125 * h.re;
       w.im -= 0.125 * h.im;
       T[t] = c128{0.0625 * f.re - 0.0390625 * h.re, 0.0625 * f.im - 0.0390625 * h.im};
+      if (Z) Z[t] = c128{0.02734375 * f.re - 0.0205078125 * h.re, 0.02734375 * f.im - 0.0205078125 * h.im};
     }
     E[t] = w;
   }
@@ -838,15 +840,19 @@ static Err gemm_kp(int ta, int kp, const c128* A, const c128* B, double beta, c1
 }
 
 // Largest ||E||_F at which a sweep is replaced by a refinement step: there the
-// first term left out of W, 7/256 E^10, is below rounding; and up to which
-// that of the short form I + E + E^2 / 2, E^4 / 8, is.
-constexpr double REFINE_MAX = 0.04, REFINE_SHORT = 1e-4;
+// first term left out of W, 33/2048 E^14, is below rounding; up to which that
+// of the form with E^8, 7/256 E^10, is; and that of I + E + E^2 / 2, E^4 / 8.
+// From 0.05 on, a sweep (500 us at kp = 384) and two steps are left, or four
+// steps of 60 to 180 us: Rayleigh-Ritz m = 4000, k = 376 4.19 -> 3.80 ms against a
+// limit of 0.04.
+constexpr double REFINE_MAX = 0.1, REFINE_MID = 0.04, REFINE_SHORT = 1e-4;
 
 // Eigenvectors V and (on the diagonal) eigenvalues of the Hermitian G: block
 // Jacobi sweeps until the off-diagonal entries are small against the gaps of
 // the diagonal, then GEMMs.  With D the diagonal, O the rest and
 // e_ij = o_ij / (d_j - d_i), the unitary W = E + sqrt(I + E^2) =
-// E + I + T / 2 - T^2 / 8 + T^3 / 16 - 5 T^4 / 128 + ... (T = E^2) takes G to
+// E + I + T / 2 - T^2 / 8 + T^3 / 16 - 5 T^4 / 128 + 7 T^5 / 256 - 21 T^6 / 1024
+// + ... (T = E^2) takes G to
 // W^H G W with off-diagonal part [O, E] / 2 to second order, ||O||_F ||E||_F
 // at most: quadratic like a sweep, which is kp / 16 - 1 dependent
 // launches.  At kp = 384 a sweep takes 500 us (21 a round), a step 150,
@@ -886,13 +892,14 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     ++sweep;
     if (ef <= REFINE_MAX) {
       const int blocks = grid_for((int64_t)kp * kp);
-      c128 *W = o[0], *T = o[1], *T2 = ef > REFINE_SHORT ? o[2] : nullptr;
+      c128 *W = o[0], *T = o[1], *T2 = ef > REFINE_SHORT ? o[2] : nullptr, *Z = ef > REFINE_MID ? ws.k4 : nullptr;
       hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, W, kp, thr * thr);
       CHASE_LAUNCH_CHECK();
       CHASE_TRY(gemm_kp(0, kp, W, W, 0.0, T, ws, s));
       if (T2) CHASE_TRY(gemm_kp(0, kp, T, T, 0.0, T2, ws, s));
-      hipLaunchKernelGGL(refine_w_kernel, dim3(blocks), dim3(256), 0, s, W, T, (const c128*)T2, kp);
+      hipLaunchKernelGGL(refine_w_kernel, dim3(blocks), dim3(256), 0, s, W, T, (const c128*)T2, Z, kp);
       CHASE_LAUNCH_CHECK();
+      if (Z) CHASE_TRY(gemm_kp(0, kp, T2, Z, 1.0, T, ws, s));
       if (T2) CHASE_TRY(gemm_kp(0, kp, T2, T, 1.0, W, ws, s));
       CHASE_TRY(gemm_kp(0, kp, V, W, 0.0, T, ws, s));
       CHASE_HIP(hipMemcpyAsync(V, T, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));

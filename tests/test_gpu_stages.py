@@ -453,6 +453,14 @@ def test_rr_near_diagonal_quotient(prob, solver80, kh, eps):
     assert np.max(np.abs(G / np.outer(d, d) - np.eye(kh))) < 1e-11
 
 
+# the same further from diagonal, around the limits of the refinement steps
+# (||o_ij / (g_jj - g_ii)||_F of 0.04 and 0.1): the series to E^8, to E^12, sweeps
+@pytest.mark.parametrize("kh", [6, 32])
+@pytest.mark.parametrize("eps", [3e-2, 6e-2, 0.1, 0.2, 0.4])
+def test_rr_refinement_limits(prob, solver80, kh, eps):
+    test_rr_near_diagonal_quotient(prob, solver80, kh, eps)
+
+
 def _unit_ritz(Q, Z):
     V = Q @ Z
     return V / np.linalg.norm(V, axis=0)[None, :]
