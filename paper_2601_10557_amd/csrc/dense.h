@@ -32,7 +32,7 @@ int pad64(int k);
 // M = diag(inner) on the first k, pad on the rest; off-diagonals zeroed
 // everywhere when zero_all, else only in the padded rows/columns.
 Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s,
-                int* clear = nullptr);  // *clear = 0 too
+                int* clear = nullptr, int nclear = 1);  // clear[0 .. nclear - 1] = 0 too
 // In place lower Cholesky of a Hermitian padded matrix (lower triangle given)
 // and X = L^{-1} (chol.hip; both ld kp); ws.flag[slot] != 0 on breakdown, both
 // then unspecified.
@@ -47,7 +47,8 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
 // Positive eigenvalues theta of the first k: Ysel (kp x k/2, ld kp) and
 // dlam[r] = 1/theta for rank r by descending theta; the numbers of positive
 // and negative ones in ws.flag[COUNTS] and the next (columns of Ysel past the
-// first are unspecified).
+// first are unspecified).  Follows jacobi_eigh, which leaves ||G||_F in dscalar
+// and the counters at zero.
 Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, double* dlam, DenseWs& ws,
                     hipStream_t s);
 

@@ -35,9 +35,9 @@ __device__ __forceinline__ c128 cfms(c128 r, c128 a, c128 b) {
 
 // ---------------------------------------------------------------- fills
 __global__ void fill_diag_kernel(c128* M, int64_t ld, int kp, int k, double inner, double pad, int zero_all,
-                                 int* clear) {
+                                 int* clear, int nclear) {
   const int64_t total = (int64_t)kp * kp;
-  if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
+  if (blockIdx.x == 0 && (int)threadIdx.x < nclear) clear[threadIdx.x] = 0;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(t / kp), i = (int)(t % kp);
     c128* p = M + (int64_t)j * ld + i;
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const c128* G, c128* 
 
 // Frobenius norm in two deterministic stages: one block per column writes the
 // column's sum of squares, then one block adds the kp column sums in a fixed
-// order (and clears two counters).
+// order.
 __global__ __launch_bounds__(256) void frob_cols_kernel(const c128* G, int64_t ld, int kp, double* part) {
   __shared__ double red[256];
   const int64_t col = blockIdx.x;
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(256) void frob_cols_kernel(const c128* G, int64_t l
   if (threadIdx.x == 0) part[col] = red[0];
 }
 
-__global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int kp, double* out, int* clear2) {
+__global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int kp, double* out) {
   __shared__ double red[256];
   double s = 0;
   for (int i = threadIdx.x; i < kp; i += 256) s += part[i];
@@ -592,7 +592,6 @@ __global__ __launch_bounds__(256) void frob_sum_kernel(const double* part, int k
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = sqrt(red[0]);
-  if (clear2 && threadIdx.x < 2) clear2[threadIdx.x] = 0;
 }
 
 // Select eigenvalues theta > 0 of the first k diagonal entries, order them
@@ -681,19 +680,19 @@ Err h2d_small(void* dev, const void* host, size_t bytes, hipStream_t s) {
 static int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, 256), 2048)); }
 
 // dscalar[0] = ||G||_F
-static Err frob_norm(const c128* G, int kp, DenseWs& ws, hipStream_t s, int* clear2) {
+static Err frob_norm(const c128* G, int kp, DenseWs& ws, hipStream_t s) {
   double* part = reinterpret_cast<double*>(ws.panel);  // kp doubles (panel holds kp x 64 c128)
   hipLaunchKernelGGL(frob_cols_kernel, dim3(kp), dim3(256), 0, s, G, (int64_t)kp, kp, part);
   CHASE_LAUNCH_CHECK();
-  hipLaunchKernelGGL(frob_sum_kernel, dim3(1), dim3(256), 0, s, (const double*)part, kp, ws.dscalar,
-                     clear2);
+  hipLaunchKernelGGL(frob_sum_kernel, dim3(1), dim3(256), 0, s, (const double*)part, kp, ws.dscalar);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
 
-Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s, int* clear) {
+Err fill_padded(c128* M, int kp, int k, double inner, double pad, bool zero_all, hipStream_t s, int* clear,
+                int nclear) {
   hipLaunchKernelGGL(fill_diag_kernel, dim3(grid_for((int64_t)kp * kp)), dim3(256), 0, s, M, (int64_t)kp, kp, k,
-                     inner, pad, zero_all ? 1 : 0, clear);
+                     inner, pad, zero_all ? 1 : 0, clear, clear ? nclear : 0);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
@@ -767,6 +766,63 @@ __global__ __launch_bounds__(256) void offdiag_cols_kernel(const c128* G, int kp
     part[2 * kp + j] = any;
   }
 }
+
+// The same, and before the first sweep ||G||_F, in one workgroup for a small
+// G; the numbers and *guard go to pinned host memory: out[0] = ||G||_F,
+// out[1 .. 3] the sums, then the flag.  kp = 64: one launch for five, of about
+// 3.5 us each.
+__global__ __launch_bounds__(1024) void offdiag_small_kernel(const c128* G, int kp, int first, double* fro,
+                                                             const int* guard, double* out) {
+  __shared__ double red[2][1024];
+  const int tid = threadIdx.x, total = kp * kp;
+  auto sum = [&](double* r) {
+    __syncthreads();
+    for (int w = 512; w > 0; w >>= 1) {
+      if (tid < w) r[tid] += r[tid + w];
+      __syncthreads();
+    }
+    return r[0];
+  };
+  double norm;
+  if (first) {
+    double s = 0;
+    for (int t = tid; t < total; t += 1024) s += G[t].re * G[t].re + G[t].im * G[t].im;
+    red[0][tid] = s;
+    norm = sqrt(sum(red[0]));
+    __syncthreads();
+    if (tid == 0) *fro = norm;
+  } else {
+    norm = *fro;
+  }
+  const double thr2 = thr_of(norm) * thr_of(norm);
+  double so = 0, se = 0;
+  int big = 0;
+  for (int t = tid; t < total; t += 1024) {
+    const int j = t / kp, i = t % kp;
+    if (i == j) continue;
+    const c128 g = G[t];
+    const double o2 = g.re * g.re + g.im * g.im;
+    so += o2;
+    if (o2 > thr2) {
+      const double gap = G[(int64_t)i * kp + i].re - G[(int64_t)j * kp + j].re;
+      se += o2 / (gap * gap);
+      big = 1;
+    }
+  }
+  red[0][tid] = so;
+  red[1][tid] = se;
+  const int any = __syncthreads_or(big);
+  so = sum(red[0]);
+  se = sum(red[1]);
+  if (tid == 0) {
+    out[0] = norm;
+    out[1] = so;
+    out[2] = se;
+    out[3] = any;
+    *reinterpret_cast<int*>(out + 4) = guard ? *guard : 0;
+  }
+}
+constexpr int OFFDIAG_SMALL = 128;  // largest kp of offdiag_small_kernel: 16 entries a thread
 
 // out[b] = sum of part[b kp ... + kp - 1] in a fixed order, b = blockIdx.x.
 __global__ __launch_bounds__(256) void offdiag_sum_kernel(const double* part, int kp, double* out) {
@@ -863,22 +919,35 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
                 bool* tripped) {
   const int nbj = kp / JB;  // even since kp % 64 == 0
   const int npair = nbj / 2;
-  CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s));
-  CHASE_TRY(frob_norm(G, kp, ws, s, nullptr));
+  CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s, ws.flag + DenseWs::COUNTS, 2));
+  const bool small = kp <= OFFDIAG_SMALL && ws.hpin && ws.hpin_bytes >= 5 * sizeof(double);
+  if (!small) CHASE_TRY(frob_norm(G, kp, ws, s));
   // G is in cur; every round writes it to o[0] and the two change places.
-  c128 *cur = G, *o[3] = {ws.k1, ws.k2, ws.k3};
+  // V is in vec, which a refinement step exchanges with o[1].
+  c128 *cur = G, *vec = V, *o[3] = {ws.k1, ws.k2, ws.k3};
+  int first = 1;
   double* part = reinterpret_cast<double*>(ws.panel);  // 3 kp doubles
   int sweep = 0;
   bool converged = false;
   for (;;) {
-    hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)cur, kp, (const double*)ws.dscalar,
-                       part);
-    CHASE_LAUNCH_CHECK();
-    hipLaunchKernelGGL(offdiag_sum_kernel, dim3(3), dim3(256), 0, s, (const double*)part, kp, ws.dscalar + 1);
-    CHASE_LAUNCH_CHECK();
     double st[4] = {0, 0, 0, 0};
     int bad = 0;
-    CHASE_TRY(d2h_small(st, ws.dscalar, sizeof(st), ws, s, &bad, ws.flag + guard, guard < 0 ? 0 : sizeof(int)));
+    if (small) {
+      hipLaunchKernelGGL(offdiag_small_kernel, dim3(1), dim3(1024), 0, s, (const c128*)cur, kp, first, ws.dscalar,
+                         guard < 0 ? (const int*)nullptr : (const int*)ws.flag + guard, (double*)ws.hpin);
+      CHASE_LAUNCH_CHECK();
+      CHASE_HIP(hipStreamSynchronize(s));
+      std::memcpy(st, ws.hpin, sizeof(st));
+      std::memcpy(&bad, (const char*)ws.hpin + sizeof(st), sizeof(int));
+      first = 0;
+    } else {
+      hipLaunchKernelGGL(offdiag_cols_kernel, dim3(kp), dim3(256), 0, s, (const c128*)cur, kp,
+                         (const double*)ws.dscalar, part);
+      CHASE_LAUNCH_CHECK();
+      hipLaunchKernelGGL(offdiag_sum_kernel, dim3(3), dim3(256), 0, s, (const double*)part, kp, ws.dscalar + 1);
+      CHASE_LAUNCH_CHECK();
+      CHASE_TRY(d2h_small(st, ws.dscalar, sizeof(st), ws, s, &bad, ws.flag + guard, guard < 0 ? 0 : sizeof(int)));
+    }
     if (bad) {
       *tripped = true;
       return ok();
@@ -901,8 +970,9 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
       CHASE_LAUNCH_CHECK();
       if (Z) CHASE_TRY(gemm_kp(0, kp, T2, Z, 1.0, T, ws, s));
       if (T2) CHASE_TRY(gemm_kp(0, kp, T2, T, 1.0, W, ws, s));
-      CHASE_TRY(gemm_kp(0, kp, V, W, 0.0, T, ws, s));
-      CHASE_HIP(hipMemcpyAsync(V, T, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
+      CHASE_TRY(gemm_kp(0, kp, vec, W, 0.0, T, ws, s));
+      std::swap(vec, o[1]);
+      T = o[1];
       if (of * ef <= 0.5 * thr) {  // what is left off the diagonal, and its shift, is below thr
         converged = true;
         break;
@@ -920,13 +990,14 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     for (int r = 0; r < nbj - 1; ++r) {
       const int nspec = r < nbj - 2 ? npair : 0;
       const int blocks = nspec + npair * (npair + 1) / 2 + npair * (kp / SP);
-      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, o[0], V, (int64_t)kp, kp,
+      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, o[0], vec, (int64_t)kp, kp,
                          nbj, r, (const c128*)U[r & 1], (const int*)fl[r & 1], U[(r + 1) & 1], fl[(r + 1) & 1], thr,
                          nspec);
       CHASE_LAUNCH_CHECK();
       std::swap(cur, o[0]);
     }
   }
+  if (vec != V) CHASE_HIP(hipMemcpyAsync(V, vec, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
   if (cur != G) CHASE_HIP(hipMemcpyAsync(G, cur, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
   if (sweeps_out) *sweeps_out = sweep;
   if (!converged)
@@ -938,7 +1009,6 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
 Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, double* dlam, DenseWs& ws,
                     hipStream_t s) {
   int* counts = ws.flag + DenseWs::COUNTS;
-  CHASE_TRY(frob_norm(G, kp, ws, s, counts));
   hipLaunchKernelGGL(select_kernel, dim3(k), dim3(256), 0, s, G, V, (int64_t)kp, k, kp, (const double*)ws.dscalar, Ysel,
                      dlam, counts, counts + 1);
   CHASE_LAUNCH_CHECK();
