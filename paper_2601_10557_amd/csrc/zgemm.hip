@@ -14,6 +14,7 @@
 // products: waves of 32 x 32, four a workgroup, K split over workgroups where
 // the tiles leave CUs idle.  Small ones, bound by latency: the waves of a
 // workgroup share K.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -23,7 +24,6 @@ namespace {
 
 constexpr int NT = 256;
 constexpr int RK = 8;   // K slab
-constexpr int RT = 64;  // large products: RT x RT outputs of a workgroup, 32 x 32 a wave
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 
@@ -48,7 +48,7 @@ struct ZgemmDev {
   int TM, TN;      // workgroup tiles of a large product (not lower_only)
   int tiles;
   int64_t kchunk;  // K range per split
-  c128* ws;        // split-K partials: one RT x RT tile per (split, batch, tile)
+  c128* ws;        // split-K partials: a workgroup's outputs per (split, batch, tile)
 };
 
 // Lane l of a fragment of 16 rows (columns) and 8 k holds row l % 16 at k = 2 (l / 16) + s, s = 0, 1: two loads of one c128, 128 contiguous
@@ -61,13 +61,14 @@ __device__ __forceinline__ int xcd_remap(int w, int T) {
   return xcd * q + (xcd < r ? xcd : r) + slot;
 }
 
-// First row and column of a wave's 32 x 32 outputs in workgroup tile t, false
+// First row and column of a wave's U x U outputs in workgroup tile t, false
 // if it has none.  lower_only: the tiles of the lower triangle row by row, four
 // neighbours a workgroup (no wave above the diagonal).  With a triangular
-// operand the four waves have the same K range, 128 rows of a column (b_upper)
-// or 128 columns of a row (a_lower), the longest ranges first.  Else 2 x 2.
+// operand the four waves have the same K range, 4 U rows of a column (b_upper)
+// or 4 U columns of a row (a_lower), the longest ranges first.  Else 2 x 2.
 // 8000 x 520 x 520 upper: 270 us strip by strip, 198 us longest first in 64 x 64 tiles, 183 so;
 // 520 x 520 x 8000 lower: 200 us on 2 x 2, 171 so.
+template <int U>
 __device__ __forceinline__ bool wave_tile(const ZgemmDev& g, int t, int wave, int64_t* m0, int64_t* n0) {
   int i, j;
   if (g.lower_only) {
@@ -89,8 +90,8 @@ __device__ __forceinline__ bool wave_tile(const ZgemmDev& g, int t, int wave, in
     j = 2 * (t - i * g.TN) + (wave & 1);
     i = 2 * i + (wave >> 1);
   }
-  *m0 = 32 * (int64_t)i;
-  *n0 = 32 * (int64_t)j;
+  *m0 = U * (int64_t)i;
+  *n0 = U * (int64_t)j;
   return *m0 < g.M && *n0 < g.N;
 }
 
@@ -137,45 +138,51 @@ __device__ __forceinline__ void accumulate(const ZgemmDev& g, int bt, int64_t m0
     pb[i] = reinterpret_cast<const doublex2*>(B) + (TBT ? (int64_t)lk * g.ldb + c : c * g.ldb + lk);
   }
   const int64_t ka = TA ? 1 : g.lda, kb = TBT ? g.ldb : 1;  // step of one k
-  doublex2 fa[2][F][2], fb[2][F][2];
+  using E = std::conditional_t<REAL, double, doublex2>;
+  E fa[2][F][2], fb[2][F][2];
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
     for (int j = 0; j < F; ++j) cr[i][j] = ci[i][j] = doublex4{0, 0, 0, 0};
 
-  auto load = [&](int64_t k, doublex2 (&xa)[F][2], doublex2 (&xb)[F][2]) __attribute__((always_inline)) {
+  auto load = [&](int64_t k, E (&xa)[F][2], E (&xb)[F][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < F; ++i)
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        xa[i][s] = pa[i][(k + s) * ka];
-        xb[i][s] = pb[i][(k + s) * kb];
+        xa[i][s] = *reinterpret_cast<const E*>(pa[i] + (k + s) * ka);
+        xb[i][s] = *reinterpret_cast<const E*>(pb[i] + (k + s) * kb);
       }
   };
-  auto load_tail = [&](int64_t k, doublex2 (&xa)[F][2], doublex2 (&xb)[F][2]) __attribute__((always_inline)) {
+  auto load_tail = [&](int64_t k, E (&xa)[F][2], E (&xb)[F][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < F; ++i)
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const bool ok = k + lk + s < kend;
         const int64_t q = ok ? k + s : -lk;  // k = 0 of the operand where past the end
-        const doublex2 va = pa[i][q * ka], vb = pb[i][q * kb];
-        xa[i][s] = ok ? va : doublex2{0, 0};
-        xb[i][s] = ok ? vb : doublex2{0, 0};
+        const E va = *reinterpret_cast<const E*>(pa[i] + q * ka), vb = *reinterpret_cast<const E*>(pb[i] + q * kb);
+        xa[i][s] = ok ? va : E{};
+        xb[i][s] = ok ? vb : E{};
       }
   };
-  auto mul = [&](int64_t k, const doublex2 (&xa)[F][2], const doublex2 (&xb)[F][2]) __attribute__((always_inline)) {
+  auto mul = [&](int64_t k, const E (&xa)[F][2], const E (&xb)[F][2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const unsigned neg = k + lk + s >= g.kneg ? 0x80000000u : 0u;
       double ar[F], ai[F], an[F], br[F], bi[F];
 #pragma unroll
       for (int i = 0; i < F; ++i) {
-        ar[i] = xa[i][s][0];
-        ai[i] = flip(xa[i][s][1], TA ? 0x80000000u : 0u);
-        an[i] = flip(xa[i][s][1], TA ? 0u : 0x80000000u);
-        br[i] = flip(xb[i][s][0], neg);
-        bi[i] = flip(xb[i][s][1], TBT ? neg ^ 0x80000000u : neg);
+        if constexpr (REAL) {
+          ar[i] = xa[i][s];
+          br[i] = flip(xb[i][s], neg);
+        } else {
+          ar[i] = xa[i][s][0];
+          ai[i] = flip(xa[i][s][1], TA ? 0x80000000u : 0u);
+          an[i] = flip(xa[i][s][1], TA ? 0u : 0x80000000u);
+          br[i] = flip(xb[i][s][0], neg);
+          bi[i] = flip(xb[i][s][1], TBT ? neg ^ 0x80000000u : neg);
+        }
       }
 #pragma unroll
       for (int i = 0; i < F; ++i)
@@ -217,18 +224,23 @@ __device__ __forceinline__ void accumulate(const ZgemmDev& g, int bt, int64_t m0
   }
 }
 
-template <bool REAL, int TA, int TBT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 3))) void zgemm_kernel(const ZgemmDev g) {
-  constexpr int F = 2;  // fragments per wave and operand
+// F: fragments per wave and operand.  Complex: 2.  Real data takes a quarter of
+// the MFMAs on the same lines, which at F = 2 the L1 bounds (64 bytes a cycle);
+// large real products run at F = 4 (24000 x 1920 x 1920 upper 3754 -> 1877 us,
+// 1920 x 1920 x 24000 lower 5211 -> 2682).
+template <bool REAL, int TA, int TBT, int F>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, F == 2 ? 3 : 2))) void zgemm_kernel(
+    const ZgemmDev g) {
+  constexpr int U = 16 * F, RT = 2 * U;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int id = g.b_upper || g.a_lower ? blockIdx.x : xcd_remap(blockIdx.x, gridDim.x);
   const int sp = id / g.tiles, bt = blockIdx.y, t = id - sp * g.tiles;
   int64_t m0, n0;
-  if (!wave_tile(g, t, wave, &m0, &n0)) return;
+  if (!wave_tile<U>(g, t, wave, &m0, &n0)) return;
   int64_t klim = g.K;
-  if (g.a_lower) klim = min(klim, m0 + 32);
-  if (g.b_upper) klim = min(klim, n0 + 32);
+  if (g.a_lower) klim = min(klim, m0 + U);
+  if (g.b_upper) klim = min(klim, n0 + U);
   const int64_t kbeg = (int64_t)sp * g.kchunk;
   doublex4 cr[F][F], ci[F][F];
   accumulate<REAL, TA, TBT, F>(g, bt, m0, n0, kbeg, min(klim, kbeg + g.kchunk), cr, ci);
@@ -305,14 +317,16 @@ __global__ __launch_bounds__(64 * NW) void zgemm_short_kernel(const ZgemmDev g) 
 
 // Sums the K splits of tile blockIdx.x in order; fragment blockIdx.z of each
 // wave.
+template <int F>
 __global__ __launch_bounds__(NT) void zgemm_reduce_kernel(const ZgemmDev g) {
+  constexpr int U = 16 * F, RT = 2 * U;
   const int t = blockIdx.x, bt = blockIdx.y, f = blockIdx.z;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t m0, n0;
-  if (!wave_tile(g, t, wave, &m0, &n0)) return;
+  if (!wave_tile<U>(g, t, wave, &m0, &n0)) return;
   const doublex2* p = reinterpret_cast<const doublex2*>(g.ws + ((int64_t)bt * g.tiles + t) * RT * RT) +
-                      (wave * 4 + f) * 256 + lane;
+                      (wave * F * F + f) * 256 + lane;
   const int64_t step = (int64_t)gridDim.y * g.tiles * RT * RT;
   doublex2 v[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
   int s = 0;
@@ -330,18 +344,18 @@ __global__ __launch_bounds__(NT) void zgemm_reduce_kernel(const ZgemmDev g) {
   for (; s < g.splits; ++s)
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] += p[s * step + 64 * r];
-  put4(g, bt, m0 + 16 * (f >> 1) + 4 * (lane >> 4), n0 + 16 * (f & 1) + (lane & 15),
+  put4(g, bt, m0 + 16 * (f / F) + 4 * (lane >> 4), n0 + 16 * (f % F) + (lane & 15),
        doublex4{v[0][0], v[0][1], v[1][0], v[1][1]}, doublex4{v[2][0], v[2][1], v[3][0], v[3][1]});
 }
 
-template <bool REAL>
+template <bool REAL, int F>
 void launch_large(const ZgemmDev& g, dim3 grid, hipStream_t s) {
   if (g.transA) {
-    if (g.transB) hipLaunchKernelGGL((zgemm_kernel<REAL, 1, 1>), grid, dim3(NT), 0, s, g);
-    else hipLaunchKernelGGL((zgemm_kernel<REAL, 1, 0>), grid, dim3(NT), 0, s, g);
+    if (g.transB) hipLaunchKernelGGL((zgemm_kernel<REAL, 1, 1, F>), grid, dim3(NT), 0, s, g);
+    else hipLaunchKernelGGL((zgemm_kernel<REAL, 1, 0, F>), grid, dim3(NT), 0, s, g);
   } else {
-    if (g.transB) hipLaunchKernelGGL((zgemm_kernel<REAL, 0, 1>), grid, dim3(NT), 0, s, g);
-    else hipLaunchKernelGGL((zgemm_kernel<REAL, 0, 0>), grid, dim3(NT), 0, s, g);
+    if (g.transB) hipLaunchKernelGGL((zgemm_kernel<REAL, 0, 1, F>), grid, dim3(NT), 0, s, g);
+    else hipLaunchKernelGGL((zgemm_kernel<REAL, 0, 0, F>), grid, dim3(NT), 0, s, g);
   }
 }
 
@@ -390,11 +404,18 @@ Err zgemm(const ZgemmArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
     CHASE_LAUNCH_CHECK();
     return ok();
   }
+  // Real data on 64 x 64 outputs a wave where these fill the chip: 400 workgroups
+  // of them, or enough for K splits to (us, 32 x 32 / 64 x 64: 12000 x 640 x 640
+  // upper 190 / 156, 8000 x 520 x 520 upper 103 / 131; 376 x 376 x 8000 lower
+  // 88 / 79, 260 x 260 x 8000 lower 61 / 71).
+  const double outputs = (double)a.M * a.N * (a.lower_only ? 0.5 : 1.0);
+  const bool wide = a.real_data && (outputs >= 400.0 * 128 * 128 || (outputs >= 65536 && a.K >= 4096));
+  const int64_t U = wide ? 64 : 32, RT = 2 * U;
   const bool col = a.b_upper && !a.lower_only, row = a.a_lower && !a.lower_only && !a.b_upper;
-  g.TM = (int)ceil_div(a.M, (int64_t)(col ? 128 : row ? 32 : RT));
-  g.TN = (int)ceil_div(a.N, (int64_t)(col ? 32 : row ? 128 : RT));
-  const int64_t t32 = ceil_div(a.M, (int64_t)32);
-  g.tiles = a.lower_only ? (int)ceil_div(t32 * (t32 + 1) / 2, (int64_t)4) : g.TM * g.TN;
+  g.TM = (int)ceil_div(a.M, col ? 4 * U : row ? U : RT);
+  g.TN = (int)ceil_div(a.N, col ? U : row ? 4 * U : RT);
+  const int64_t tu = ceil_div(a.M, U);
+  g.tiles = a.lower_only ? (int)ceil_div(tu * (tu + 1) / 2, (int64_t)4) : g.TM * g.TN;
   // K splits while the tiles leave workgroup slots empty, at least 8 slabs
   // each: to two workgroups per CU, and two splits where that leaves one tile
   // on most CUs (three fit: 8000 x 188 x 376, 375 tiles: 113 us whole, 89 + 17
@@ -411,11 +432,14 @@ Err zgemm(const ZgemmArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
   g.splits = (int)ceil_div(std::max<int64_t>(a.K, 1), g.kchunk);
   g.ws = (c128*)ws;
   const dim3 grid((unsigned)((int64_t)g.tiles * g.splits), (unsigned)a.batch);
-  if (a.real_data) launch_large<true>(g, grid, s);
-  else launch_large<false>(g, grid, s);
+  if (wide) launch_large<true, 4>(g, grid, s);
+  else if (a.real_data) launch_large<true, 2>(g, grid, s);
+  else launch_large<false, 2>(g, grid, s);
   CHASE_LAUNCH_CHECK();
   if (g.splits > 1) {
-    hipLaunchKernelGGL(zgemm_reduce_kernel, dim3((unsigned)g.tiles, (unsigned)a.batch, 4), dim3(NT), 0, s, g);
+    const dim3 rgrid((unsigned)g.tiles, (unsigned)a.batch, wide ? 16 : 4);
+    if (wide) hipLaunchKernelGGL(zgemm_reduce_kernel<4>, rgrid, dim3(NT), 0, s, g);
+    else hipLaunchKernelGGL(zgemm_reduce_kernel<2>, rgrid, dim3(NT), 0, s, g);
     CHASE_LAUNCH_CHECK();
   }
   return ok();

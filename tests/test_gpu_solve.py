@@ -248,3 +248,37 @@ def test_solve_clustered_spectrum_to_convergence(prec):
     assert np.all(ores.residual_norms(p.A, p.B, to_host(V), ev) <= 1.5 * p.tol)
     assert 150 <= info.iterations <= 320
     assert 1 <= info.rr_sweeps_max < 40
+
+
+def test_solve_on_wide_real_products():
+    # 840 columns of 8000 reals: the orthonormalisation's Gram matrix, its
+    # triangular product and the projection off the locked pairs run on the
+    # widest tiles of the real GEMM, with cut-off tiles (840 = 13 x 64 + 8).
+    # Every returned pair against H V formed by matmul, and eq. 3.5
+    m, nev, nex, tol = 4000, 400, 20, 1e-7
+    print_case("solve_wide_real", m=m, nev=nev, nex=nex)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def normal(*shape):
+        return torch.complex(torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen),
+                             torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen))
+
+    d = torch.linspace(1.0, 9.0, m, dtype=torch.float64, device="cuda")
+    B = normal(m, m) * (0.05 / m ** 0.5)
+    B = (0.5 * (B + B.T)).contiguous()
+    A = torch.diag(d).to(torch.complex128)
+    W0 = (torch.eye(2 * m, nev + nex, dtype=torch.complex128, device="cuda") + 1e-2 * normal(2 * m, nev + nex) / m ** 0.5)
+    Lz = normal(2 * m, 4)
+    s = PHSolver(A, B, nev, nex, deg=20, tol=tol, max_iter=30, precision=FP64)
+    ev, V, res, info = s.solve(W0.T.contiguous().T, Lz.T.contiguous().T)
+    assert info.iterations > 1
+    lam = torch.from_numpy(np.asarray(ev)).cuda().to(torch.complex128)
+    X, Y = V[:m], V[m:]
+    HV = torch.cat([A @ X + B @ Y, -(B.conj() @ X) - A.conj() @ Y])
+    r = torch.linalg.vector_norm(HV - V * lam[None, :], dim=0).cpu().numpy()
+    assert np.all(r <= 1.5 * tol), r.max()
+    assert np.all(np.abs(r - np.asarray(res)) <= 1e-10)
+    D = (X.conj().T.contiguous() @ X - Y.conj().T.contiguous() @ Y).cpu().numpy()
+    assert np.max(np.abs(D - np.diag(np.diag(D)))) < 1e-5
+    s.close()
