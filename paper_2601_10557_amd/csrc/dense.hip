@@ -490,6 +490,7 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const c128* G, c128* 
     }
     const int b = a + rest;
     const bool ua = pflag[a], ub = pflag[b];
+    if (Gn == G && !ua && !ub) return;  // in place: both rotations are the identity
     const c128* Ua = Uw + (int64_t)a * SP * SP;
     const c128* Ub = Uw + (int64_t)b * SP * SP;
     for (int t = tid; t < SP * SP; t += 256) {
@@ -902,6 +903,14 @@ static Err gemm_kp(int ta, int kp, const c128* A, const c128* B, double beta, c1
 // steps of 60 to 180 us: Rayleigh-Ritz m = 4000, k = 376 4.19 -> 3.80 ms against a
 // limit of 0.04.
 constexpr double REFINE_MAX = 0.1, REFINE_MID = 0.04, REFINE_SHORT = 1e-4;
+// From REFINE_KP on, a step of 6 or 7 products takes as long as a sweep and does
+// less, so only the short form replaces one (k = 2600, solve of 5 iterations:
+// Rayleigh-Ritz 525 -> 502 ms).
+constexpr int REFINE_KP = 1536;
+// From IN_PLACE_KP on, a round is bound by reading and writing G and V: there
+// the rotations are found in a launch of their own and applied in place, so that
+// blocks whose pairs did not rotate, most of them in late sweeps, stay untouched.
+constexpr int IN_PLACE_KP = 3072;
 
 // Eigenvectors V and (on the diagonal) eigenvalues of the Hermitian G: block
 // Jacobi sweeps until the off-diagonal entries are small against the gaps of
@@ -920,6 +929,9 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   const int nbj = kp / JB;  // even since kp % 64 == 0
   const int npair = nbj / 2;
   CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s, ws.flag + DenseWs::COUNTS, 2));
+  const bool in_place = kp >= IN_PLACE_KP;
+  int* none = ws.pflag + 2 * npair;  // flags of no rotation
+  if (in_place) CHASE_HIP(hipMemsetAsync(none, 0, (size_t)npair * sizeof(int), s));
   const bool small = kp <= OFFDIAG_SMALL && ws.hpin && ws.hpin_bytes >= 5 * sizeof(double);
   if (!small) CHASE_TRY(frob_norm(G, kp, ws, s));
   // G is in cur; every round writes it to o[0] and the two change places.
@@ -959,7 +971,7 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     }
     if (sweep == max_sweeps) break;
     ++sweep;
-    if (ef <= REFINE_MAX) {
+    if (ef <= (kp < REFINE_KP ? REFINE_MAX : REFINE_SHORT)) {
       const int blocks = grid_for((int64_t)kp * kp);
       c128 *W = o[0], *T = o[1], *T2 = ef > REFINE_SHORT ? o[2] : nullptr, *Z = ef > REFINE_MID ? ws.k4 : nullptr;
       hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, W, kp, thr * thr);
@@ -987,14 +999,22 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     hipLaunchKernelGGL(jacobi_first_kernel, dim3(npair), dim3(256), 0, s, (const c128*)cur, (int64_t)kp, nbj, U[0], thr,
                        fl[0]);
     CHASE_LAUNCH_CHECK();
+    const int apply = npair * (npair + 1) / 2 + npair * (kp / SP);
+    auto round = [&](int r, int nspec, int blocks, c128* Gn, const int* flags) -> Err {
+      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, Gn, vec, (int64_t)kp, kp,
+                         nbj, r, (const c128*)U[r & 1], flags, U[(r + 1) & 1], fl[(r + 1) & 1], thr, nspec);
+      CHASE_LAUNCH_CHECK();
+      return ok();
+    };
     for (int r = 0; r < nbj - 1; ++r) {
       const int nspec = r < nbj - 2 ? npair : 0;
-      const int blocks = nspec + npair * (npair + 1) / 2 + npair * (kp / SP);
-      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, o[0], vec, (int64_t)kp, kp,
-                         nbj, r, (const c128*)U[r & 1], (const int*)fl[r & 1], U[(r + 1) & 1], fl[(r + 1) & 1], thr,
-                         nspec);
-      CHASE_LAUNCH_CHECK();
-      std::swap(cur, o[0]);
+      if (in_place) {
+        CHASE_TRY(round(r, 0, apply, cur, fl[r & 1]));
+        if (nspec) CHASE_TRY(round(r, nspec, nspec, cur, none));
+      } else {
+        CHASE_TRY(round(r, nspec, nspec + apply, o[0], fl[r & 1]));
+        std::swap(cur, o[0]);
+      }
     }
   }
   if (vec != V) CHASE_HIP(hipMemcpyAsync(V, vec, (size_t)kp * kp * sizeof(c128), hipMemcpyDeviceToDevice, s));
