@@ -464,14 +464,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Sum the split-K partials in a fixed order and apply the epilogue: one
-// thread per complex row i and X column j.  Blocks from na on take part b.
-__global__ void hx_reduce(const ApplyHArgs aa, int splits_a, const R* ws_a, int na, const ApplyHArgs ab, int splits_b,
-                          const R* ws_b) {
-  const bool first = (int)blockIdx.x < na;
-  const ApplyHArgs& a = first ? aa : ab;
-  const int splits = first ? splits_a : splits_b;
-  const R* ws = first ? ws_a : ws_b;
-  const int64_t block = first ? blockIdx.x : blockIdx.x - na, blocks = first ? na : gridDim.x - na;
+// thread per complex row i and X column j of one part, on its blocks.
+__device__ __forceinline__ void reduce_part(const ApplyHArgs& a, int splits, const R* ws, int64_t block,
+                                            int64_t blocks) {
   const int64_t m = a.m, M2 = 2 * m;
   const int N = a.tda ? a.k : 2 * a.k;
   const int64_t total = m * a.k;
@@ -500,6 +495,22 @@ __global__ void hx_reduce(const ApplyHArgs aa, int splits_a, const R* ws_a, int 
     finish_pair(a, i, 2 * j, ur, ui, vr, vi);
     finish_pair(a, i, 2 * j + 1, vr, vi, ur, ui);
   }
+}
+
+__global__ void hx_reduce(const ApplyHArgs a, int splits, const R* ws) {
+  reduce_part(a, splits, ws, blockIdx.x, gridDim.x);
+}
+
+// Two parts in one launch, blocks from na on the second.  A kernel of its own:
+// with the part chosen at run time (twice the arguments, reached through a
+// pointer) a reduction of one part took half a microsecond longer (a product of
+// m = 500, k = 8: 24.5 us against 23.9; m = 300, k = 30: 24.9 / 24.3).
+__global__ void hx_reduce_pair(const ApplyHArgs aa, int splits_a, const R* ws_a, int na, const ApplyHArgs ab,
+                               int splits_b, const R* ws_b) {
+  if ((int)blockIdx.x < na)
+    reduce_part(aa, splits_a, ws_a, blockIdx.x, na);
+  else
+    reduce_part(ab, splits_b, ws_b, blockIdx.x - na, gridDim.x - na);
 }
 
 struct Plan {
@@ -556,16 +567,23 @@ void plan_override(Plan& p, int64_t m2, int64_t n2, const int (&bm)[NCFG], const
   p.tiles = ceil_div(m2, bm[c]) * ceil_div(n2, bn[c]);
 }
 
-// Part b (null: none) in the same launch: at 8 columns it is latency, 8 us in a
-// launch of its own.
-Err launch_reduce(const ApplyHArgs& a, int splits, const R* ws, const ApplyHArgs* b, int splits_b, const R* ws_b,
-                  hipStream_t s) {
-  auto blocks = [](const ApplyHArgs& x, int sp) {
-    return sp <= 1 ? 0 : (int)std::min<int64_t>(ceil_div(x.m * (int64_t)x.k, 256), 8192);
-  };
-  const int na = blocks(a, splits), nb = b ? blocks(*b, splits_b) : 0;
-  if (na + nb == 0) return ok();
-  hipLaunchKernelGGL(hx_reduce, dim3(na + nb), dim3(256), 0, s, a, splits, ws, na, b ? *b : a, splits_b, ws_b);
+int reduce_blocks(const ApplyHArgs& a) { return (int)std::min<int64_t>(ceil_div(a.m * (int64_t)a.k, 256), 8192); }
+
+Err launch_reduce(const ApplyHArgs& a, int splits, const R* ws, hipStream_t s) {
+  if (splits <= 1) return ok();
+  hipLaunchKernelGGL(hx_reduce, dim3(reduce_blocks(a)), dim3(256), 0, s, a, splits, ws);
+  CHASE_LAUNCH_CHECK();
+  return ok();
+}
+
+// Both parts of a split product in one launch: at 8 columns a reduction is
+// latency, 8 us in a launch of its own.
+Err launch_reduce_pair(const ApplyHArgs& a, int splits, const R* ws, const ApplyHArgs& b, int splits_b, const R* ws_b,
+                       hipStream_t s) {
+  if (splits <= 1) return launch_reduce(b, splits_b, ws_b, s);
+  if (splits_b <= 1) return launch_reduce(a, splits, ws, s);
+  const int na = reduce_blocks(a);
+  hipLaunchKernelGGL(hx_reduce_pair, dim3(na + reduce_blocks(b)), dim3(256), 0, s, a, splits, ws, na, b, splits_b, ws_b);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
@@ -576,7 +594,7 @@ Err launch_cfg(const ApplyHArgs& a, const Plan& p, void* ws, hipStream_t s) {
   hipLaunchKernelGGL((hx_kernel<Tr, BM, BN, BK, NST, WGM, WGN, SCHED>), dim3((unsigned)grid), dim3(256), 0, s, a, p.splits,
                      p.kps, (R*)ws);
   CHASE_LAUNCH_CHECK();
-  return launch_reduce(a, p.splits, (const R*)ws, nullptr, 1, nullptr, s);
+  return launch_reduce(a, p.splits, (const R*)ws, s);
 }
 
 // Main part on tile shape (BM, BN, ...), remainder on (BMR, BNR, ...).
@@ -593,7 +611,7 @@ Err launch_pair_cfg(const ApplyHArgs& am, const Plan& pm, void* wsm,
                      dim3((unsigned)grid), dim3(256), 0, s, am, pm.splits, pm.kps, (R*)wsm, ar, pr.splits, pr.kps,
                      (R*)wsr, nrem, live, nmain, main_live, main_live % 512 == 0);
   CHASE_LAUNCH_CHECK();
-  return launch_reduce(am, pm.splits, (const R*)wsm, &ar, pr.splits, (const R*)wsr, s);
+  return launch_reduce_pair(am, pm.splits, (const R*)wsm, ar, pr.splits, (const R*)wsr, s);
 }
 
 // Tile shapes (BM x BN reals, K slab BK, NST ring stages), two workgroups
