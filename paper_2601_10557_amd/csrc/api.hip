@@ -16,6 +16,7 @@
 #include "dense.h"
 #include "geev.h"
 #include "hx.h"
+#include "hx_plan.h"
 #include "vec.h"
 
 using namespace chase;
@@ -1698,13 +1699,16 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   // counts, Ritz values, residuals: at most kmax doubles)
   h->dws.hpin_bytes = std::max<size_t>(4096, sizeof(double) * (size_t)h->kmax) + 64;
   CHASE_HIP(hipHostMalloc(&h->dws.hpin, h->dws.hpin_bytes, hipHostMallocDefault));
-  // zgemm split-K partials (up to 8 k x k blocks) and the partial tiles of
-  // the H X products (two per workgroup: 128 MiB when all 512 take part,
-  // which small m never do), within [16 MiB, 1 GiB]
+  // partial sums of the c64 H X products (up to 8 x m x 2 nevex complex) and of
+  // split GEMMs (up to 8 k x k blocks), within [16 MiB, 1 GiB]
   h->ws_bytes = std::max(kp2 * sizeof(c128) * 8, (size_t)8 * h->m * h->kmax * sizeof(c128));
   h->ws_bytes = std::min<size_t>((size_t)1 << 30, std::max<size_t>((size_t)16 << 20, h->ws_bytes));
   h->ws32_bytes = h->ws_bytes;
-  h->ws_bytes = std::max(h->ws_bytes, std::min<size_t>((size_t)128 << 20, (size_t)h->m << 16));
+  // GEMMs of up to kmax x kmax x n: 64 KB a tile of 64 x 64, 64 of K and 768 in
+  // all at most; the c128 products: what the widest one's plan takes
+  const int64_t gt = ceil_div(h->kmax, 64);
+  h->ws_bytes = std::max(h->ws_bytes, (size_t)std::min<int64_t>(768, gt * gt * ceil_div(h->n, 64)) << 16);
+  if (h->ws_bytes < HX_WS_MAX) h->ws_bytes = std::max(h->ws_bytes, hx_workspace(2 * h->m, 2 * (int64_t)h->kcap));
   CHASE_TRY(dalloc(h, (char**)&h->ws, h->ws_bytes));
   // free while the projected eigenproblem is solved
   h->dws.k1 = h->Nb;

@@ -33,7 +33,7 @@
 // the team's XCD once.  Two workgroups per CU in all.  A part may start or end
 // inside a strip; the partial sums of such a strip go to a workspace and a
 // second kernel adds them in K order and applies the epilogue, so results do
-// not depend on timing.  Short products (short_shape) run in one launch of
+// not depend on timing.  Short products (hx_plan.h) run in one launch of
 // hx_short_kernel instead, where the waves of a workgroup share K.
 //
 // Bound by the FP64 MFMA for N >= 100 or so at m >= 4000 (below that by the
@@ -45,6 +45,7 @@
 // M read by a team's workgroups in step, rather than by workgroups with parts
 // of their own of (strip, tile, K): 2 - 7% at m = 4000.
 #include "hx.h"
+#include "hx_plan.h"
 
 #include <algorithm>
 #include <cmath>
@@ -61,15 +62,12 @@ typedef double doublex2 __attribute__((ext_vector_type(2)));
 // k = l / 16 of the four, and rows l / 16 + 4 r of output column l % 16.  A
 // fragment load of 16 bytes covers two MFMAs: a slab of 8 reals of K, lane l
 // holding k = 2 (l / 16) + s for MFMA s.
-constexpr int V = 2, BK = 8;
-constexpr int FM = 2;            // 16-row fragments per wave
+constexpr int V = 2, BK = HX_BK;
+constexpr int FM = HX_FM;
 constexpr int WROWS = 16 * FM;   // rows per wave
-constexpr int BM = 4 * WROWS;    // rows per workgroup
-static_assert(HX_RPAD % BM == 0, "row padding");
-constexpr int MAX_WG = 512;      // two workgroups per CU
-constexpr int MAX_NL = 8;        // column fragments of the widest tile
-// K slabs per stage: about as many loads in flight at every width
-constexpr int stage_slabs(int w) { return w <= 2 ? 4 : w <= 4 ? 2 : 1; }
+constexpr int BM = HX_BM;        // rows per workgroup
+static_assert(BM == 4 * WROWS && HX_RPAD % BM == 0, "row padding");
+constexpr int MAX_WG = HX_MAX_WG, MAX_NL = HX_MAX_NL;
 static_assert(HX_KPAD % (4 * BK) == 0, "column padding");
 
 // Real row (of 16) whose M entries lane l holds: fed from row
@@ -77,21 +75,13 @@ static_assert(HX_KPAD % (4 * BK) == 0, "column padding");
 // are rows 4 (l / 16) .. + 3.
 __device__ __forceinline__ int a_row(int l) { return 4 * (l & 3) + ((l & 15) >> 2); }
 
-struct HxDev {
+struct HxDev : HxPlan {
   const double* M;
   const double* y;
   int64_t ldc4;   // reals per quad row
   int64_t wstep;  // reals of M per 32-row group
   int rows2, N, m;
-  // plan: TM strips x TN tiles of wq or wq + 1 (the first wr) fragments, KB
-  // stages of K per strip; team t of `teams` starts at stage
-  // unit * floor(t len / teams) of the TM * KB, with len = lq * teams + lr
-  int TM, TN, wq, wr, KB, teams, lr;
-  int64_t lq, unit;
-  double i_KB, i_teams;  // reciprocals
-  double* ws;
-  int64_t slot;    // reals per partial-sum slot (two per workgroup)
-  int wmax;
+  double* ws;  // partial sums
   // epilogue: X4 output (out != null) or complex Y of one product
   double* out;
   const double *P, *Q;
@@ -460,119 +450,27 @@ bool plan_override(int* w, int* splits) {
   return e && std::sscanf(e, "%d,%d", w, splits) == 2 && *w >= 0 && *w <= 9 && *splits >= 1;
 }
 
-// Cuts NB column fragments into TN tiles and the strips' K range into parts
-// for at most MAX_WG / TN teams.
-void set_tiles(HxDev& a, int NB, int TN) {
-  a.TN = TN;
-  a.wq = NB / TN;
-  a.wr = NB % TN;
-  a.wmax = a.wq + (a.wr ? 1 : 0);
-  a.KB = (int)ceil_div(a.rows2, (int64_t)stage_slabs(a.wmax) * BK);
-  a.slot = (int64_t)BM * 16 * a.wmax;
-}
-
-// Column tiles of a long product and the estimate of its time: a team's widest
-// tile, where the padding of unequal tiles shows, plus the partial sums (at
-// 12 TB/s, mostly from the Infinity Cache).  Tiles of fewer than 5 fragments
-// read more per MFMA.  m = 4000: k = 130 (17 fragments) 549 us on 3 tiles, 573
-// on 5, 597 on 4; k = 260 (33) 1037 on 5, 1071 on 6.
-double long_plan(const HxDev& a, int* tn) {
-  const int NB = (int)ceil_div(a.N, (int64_t)16);
-  const int64_t slabs = ceil_div(a.rows2, (int64_t)BM) * ceil_div(a.rows2, (int64_t)BK);
-  const double frag_us = FM * V * 64 / 2400.0;  // MFMA time of one slab and column fragment
-  static const double narrow[5] = {0, 1.2, 1.12, 1.06, 1.05};
-  const int t0 = (int)ceil_div(NB, (int64_t)MAX_NL);
-  double best = 1e300;
-  for (int t = t0; t <= std::min(NB, 3 * t0); ++t) {
-    const int w = (int)ceil_div(NB, (int64_t)t), teams = std::max(1, MAX_WG / t);
-    const double us = slabs * frag_us * w * (w < 5 ? narrow[w] : 1.0) / teams +
-                      2.0 * BM * 16 * w * t * teams * sizeof(double) / 12e6;
-    if (us < best) {
-      best = us;
-      *tn = t;
-    }
-  }
-  return best;
-}
-
-// Shapes (FMS, NL) of hx_short_kernel.
-constexpr int SHORT_SHAPES = 6;
-constexpr int short_f[SHORT_SHAPES] = {1, 1, 2, 2, 2, 2}, short_n[SHORT_SHAPES] = {1, 2, 1, 2, 3, 4};
-
-// The shape that computes a short product soonest, or -1 if teams on long
-// parts do.  A CU's workgroups each cost 10.6 ns per slab and fragment pair
-// (MFMA) and 5.8 per fragment loaded (L1), on top of 3.6 us; M comes from the
-// caches at 10 TB/s or so, from HBM at 6 (4.5 where a workgroup reads only
-// half of a 32-row group).  Whole workgroups per CU count: that is what the
-// teams' equal parts avoid, at the price of a second launch and of partial
-// sums (5 us and 2.3 times the estimate of long_plan, M at 4.8 TB/s).  Measured
-// (us a product; teams / this): m = 100, k = 30 11.9 / 4.0; m = 500, k = 30
-// 15.1 / 6.5; m = 1000, k = 120 46.2 / 35.4; m = 2000, k = 35 61.0 / 53.2, k = 70
-// 85.2 / 91; m = 3000, k = 35 111 / 128; m = 4000, k = 4 107 / 91, k = 32
-// 158 / 136.
-int short_shape(const HxDev& a) {
-  int w = 0, splits = 0;
-  if (plan_override(&w, &splits)) return w < 4 ? -1 : w - 4;
-  const double slabs = (double)ceil_div(a.rows2, (int64_t)BK);
-  const double bytes = 8.0 * a.rows2 * a.rows2 * 1e-6;
-  const bool cached = bytes < 256;
-  int tn = 0, shape = -1;
-  auto overlap = [](double x, double y) { return std::max(x, y) + 0.2 * std::min(x, y); };
-  double best = overlap(5.0 + 2.3 * long_plan(a, &tn), bytes / 4.8);
-  for (int c = 0; c < SHORT_SHAPES; ++c) {
-    const int f = short_f[c], n = short_n[c];
-    const int64_t rounds = ceil_div(ceil_div(a.rows2, (int64_t)(16 * f)) * ceil_div(a.N, (int64_t)(16 * n)),
-                                    (int64_t)(MAX_WG / 2));
-    if (rounds > 4) continue;
-    const double comp = 3.6 + slabs * rounds * (f * n * 0.0106 + (f + n) * 0.0058);
-    const double mem = bytes / (cached ? 10.0 : f == 1 ? 4.5 : 6.0);
-    const double us = overlap(comp, mem);
-    if (us < best) {
-      best = us;
-      shape = c;
-    }
-  }
-  return shape;
-}
-
+// The plan of a's product into a.
 void make_plan(HxDev& a, size_t ws_bytes) {
-  const int NB = (int)ceil_div(a.N, (int64_t)16);
-  a.TM = (int)ceil_div(a.rows2, (int64_t)BM);
-  auto most = [](int TN) { return std::max<int64_t>(1, MAX_WG / TN); };
-  int force_w = 0, force_s = 0;
-  int64_t teams;
-  if (plan_override(&force_w, &force_s)) {
-    set_tiles(a, NB, (int)ceil_div(NB, (int64_t)(MAX_NL >> force_w)));
-    teams = std::min((int64_t)a.TM * force_s, most(a.TN));
+  HxPlan& p = a;
+  int w = 0, splits = 0;
+  if (!plan_override(&w, &splits)) {
+    p = hx_plan(a.rows2, a.N, ws_bytes);
+  } else if (w >= 4) {
+    hx_set_short(p, a.rows2, a.N, w - 4);
   } else {
-    int tn = 1;
-    long_plan(a, &tn);
-    set_tiles(a, NB, tn);
-    teams = most(tn);
+    const int NB = (int)ceil_div(a.N, (int64_t)16), TN = (int)ceil_div(NB, (int64_t)(MAX_NL >> w));
+    const int64_t strips = ceil_div(a.rows2, (int64_t)BM);
+    hx_cut(p, a.rows2, NB, TN, std::min<int64_t>(strips * splits, std::max(1, MAX_WG / TN)), ws_bytes);
   }
-  // at least two stages a part, so that none is empty
-  teams = std::min(teams, std::max<int64_t>(a.TM, (int64_t)a.TM * a.KB / 2));
-  a.unit = 1;
-  int64_t len = (int64_t)a.TM * a.KB;
-  if (2 * (size_t)teams * a.TN * a.slot * sizeof(double) > ws_bytes) {  // no room for partial sums: whole strips
-    a.unit = a.KB;
-    len = a.TM;
-    teams = std::min<int64_t>(a.TM, most(a.TN));
-  }
-  a.teams = (int)teams;
-  a.lq = len / teams;
-  a.lr = (int)(len % teams);
-  a.i_KB = 1.0 / a.KB;
-  a.i_teams = 1.0 / a.teams;
 }
 
 Err launch(HxDev& a, void* ws, size_t ws_bytes, hipStream_t s) {
-  const int shape = short_shape(a);
-  if (shape >= 0) {
+  a.ws = (double*)ws;
+  make_plan(a, ws ? ws_bytes : 0);
+  if (a.shape >= 0) {
     auto go = [&](auto F, auto NL, auto NW, auto KS) {
       constexpr int f = decltype(F)::value, nl = decltype(NL)::value, nw = decltype(NW)::value;
-      a.TN = (int)ceil_div(a.N, (int64_t)(16 * nl));
-      a.KB = (int)ceil_div(a.rows2, (int64_t)BK);
       const unsigned blocks = (unsigned)(ceil_div(a.rows2, (int64_t)(16 * f)) * a.TN);
       hipLaunchKernelGGL((hx_short_kernel<f, nl, nw, decltype(KS)::value>), dim3(blocks), dim3(64 * nw), 0, s, a);
     };
@@ -581,7 +479,7 @@ Err launch(HxDev& a, void* ws, size_t ws_bytes, hipStream_t s) {
     using I3 = std::integral_constant<int, 3>;
     using I4 = std::integral_constant<int, 4>;
     using I8 = std::integral_constant<int, 8>;
-    switch (shape) {
+    switch (a.shape) {
       case 0: go(I1{}, I1{}, I4{}, I4{}); break;
       case 1: go(I1{}, I2{}, I4{}, I2{}); break;
       case 2: go(I2{}, I1{}, I4{}, I2{}); break;
@@ -592,12 +490,10 @@ Err launch(HxDev& a, void* ws, size_t ws_bytes, hipStream_t s) {
     CHASE_LAUNCH_CHECK();
     return ok();
   }
-  a.ws = (double*)ws;
-  make_plan(a, ws ? ws_bytes : 0);
   const dim3 grid((unsigned)(a.teams * a.TN)), block(256);
   auto go = [&](auto W) {
     constexpr int w = decltype(W)::value;
-    hipLaunchKernelGGL((hx_kernel<w, stage_slabs(w)>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((hx_kernel<w, hx_stage_slabs(w)>), grid, block, 0, s, a);
   };
   switch (a.wmax) {
     case 1: go(std::integral_constant<int, 1>{}); break;
@@ -610,7 +506,7 @@ Err launch(HxDev& a, void* ws, size_t ws_bytes, hipStream_t s) {
     default: go(std::integral_constant<int, 8>{}); break;
   }
   CHASE_LAUNCH_CHECK();
-  if (a.unit != 1 || a.TM % a.teams == 0) return ok();  // every strip whole in one part
+  if (hx_plan_bytes(a) == 0) return ok();  // every strip whole in one part
   hipLaunchKernelGGL(hx_reduce_kernel, dim3((unsigned)a.TM, (unsigned)ceil_div(a.N, (int64_t)16)), block, 0, s, a);
   CHASE_LAUNCH_CHECK();
   return ok();

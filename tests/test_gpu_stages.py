@@ -740,3 +740,32 @@ def test_qr_product_shapes(k):
     assert np.max(np.abs(R - Rr * ph.conj()[:, None])) < 1e-11 * np.max(np.abs(Rr))
     assert np.max(np.abs(np.tril(R, -1))) == 0.0
     s.close()
+
+
+# c128 products where the workspace decides the cut: sizes that ran on whole
+# strips for want of room (m = 1050, 2 k = 544, 1450 with 576), a forced split whose
+# partial sums do not fit (m = 850: "0,64" wants 14 strips in 64 parts of 8
+# column tiles, whole strips), one whose do in part (4 tiles), and exactly one
+# workgroup of the widest tiles per CU (m = 2000, 2 k = 1024).  Each against H X
+# formed by matmul, a sum of 2n products: 1e-12 of the largest entry
+@pytest.mark.parametrize("m,k,plan", [(1050, 272, None), (1450, 288, None), (850, 512, "0,64"), (850, 256, "0,64"),
+                                      (2000, 512, None)])
+def test_apply_h_fp64_workspace(m, k, plan, monkeypatch):
+    print_case("apply_h_fp64_workspace", m=m, k=k, plan=plan)
+    if plan:
+        monkeypatch.setenv("CHASE_PH_APPLY_PLAN", plan)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + k)
+
+    def normal(*shape):
+        return torch.complex(torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen),
+                             torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen))
+
+    A, B = normal(m, m), normal(m, m)
+    A, B = (A + A.mH).contiguous(), (B + B.T).contiguous()
+    x, y = normal(m, k), normal(m, k)
+    ref = torch.cat([A @ x + B @ y, -(B.conj() @ x) - A.conj() @ y])
+    s = PHSolver(A, B, 8, 8)
+    Y = s.apply_h(torch.cat([x, y]).T.contiguous().T)
+    assert (Y - ref).abs().max() <= 1e-12 * ref.abs().max()
+    s.close()
