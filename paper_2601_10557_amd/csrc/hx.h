@@ -64,8 +64,8 @@ enum HxKind {
 };
 
 // Y = H X (HX_TDA: A X) on k columns of complex X; yr holds the packed X
-// (hx_block_reals(m, 2 kcap) reals), calls with more than kcap columns run in
-// chunks.
+// (hx_block_reals(m, 2 kcap) reals); calls with more columns than that, or than
+// the cache holds packed (hx_group), run in chunks.
 struct HxApply {
   const double* M = nullptr;
   int64_t m = 0;

@@ -636,25 +636,32 @@ Err hx_step(const HxStep& a, void* ws, size_t ws_bytes, hipStream_t s) {
   if (a.N <= 0 || a.m <= 0) return ok();
   if (!a.M || !a.y || !a.out || a.ldc < ceil_div(a.N, (int64_t)16) * 16)
     return fail(CHASE_PH_ERR_ARG, "hx_step: operand or output missing");
-  HxDev d = operand(a.M, a.m, a.y, a.ldc, a.N);
-  d.out = a.out;
-  d.P = a.P;
-  d.Q = a.Q;
-  d.alpha = a.alpha;
-  d.beta = a.beta;
-  d.gamma = a.gamma;
-  d.rot = a.rot;
-  return launch(d, ws, ws_bytes, s);
+  const int group = (int)std::min<int64_t>(a.N, hx_group(2 * a.m));
+  for (int c0 = 0; c0 < a.N; c0 += group) {
+    const int64_t off = 4 * (int64_t)c0;
+    HxDev d = operand(a.M, a.m, a.y + off, a.ldc, std::min(group, a.N - c0));
+    d.out = a.out + off;
+    d.P = a.P ? a.P + off : nullptr;
+    d.Q = a.Q ? a.Q + off : nullptr;
+    d.alpha = a.alpha;
+    d.beta = a.beta;
+    d.gamma = a.gamma;
+    d.rot = a.rot;
+    CHASE_TRY(launch(d, ws, ws_bytes, s));
+  }
+  return ok();
 }
 
 Err hx_apply(const HxApply& a, void* ws, size_t ws_bytes, hipStream_t s) {
   if (a.k <= 0 || a.m <= 0) return ok();
   if (!a.M || !a.yr || a.kcap <= 0) return fail(CHASE_PH_ERR_ARG, "apply_h: operand or packed buffer missing");
   const int64_t ldc = hx_ldc(2 * (int64_t)a.kcap);
-  for (int c0 = 0; c0 < a.k; c0 += a.kcap) {
-    const int k = std::min(a.kcap, a.k - c0);
+  const int per = a.kind == HX_GENERAL ? 2 : 1;  // real columns of one of X
+  const int cap = (int)std::min<int64_t>(a.kcap, hx_group(2 * a.m) / per);
+  for (int c0 = 0; c0 < a.k; c0 += cap) {
+    const int k = std::min(cap, a.k - c0);
     CHASE_TRY(hx_pack(a.X + (int64_t)c0 * a.ldx, a.ldx, a.m, k, a.kind, a.yr, ldc, s));
-    HxDev d = operand(a.M, a.m, a.yr, ldc, a.kind == HX_GENERAL ? 2 * k : k);
+    HxDev d = operand(a.M, a.m, a.yr, ldc, per * k);
     d.kind = a.kind;
     d.Yc = a.Y + (int64_t)c0 * a.ldy;
     d.ldy = a.ldy;

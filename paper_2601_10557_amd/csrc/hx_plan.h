@@ -85,7 +85,11 @@ inline void hx_cut(HxPlan& p, int64_t rows2, int NB, int TN, int64_t most, size_
 inline double hx_long_us(const HxPlan& p, int64_t rows2) {
   const double frag_us = HX_FM * 2 * 64 / 2400.0;  // MFMA time of one slab and column fragment
   static const double narrow[5] = {0, 1.2, 1.12, 1.06, 1.05};
-  const double w = p.wmax * (p.wmax < 5 ? narrow[p.wmax] : 1.0);
+  double w = p.wmax * (p.wmax < 5 ? narrow[p.wmax] : 1.0);
+  // From m = 16000 on near ties go to the widest tiles: N = 384 in 4 tiles of 6
+  // fragments or 3 of 8: m = 16000 11.9 / 11.5 ms, 20000 18.8 / 18.2, 30000 47 / 42
+  // (N = 320, 4 of 5 or 3 of 7, is no tie: 35 / 43).
+  if (rows2 >= 32000 && p.wmax < HX_MAX_NL) w *= 1.02;
   // slabs of a team's part; alone on its CU a workgroup takes half the time
   double part = (double)p.TM / p.teams;
   if (p.unit != 1) part = hx_ceil(p.TM, p.teams) * (p.teams * p.TN <= HX_MAX_WG / 2 ? 0.5 : 1.0);
@@ -148,12 +152,22 @@ inline HxPlan hx_plan(int64_t rows2, int64_t N, size_t ws_bytes) {
   return p;
 }
 
+// Real columns of one launch: as many as stay in the Infinity Cache (256 MB),
+// whole tiles of 128.  Every strip of 128 rows reads all of them again, and the
+// one slab that a fragment of y is loaded ahead does not cover HBM: m = 30000,
+// N = 4800 (2.3 GB) 737 ms in one launch, 522 in launches of 512 columns (66 TF/s);
+// N = 1536 216 / 168; m = 16000, N = 2400 75.3 / 73.5 (1024 columns).
+inline int64_t hx_group(int64_t rows2) {
+  return std::max<int64_t>(128, ((int64_t)256 << 20) / (8 * rows2) / 128 * 128);
+}
+
 // Workspace with which every product of up to N real columns runs as planned with
 // unlimited room: none up to m = 850 or so (short products), 84 to 128 MiB above.
 // With less, parts are fewer: m = 1050, 2 k = 544 in 70 MB ran 17 teams of 73 and took
 // 195 us instead of 119, m = 1450, 2 k = 576 304 instead of 193.
 inline size_t hx_workspace(int64_t rows2, int64_t N) {
   size_t most = 0;
+  N = std::min(N, hx_group(rows2));
   for (int64_t c = 16; c < N + 16; c += 16)
     most = std::max(most, hx_plan_bytes(hx_plan(rows2, std::min(c, N), (size_t)1 << 40)));
   return most;

@@ -769,3 +769,43 @@ def test_apply_h_fp64_workspace(m, k, plan, monkeypatch):
     Y = s.apply_h(torch.cat([x, y]).T.contiguous().T)
     assert (Y - ref).abs().max() <= 1e-12 * ref.abs().max()
     s.close()
+
+
+# c128 products of more columns than one launch takes (2 x 12000 reals: 1280):
+# 1300 real columns of a product and of the recurrence, whose even and odd
+# degrees end in different buffers.  Against matmul at the bounds of the
+# smaller cases
+def test_c128_products_in_column_groups():
+    m, k = 12000, 650
+    print_case("column_groups", m=m, k=k)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+
+    def normal(*shape):
+        return torch.complex(torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen),
+                             torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen))
+
+    A = torch.diag(torch.linspace(1.0, 5.0, m, dtype=torch.float64, device="cuda")).to(torch.complex128)
+    B = normal(m, m) * (0.1 / m ** 0.5)
+    B = (B + B.T).contiguous()
+    X = normal(2 * m, k)
+
+    def hx(x):
+        u, v = x[:m], x[m:]
+        return torch.cat([A @ u + B @ v, -(B.conj() @ u) - A.conj() @ v])
+
+    s = PHSolver(A, B, k, 0)
+    ref = hx(X)
+    assert (s.apply_h(X.T.contiguous().T) - ref).abs().max() <= 1e-12 * ref.abs().max()
+    mu1, mu_nevex, mu_n = 0.8, 2.0, 6.0
+    c, e = 0.5 * (mu_n ** 2 + mu_nevex ** 2), 0.5 * (mu_n ** 2 - mu_nevex ** 2)
+    s1 = e / (mu1 ** 2 - c)
+    W1 = (s1 / e) * (hx(ref) - c * X)
+    s2 = 1.0 / (2.0 / s1 - s1)
+    W2 = (2.0 * s2 / e) * (hx(hx(W1)) - c * W1) - s1 * s2 * X
+    ref = torch.cat([W1[:, :30], W2[:, 30:]], dim=1)
+    W = X.T.contiguous().T
+    s.filter(W, mu1, mu_nevex, mu_n, degs=[1] * 30 + [2] * (k - 30), prec=FP64)
+    err = torch.linalg.vector_norm(W - ref, dim=0) / torch.linalg.vector_norm(ref, dim=0)
+    assert err.max() < 1e-11, err.max()
+    s.close()

@@ -19,12 +19,12 @@ int main() {
   while (std::scanf("%lld %lld %lld", &rows2, &N, &ws) == 3) {
     const size_t bytes = ws < 0 ? hx_workspace(rows2, -ws) : (size_t)ws;
     const HxPlan p = hx_plan(rows2, N, bytes);
-    std::printf("%zu %d %d %d %d %d %d %d %lld %lld %d %zu\n", bytes, p.shape, p.TM, p.TN, p.wq, p.wr, p.KB, p.teams,
+    std::printf("%lld %zu %d %d %d %d %d %d %d %lld %lld %d %zu\n", (long long)hx_group(rows2), bytes, p.shape, p.TM, p.TN, p.wq, p.wr, p.KB, p.teams,
                 (long long)p.lq, (long long)p.unit, p.lr, hx_plan_bytes(p));
   }
 }
 """
-KEYS = "ws shape TM TN wq wr KB teams lq unit lr need".split()
+KEYS = "group ws shape TM TN wq wr KB teams lq unit lr need".split()
 
 
 @pytest.fixture(scope="module")
@@ -55,7 +55,7 @@ def test_every_product_runs_as_with_unlimited_workspace(plans):
     have = plans([(r, n, -1024) for r, n in sizes])
     free = plans([(r, n, 1 << 40) for r, n in sizes])
     for (r, n), p, q in zip(sizes, have, free):
-        assert {k: p[k] for k in KEYS[1:]} == {k: q[k] for k in KEYS[1:]}, (r, n)
+        assert {k: p[k] for k in KEYS[2:]} == {k: q[k] for k in KEYS[2:]}, (r, n)
         assert p["need"] <= p["ws"] <= 128 << 20
 
 
@@ -82,3 +82,19 @@ def test_little_workspace(plans, ws):
         assert p["wq"] * p["TN"] + p["wr"] == -(-n // 16)
         if ws == 0 and p["KB"] > 1:
             assert p["unit"] == p["KB"] or p["TM"] % p["teams"] == 0
+
+
+def test_wide_products_stay_in_the_cache(plans):
+    # a launch takes as many columns as 256 MiB hold, whole tiles of 128
+    ms = [10, 4000, 8000, 12000, 16000, 30000, 60000, 200000]
+    for m, p in zip(ms, plans([(2 * m, 128, 0) for m in ms])):
+        g = p["group"]
+        assert g % 128 == 0 and g >= 128
+        assert g == 128 or 16 * m * g <= 256 << 20 < 16 * m * (g + 128), m
+    assert [p["group"] for p in plans([(60000, 1, 0), (32000, 1, 0)])] == [512, 1024]
+
+
+def test_near_ties_of_the_largest_products(plans):
+    wide = plans([(2 * m, n, 1 << 40) for m in (16000, 20000, 30000) for n in (384, 768)])
+    assert all(p["wq"] == 8 and p["wr"] == 0 for p in wide)
+    assert plans([(60000, 320, 1 << 40)])[0]["TN"] == 4
