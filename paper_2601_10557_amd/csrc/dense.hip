@@ -326,13 +326,15 @@ __device__ __forceinline__ void jacobi_block(c128 (*S)[SP][SP + 1], c128 (*U)[SP
   }
 }
 
-// Round 0 of a sweep, workgroup = pair.
-__global__ __launch_bounds__(256) void jacobi_first_kernel(const c128* G, int64_t ld, int nbj, c128* Uw, double thr,
-                                                           int* pflag) {
+// The rotations of round `round` from G as it is, workgroup = pair: round 0 of a
+// sweep (CROSS false) or a later one.
+template <bool CROSS>
+__global__ __launch_bounds__(256) void jacobi_pairs_kernel(const c128* G, int64_t ld, int nbj, int round, c128* Uw,
+                                                           double thr, int* pflag) {
   __shared__ c128 S[2][SP][SP + 1];
-  __shared__ c128 U[SP][SP + 1];
+  __shared__ c128 U[CROSS ? 1 : SP][SP + 1];
   const int pair = blockIdx.x;
-  const int bp = rr_player(pair, 0, nbj), bq = rr_player(nbj - 1 - pair, 0, nbj);
+  const int bp = rr_player(pair, round, nbj), bq = rr_player(nbj - 1 - pair, round, nbj);
   const int P = min(bp, bq) * JB, Q = max(bp, bq) * JB;
   int big = 0;
   for (int t = threadIdx.x; t < SP * SP; t += 256) {
@@ -341,11 +343,11 @@ __global__ __launch_bounds__(256) void jacobi_first_kernel(const c128* G, int64_
     const int gj = j < JB ? P + j : Q + j - JB;
     const c128 g = G[(int64_t)gj * ld + gi];
     S[0][i][j] = g;
-    U[i][j] = (i == j) ? c128{1.0, 0.0} : c128{0.0, 0.0};
+    if constexpr (!CROSS) U[i][j] = (i == j) ? c128{1.0, 0.0} : c128{0.0, 0.0};
     if (i != j && g.re * g.re + g.im * g.im > thr * thr) big = 1;
   }
   const bool needed = __syncthreads_or(big);
-  jacobi_block<false>(S, U, thr, needed, Uw + (int64_t)pair * SP * SP, pflag + pair);
+  jacobi_block<CROSS>(S, U, thr, needed, Uw + (int64_t)pair * SP * SP, pflag + pair);
 }
 
 // Index of row/col i (0..2*JB-1) of the subproblem of pair `pair` in round `round`.
@@ -910,6 +912,9 @@ constexpr int REFINE_KP = 1536;
 // From IN_PLACE_KP on, a round is bound by reading and writing G and V: there
 // the rotations are found in a launch of their own and applied in place, so that
 // blocks whose pairs did not rotate, most of them in late sweeps, stay untouched.
+// That launch reads its blocks of G as they are (taken through identity blocks, as
+// next_rotations would: Rayleigh-Ritz m = 5000, k = 4800 2000 ms against 1959, k = 3072
+// 542 / 518).
 constexpr int IN_PLACE_KP = 3072;
 
 // Eigenvectors V and (on the diagonal) eigenvalues of the Hermitian G: block
@@ -930,8 +935,6 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   const int npair = nbj / 2;
   CHASE_TRY(fill_padded(V, kp, kp, 1.0, 1.0, true, s, ws.flag + DenseWs::COUNTS, 2));
   const bool in_place = kp >= IN_PLACE_KP;
-  int* none = ws.pflag + 2 * npair;  // flags of no rotation
-  if (in_place) CHASE_HIP(hipMemsetAsync(none, 0, (size_t)npair * sizeof(int), s));
   const bool small = kp <= OFFDIAG_SMALL && ws.hpin && ws.hpin_bytes >= 5 * sizeof(double);
   if (!small) CHASE_TRY(frob_norm(G, kp, ws, s));
   // G is in cur; every round writes it to o[0] and the two change places.
@@ -996,24 +999,23 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
     // U and flags of a round and of the next
     c128* U[2] = {ws.U, ws.U + (int64_t)npair * SP * SP};
     int* fl[2] = {ws.pflag, ws.pflag + npair};
-    hipLaunchKernelGGL(jacobi_first_kernel, dim3(npair), dim3(256), 0, s, (const c128*)cur, (int64_t)kp, nbj, U[0], thr,
-                       fl[0]);
+    hipLaunchKernelGGL(jacobi_pairs_kernel<false>, dim3(npair), dim3(256), 0, s, (const c128*)cur, (int64_t)kp, nbj, 0,
+                       U[0], thr, fl[0]);
     CHASE_LAUNCH_CHECK();
     const int apply = npair * (npair + 1) / 2 + npair * (kp / SP);
-    auto round = [&](int r, int nspec, int blocks, c128* Gn, const int* flags) -> Err {
-      hipLaunchKernelGGL(jacobi_round_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, Gn, vec, (int64_t)kp, kp,
-                         nbj, r, (const c128*)U[r & 1], flags, U[(r + 1) & 1], fl[(r + 1) & 1], thr, nspec);
-      CHASE_LAUNCH_CHECK();
-      return ok();
-    };
     for (int r = 0; r < nbj - 1; ++r) {
-      const int nspec = r < nbj - 2 ? npair : 0;
-      if (in_place) {
-        CHASE_TRY(round(r, 0, apply, cur, fl[r & 1]));
-        if (nspec) CHASE_TRY(round(r, nspec, nspec, cur, none));
-      } else {
-        CHASE_TRY(round(r, nspec, nspec + apply, o[0], fl[r & 1]));
+      const int nspec = r < nbj - 2 && !in_place ? npair : 0;
+      c128* Gn = in_place ? cur : o[0];
+      hipLaunchKernelGGL(jacobi_round_kernel, dim3(nspec + apply), dim3(256), 0, s, (const c128*)cur, Gn, vec,
+                         (int64_t)kp, kp, nbj, r, (const c128*)U[r & 1], (const int*)fl[r & 1], U[(r + 1) & 1],
+                         fl[(r + 1) & 1], thr, nspec);
+      CHASE_LAUNCH_CHECK();
+      if (!in_place) {
         std::swap(cur, o[0]);
+      } else if (r < nbj - 2) {
+        hipLaunchKernelGGL(jacobi_pairs_kernel<true>, dim3(npair), dim3(256), 0, s, (const c128*)cur, (int64_t)kp, nbj,
+                           r + 1, U[(r + 1) & 1], thr, fl[(r + 1) & 1]);
+        CHASE_LAUNCH_CHECK();
       }
     }
   }

@@ -809,3 +809,45 @@ def test_c128_products_in_column_groups():
     err = torch.linalg.vector_norm(W - ref, dim=0) / torch.linalg.vector_norm(ref, dim=0)
     assert err.max() < 1e-11, err.max()
     s.close()
+
+
+# a quotient large enough (k = 3072) that the Jacobi rounds are applied in place,
+# their rotations found in launches of their own: Galerkin condition, diagonal
+# V^H S H V and residuals, formed by matmul; sums of 3200 products, the bounds of
+# the small quotients
+def test_rr_rounds_in_place():
+    m, kh = 1600, 1536
+    print_case("rr_in_place", m=m, k=2 * kh)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+
+    def normal(*shape):
+        return torch.complex(torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen),
+                             torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen))
+
+    E = normal(m, m) * (0.2 / m ** 0.5)
+    A = (torch.diag(torch.linspace(1.0, 5.0, m, dtype=torch.float64, device="cuda")).to(torch.complex128) + E + E.mH)
+    B = normal(m, m) * (0.05 / m ** 0.5)
+    A, B = A.contiguous(), (B + B.T).contiguous()
+    W = normal(2 * m, kh)
+    W[m:] *= 1e-3
+    X = torch.cat([W, torch.cat([W[m:].conj(), W[:m].conj()])], dim=1).T.contiguous().T
+    s = PHSolver(A, B, kh, 0)
+    s.qr(X)
+    ritz, Z, T = s.oblique_rr(X)
+    lam = torch.from_numpy(np.asarray(ritz)).cuda()
+    assert bool((lam[1:] >= lam[:-1]).all()) and lam[0] > 0
+    HX = torch.cat([A @ X[:m] + B @ X[m:], -(B.conj() @ X[:m]) - A.conj() @ X[m:]])
+    assert (T - HX).abs().max() <= 1e-12 * HX.abs().max()
+    V = X @ Z
+    nu = torch.linalg.vector_norm(V, dim=0)
+    V, HV = V / nu, (HX @ Z) / nu
+    R = HV - V * lam[None, :]
+    R[m:] *= -1.0
+    assert (X.mH @ R).abs().max() < 1e-11
+    HV[m:] *= -1.0
+    G = V.mH @ HV
+    d = torch.diagonal(G).real.abs().sqrt()
+    G = G / torch.outer(d, d) - torch.eye(kh, dtype=G.dtype, device="cuda")
+    assert G.abs().max() < 1e-11
+    s.close()
