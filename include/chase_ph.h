@@ -115,7 +115,8 @@ typedef struct {
                         /* those that take a residual of mu_m - mu_1 down to tol (p->nex is */
                         /* the largest candidate and sizes the workspace)                   */
   int32_t rr_max_sweeps; /* sweep limit of the Jacobi eigensolver of the Rayleigh quotient  */
-                        /* (default 40); CHASE_PH_ERR_EIG when it is reached unconverged    */
+                        /* (default 40); CHASE_PH_ERR_EIG when it is reached unconverged.   */
+                        /* Refinement steps in place of its last sweeps are not counted     */
 } chase_ph_params;
 
 typedef struct {
@@ -136,7 +137,8 @@ typedef struct {
   int32_t backup_rr_used;  /* iterations whose Rayleigh-Ritz used the back-up quotient      */
   int32_t general_rr_used; /* iterations whose Rayleigh-Ritz used the general quotient      */
   int32_t nex_used;        /* extra search vectors of the solve (p->nex unless nex_auto)     */
-  int32_t rr_sweeps_max;   /* most Jacobi sweeps one Rayleigh-Ritz step took                 */
+  int32_t rr_sweeps_max;   /* most Jacobi sweeps one Rayleigh-Ritz step took (refinement     */
+                           /* steps in place of the last ones not counted)                   */
   int32_t qr_one_pass;     /* iterations whose Cholesky QR stopped after one pass (Q^H Q     */
                            /* within 1e-13 of I after it: a well-conditioned block)          */
 } chase_ph_info;

@@ -40,8 +40,9 @@ Err cholesky_inverse(c128* M, c128* X, int kp, DenseWs& ws, hipStream_t s, int s
 // X = L^{-1} for lower-triangular L (both kp x kp, ld kp); X must not alias L.
 Err tri_inverse_lower(const c128* L, c128* X, int kp, DenseWs& ws, hipStream_t s);
 // G (Hermitian, in place) -> eigenvalues theta on the diagonal, V ->
-// eigenvectors, by block Jacobi sweeps and GEMM refinement steps, each counted
-// as a sweep.  guard >= 0: if ws.flag[guard] is set, *tripped and nothing else.
+// eigenvectors, by at most max_sweeps block Jacobi sweeps and by GEMM refinement
+// steps, which are not counted.  guard >= 0: if ws.flag[guard] is set, *tripped
+// and nothing else.
 Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sweeps, int* sweeps_out,
                 int guard = -1, bool* tripped = nullptr);
 // Positive eigenvalues theta of the first k: Ysel (kp x k/2, ld kp) and

@@ -943,6 +943,7 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
   int first = 1;
   double* part = reinterpret_cast<double*>(ws.panel);  // 3 kp doubles
   int sweep = 0;
+  double ef_last = 1e300;  // ||E||_F of the step before, where there was one
   bool converged = false;
   for (;;) {
     double st[4] = {0, 0, 0, 0};
@@ -972,9 +973,10 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
       converged = true;
       break;
     }
-    if (sweep == max_sweeps) break;
-    ++sweep;
-    if (ef <= (kp < REFINE_KP ? REFINE_MAX : REFINE_SHORT)) {
+    // steps do not count as sweeps: where one at least halves ||E||_F there are
+    // fewer than 30 in a row, where it does not a sweep is next
+    if (ef <= std::min(kp < REFINE_KP ? REFINE_MAX : REFINE_SHORT, 0.5 * ef_last)) {
+      ef_last = ef;
       const int blocks = grid_for((int64_t)kp * kp);
       c128 *W = o[0], *T = o[1], *T2 = ef > REFINE_SHORT ? o[2] : nullptr, *Z = ef > REFINE_MID ? ws.k4 : nullptr;
       hipLaunchKernelGGL(refine_e_kernel, dim3(blocks), dim3(256), 0, s, (const c128*)cur, W, kp, thr * thr);
@@ -996,6 +998,9 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
       CHASE_TRY(gemm_kp(1, kp, W, T, 0.0, cur, ws, s));
       continue;
     }
+    if (sweep == max_sweeps) break;
+    ++sweep;
+    ef_last = 1e300;
     // U and flags of a round and of the next
     c128* U[2] = {ws.U, ws.U + (int64_t)npair * SP * SP};
     int* fl[2] = {ws.pflag, ws.pflag + npair};

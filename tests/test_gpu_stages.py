@@ -851,3 +851,22 @@ def test_rr_rounds_in_place():
     G = G / torch.outer(d, d) - torch.eye(kh, dtype=G.dtype, device="cuda")
     assert G.abs().max() < 1e-11
     s.close()
+
+
+# A search block eps away from an invariant subspace and the number of sweeps that
+# a cyclic Jacobi method needs from its quotient (counted in numpy): enough as the
+# limit, also where refinement steps, which need one more than sweeps do from
+# ||o_ij / (g_jj - g_ii)||_F of 0.1 on, take the place of the last ones
+@pytest.mark.parametrize("kh,eps,limit", [(6, 1e-3, 3), (20, 1e-2, 3), (32, 1e-2, 3), (32, 3e-2, 4), (32, 0.1, 5)])
+def test_rr_sweep_limit_of_a_cyclic_jacobi(prob, kh, eps, limit):
+    print_case("rr_sweep_limit", m=prob.m, k=2 * kh, eps=eps, limit=limit)
+    lam, Vp = dense.dense_ph_eig(prob.A, prob.B)
+    X = np.concatenate([Vp[:, :kh], ham.apply_k_conj(Vp[:, :kh])], axis=1)
+    X = X / np.linalg.norm(X, axis=0)
+    X = X + eps * complex_normal(np.random.default_rng(kh), X.shape) / np.sqrt(prob.n)
+    Q, _, _ = oqr.cholqr2(X)
+    A, B = dev_blocks(prob)
+    s = PHSolver(A, B, 32, 0, rr_max_sweeps=limit)
+    ritz, _, _ = s.oblique_rr(to_dev(Q))
+    assert np.allclose(ritz, rayleigh_ritz.oblique_rr(prob.A, prob.B, Q)[0], rtol=1e-11, atol=0)
+    s.close()
