@@ -767,7 +767,11 @@ Err rr_impl(chase_ph_t h, int k, const c128* Q, int64_t ldq, double* ritz, c128*
   if (failed) return fail(CHASE_PH_ERR_NOT_DEFINITE, "Cholesky of Q^H S H Q failed (SH not positive definite on range(Q))");
   h->last_sweeps = sweeps;
   CHASE_TRY(select_positive(h->G, h->Ev, k, kp, h->Ys, h->dlam, h->dws, h->st));
-  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, Zpos, ldz));  // Z = L^{-H} Y
+  // Z = L^{-H} Y, into a caller's buffer only when all k / 2 pairs are resolved
+  // (their number is read below, after one wait for everything)
+  const bool own = Zpos == h->Zp;
+  CHASE_TRY(gemm(h, 1, 0, k, k / 2, k, {1, 0}, h->Li, kp, h->Ys, kp, {0, 0}, own ? Zpos : h->G, own ? ldz : kp));
+  if (!own) CHASE_TRY(copy_if_resolved(h->G, kp, Zpos, ldz, k, k / 2, h->dws, h->st));
   int cnt[2] = {0, 0};
   std::vector<double> lam(ritz ? k / 2 : 0);
   CHASE_TRY(d2h_small(lam.data(), h->dlam, sizeof(double) * lam.size(), h->dws, h->st, cnt,

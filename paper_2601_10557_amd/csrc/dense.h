@@ -52,6 +52,10 @@ Err jacobi_eigh(c128* G, c128* V, int kp, DenseWs& ws, hipStream_t s, int max_sw
 // and the counters at zero.
 Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, double* dlam, DenseWs& ws,
                     hipStream_t s);
+// dst (rows x half) <- src if select_positive found half positive and half
+// negative eigenvalues, else nothing.
+Err copy_if_resolved(const c128* src, int64_t lds, c128* dst, int64_t ldd, int rows, int half, DenseWs& ws,
+                     hipStream_t s);
 
 // Householder QR (householder.hip): panels of HH_PANEL columns, row-parallel
 // launches of HH_PARTS one-wave workgroups.

@@ -629,6 +629,12 @@ __global__ void select_kernel(const c128* G, const c128* V, int64_t ld, int k, i
   for (int row = threadIdx.x; row < kp; row += blockDim.x) Ysel[(int64_t)r * kp + row] = V[(int64_t)i * ld + row];
 }
 
+__global__ void copy_if_resolved_kernel(const c128* src, int64_t lds, c128* dst, int64_t ldd, int rows, int half,
+                                        const int* counts) {
+  if (counts[0] != half || counts[1] != half) return;
+  for (int i = threadIdx.x; i < rows; i += blockDim.x) dst[blockIdx.x * ldd + i] = src[blockIdx.x * lds + i];
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1038,6 +1044,14 @@ Err select_positive(const c128* G, const c128* V, int k, int kp, c128* Ysel, dou
   int* counts = ws.flag + DenseWs::COUNTS;
   hipLaunchKernelGGL(select_kernel, dim3(k), dim3(256), 0, s, G, V, (int64_t)kp, k, kp, (const double*)ws.dscalar, Ysel,
                      dlam, counts, counts + 1);
+  CHASE_LAUNCH_CHECK();
+  return ok();
+}
+
+Err copy_if_resolved(const c128* src, int64_t lds, c128* dst, int64_t ldd, int rows, int half, DenseWs& ws,
+                     hipStream_t s) {
+  hipLaunchKernelGGL(copy_if_resolved_kernel, dim3(half), dim3(256), 0, s, src, lds, dst, ldd, rows, half,
+                     (const int*)ws.flag + DenseWs::COUNTS);
   CHASE_LAUNCH_CHECK();
   return ok();
 }

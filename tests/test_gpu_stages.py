@@ -870,3 +870,20 @@ def test_rr_sweep_limit_of_a_cyclic_jacobi(prob, kh, eps, limit):
     ritz, _, _ = s.oblique_rr(to_dev(Q))
     assert np.allclose(ritz, rayleigh_ritz.oblique_rr(prob.A, prob.B, Q)[0], rtol=1e-11, atol=0)
     s.close()
+
+
+def test_singular_qsq_leaves_the_outputs_alone(prob, solver):
+    # the refused call writes neither the Ritz values nor Z
+    import ctypes
+    print_case("singular_qsq_outputs", m=prob.m, k=4)
+    m, k = prob.m, 4
+    Q = np.zeros((prob.n, k), dtype=np.complex128)
+    for j in range(k):
+        Q[j, j] = Q[m + j, j] = 1 / np.sqrt(2)
+    Q = to_dev(Q)
+    Z, T = torch.full((k // 2, k), 7.0 - 3.0j, dtype=torch.complex128, device="cuda").T, empty_cm(prob.n, k)
+    ritz = (ctypes.c_double * (k // 2))(5.0, 6.0)
+    st = _lib.load().chase_ph_oblique_rr(solver._h, k, Q.data_ptr(), prob.n, ritz, Z.data_ptr(), k, T.data_ptr(), prob.n)
+    assert st == _lib.ERR_SINGULAR_QSQ
+    assert list(ritz) == [5.0, 6.0]
+    assert bool((Z == 7.0 - 3.0j).all())
