@@ -93,6 +93,7 @@ struct chase_ph_s {
   DenseWs dws;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   double last_ms = 0;
+  bool timing_pending = false;  // last_ms is still to be read from e0 and e1
   int last_launches = 0;
   int last_sweeps = 0;  // Jacobi sweeps of the last Alg. 2 Rayleigh-Ritz step
   bool qr_one_pass = false;  // the last qr_impl stopped after one Cholesky QR pass
@@ -488,15 +489,18 @@ Err read_timing(chase_ph_t h) {
   float ms = 0;
   CHASE_HIP(hipEventElapsedTime(&ms, h->e0, h->e1));
   h->last_ms = ms;
+  h->timing_pending = false;
   return ok();
 }
 
-// wait = false: the caller reads the timing later (read_timing).
+// wait = false: the timing is read later (read_timing, at the solve's end or by
+// chase_ph_last_timing).
 Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
                double mu_n, int prec, double* flops, bool wait = true) {
   if (k == 0) return ok();
   int launches = 0;
   double fl = 0;
+  h->timing_pending = false;
   CHASE_HIP(hipEventRecord(h->e0, h->st));
   if (prec == CHASE_PH_FP32) {
     CHASE_TRY(ensure_shadow(h));
@@ -507,6 +511,7 @@ Err filter_any(chase_ph_t h, int k, void* dW, int64_t ldw, const std::vector<int
   CHASE_HIP(hipEventRecord(h->e1, h->st));
   h->last_launches = launches;
   if (flops) *flops = fl;
+  h->timing_pending = true;
   return wait ? read_timing(h) : ok();
 }
 
@@ -1196,7 +1201,6 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
   int g0 = mixed ? 0 : nevex, g1 = 0;  // W columns: [mode 0 | mode 1 | mode 2]
   int hist_pos = 0;
   *converged = false;
-  bool filtered = false;
   for (int it = 0; it < p.max_iter; ++it) {
     const int kw = nevex - locked;
     double fl = 0;
@@ -1204,7 +1208,6 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
     if (g0 > 0) {
       std::vector<int> d0(degs.begin(), degs.begin() + g0);
       CHASE_TRY(filter_any(h, g0, h->Wk, n, d0, mu1, mu_nevex, mu_n, CHASE_PH_FP64, &fl, false));
-      filtered = true;
       inf.filter_flops += fl;
       if (inf.switch_iter < 0 && mixed) inf.switch_iter = it;
     }
@@ -1223,7 +1226,6 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
       std::vector<int> d2(degs.begin() + c0, degs.begin() + kw);
       CHASE_TRY(convert_to_c64(h->Wk + (int64_t)c0 * n, n, h->W32, n, n, k32, h->st));
       CHASE_TRY(filter_any(h, k32, h->W32, n, d2, mu1, mu_nevex, mu_n, CHASE_PH_FP32, &fl, false));
-      filtered = true;
       CHASE_TRY(convert_to_c128(h->W32, n, h->Wk + (int64_t)c0 * n, n, n, k32, h->st));
       inf.filter_flops_fp32 += fl;
       inf.filter_flops += fl;
@@ -1438,7 +1440,7 @@ Err solve_impl(chase_ph_t h, const c128* W0, int64_t ldw0, const c128* Lz, int64
   CHASE_HIP(hipEventSynchronize(t1));
   float ms = 0;
   CHASE_TRY(tm.collect());
-  if (filtered) CHASE_TRY(read_timing(h));
+  if (h->timing_pending) CHASE_TRY(read_timing(h));
   CHASE_HIP(hipEventElapsedTime(&ms, t0, t1));
   (void)hipEventDestroy(t0);
   (void)hipEventDestroy(t1);
@@ -1829,6 +1831,7 @@ chase_ph_status chase_ph_apply_h(chase_ph_t h, int32_t k, const void* dX, int64_
       hipEventElapsedTime(&ms, h->e0, h->e1) != hipSuccess)
     return finish(h, fail(CHASE_PH_ERR_HIP, "apply_h: kernel failed"));
   h->last_ms = ms;
+  h->timing_pending = false;
   h->last_launches = 1;
   return CHASE_PH_OK;
 }
@@ -1969,6 +1972,10 @@ chase_ph_status chase_ph_profile_read(chase_ph_t h, int32_t prec, double* total_
 
 chase_ph_status chase_ph_last_timing(chase_ph_t h, double* ms, int32_t* launches) {
   if (!h) return CHASE_PH_ERR_ARG;
+  if (h->timing_pending && !h->dead) {  // the solve ended with an error after this filter
+    const Err e = read_timing(h);
+    if (e) return finish(h, e);
+  }
   if (ms) *ms = h->last_ms;
   if (launches) *launches = h->last_launches;
   return CHASE_PH_OK;

@@ -282,3 +282,22 @@ def test_solve_on_wide_real_products():
     D = (X.conj().T.contiguous() @ X - Y.conj().T.contiguous() @ Y).cpu().numpy()
     assert np.max(np.abs(D - np.diag(np.diag(D)))) < 1e-5
     s.close()
+
+
+def test_timing_of_the_last_filter_after_a_failed_solve():
+    # one Jacobi sweep does not converge in the first iteration: the solve ends
+    # with CHASE_PH_ERR_EIG after its first filter, whose time and launches (two
+    # products a degree) chase_ph_last_timing reports
+    p = make_problem(300, lambda rng, m: rng.uniform(1.0, 5.0, m), 0.4, 12, 8, 10, 1e-10, seed=0)
+    print_case("timing_after_failed_solve", m=p.m)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, p.nev, p.nex, deg=10, rr_max_sweeps=1)
+    with pytest.raises(ChasePHError) as e:
+        s.solve(to_dev(p.w0_raw), to_dev(p.lanczos_raw))
+    assert e.value.status == _lib.ERR_EIG
+    ms, launches = s.last_timing()
+    assert launches == 20
+    assert 0 < ms < 1000
+    s.apply_h(to_dev(p.w0_raw))
+    assert s.last_timing()[1] == 1
+    s.close()
