@@ -904,13 +904,15 @@ static Err gemm_kp(int ta, int kp, const c128* A, const c128* B, double beta, c1
   return zgemm(g, ws.gemm_ws, ws.gemm_ws_bytes, s);
 }
 
-// Largest ||E||_F at which a sweep is replaced by a refinement step: there the
-// first term left out of W, 33/2048 E^14, is below rounding; up to which that
-// of the form with E^8, 7/256 E^10, is; and that of I + E + E^2 / 2, E^4 / 8.
+// Largest ||E||_F at which a sweep is replaced by a refinement step, up to which
+// the form with E^8 is enough, and that of I + E + E^2 / 2: there the first term
+// left out, 33/2048 ||E||^14, 7/256 ||E||^10 and ||E||^4 / 8, is below the unit
+// roundoff (in the spectral norm, at most the Frobenius one: 7.9e-17, 7.5e-17 and
+// 1.3e-17).
 // From 0.05 on, a sweep (500 us at kp = 384) and two steps are left, or four
 // steps of 60 to 180 us: Rayleigh-Ritz m = 4000, k = 376 4.19 -> 3.80 ms against a
 // limit of 0.04.
-constexpr double REFINE_MAX = 0.1, REFINE_MID = 0.04, REFINE_SHORT = 1e-4;
+constexpr double REFINE_MAX = 0.095, REFINE_MID = 0.035, REFINE_SHORT = 1e-4;
 // From REFINE_KP on, a step of 6 or 7 products takes as long as a sweep and does
 // less, so only the short form replaces one (k = 2600, solve of 5 iterations:
 // Rayleigh-Ritz 525 -> 502 ms).
