@@ -43,10 +43,11 @@ struct chase_ph_s {
   int64_t ldyr = 0;
   int kcap = 0;
   int64_t yrows = 0;
-  // c128 filter state in X4, 2 nevex real columns of pitch xld: even and odd
-  // degrees and the product in between; c64 filter work buffers (n x nevex)
+  // c128 filter state in X4, 2 nevex real columns (nevex on a TDA handle) of pitch
+  // xld: even and odd degrees (the product in between is in Yr); c64 filter work
+  // buffers (n x nevex)
   int64_t xld = 0;
-  double* X64[3] = {};
+  double* X64[2] = {};
   c64* W32 = nullptr;
   c64* F1_32 = nullptr;
   c64* FT_32 = nullptr;
@@ -164,12 +165,14 @@ Err gemm(chase_ph_t h, int ta, int tb, int64_t M, int64_t N, int64_t K, c128 alp
   return zgemm(g, h->ws, h->ws_bytes, h->st);
 }
 
-// Block of 2 nevex real columns in X4, all zero: the products write the live
-// rows only, the pad rows stay zero.
-Err alloc_x4(chase_ph_t h, double** p) {
-  const size_t reals = (size_t)hx_block_reals(h->m, 2 * (int64_t)h->nevex);
-  CHASE_TRY(dalloc(h, p, reals));
-  CHASE_HIP(hipMemsetAsync(*p, 0, reals * sizeof(double), h->st));
+// Blocks of the c128 filter in X4.  Products write the live rows only: the pad rows
+// of the odd degrees' block are zero from here on, those of the others are packed.
+Err alloc_x4(chase_ph_t h) {
+  const int64_t cols = (h->p.tda ? 1 : 2) * (int64_t)h->nevex;
+  const size_t reals = (size_t)hx_block_reals(h->m, cols);
+  h->xld = hx_ldc(cols);
+  for (double*& x : h->X64) CHASE_TRY(dalloc(h, &x, reals));
+  CHASE_HIP(hipMemsetAsync(h->X64[1], 0, reals * sizeof(double), h->st));
   return ok();
 }
 
@@ -293,16 +296,17 @@ Err step64(chase_ph_t h, int k, const double* y, double* out, int rot, double al
 // Scaled Chebyshev recurrence on H^2 (eq. 4.1, Zhou-Saad scaling); see
 // chase_ph_filter.  The block is packed once and stays in X4 until the
 // columns' degrees are done: W_s in X[s % 2] (the second product of each
-// degree writes W_s in place over W_{s-2}), the product in between in X[2].
+// degree writes W_s in place over W_{s-2}), the product in between in X[2], the
+// buffer that other products pack into.
 Err filter64(chase_ph_t h, int k, c128* W, int64_t ldw, const std::vector<int>& d, double mu1, double mu_nevex,
              double mu_n, int* launches, double* flops) {
-  double* const (&X)[3] = h->X64;
+  double* const X[3] = {h->X64[0], h->X64[1], h->Yr};
   const double c = 0.5 * (mu_n * mu_n + mu_nevex * mu_nevex);
   const double e = 0.5 * (mu_n * mu_n - mu_nevex * mu_nevex);
   const double sigma1 = e / (mu1 * mu1 - c);
   double sigma = sigma1;
   const int maxd = d[k - 1];
-  CHASE_TRY(hx_pack(W, ldw, h->m, k, HX_GENERAL, X[0], h->xld, h->st));
+  CHASE_TRY(hx_pack(W, ldw, h->m, k, HX_GENERAL, X[0], h->xld, h->st, X[2]));
   int j0 = 0;
   for (int s = 1; s <= maxd; ++s) {
     while (j0 < k && d[j0] < s) ++j0;
@@ -1090,7 +1094,7 @@ Err filter_tda(chase_ph_t h, int k, c128* W, int64_t ldw, int deg, double mu1, d
   if (k == 0) return ok();
   const double c = 0.5 * (mu_m + mu_nevex), e = 0.5 * (mu_m - mu_nevex);
   const double s1 = e / (mu1 - c);
-  double* const (&X)[3] = h->X64;
+  double* const (&X)[2] = h->X64;
   CHASE_TRY(hx_pack(W, ldw, h->m, k, HX_TDA, X[0], h->xld, h->st));
   CHASE_TRY(step64(h, k, X[0], X[1], HX_NONE, s1 / e, X[0], -s1 * c / e));
   double sigma = s1;
@@ -1652,8 +1656,7 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   h->ldyr = 4 * (int64_t)h->kcap + 8;
   h->yrows = (h->m + 31) / 32 * 32;
   CHASE_TRY(dalloc(h, &h->Yr, (size_t)std::max(hx_block_reals(h->m, 2 * (int64_t)h->kcap), h->ldyr * h->yrows)));
-  h->xld = hx_ldc(2 * (int64_t)h->nevex);
-  for (double*& x : h->X64) CHASE_TRY(alloc_x4(h, &x));
+  CHASE_TRY(alloc_x4(h));
   CHASE_TRY(dalloc(h, &h->Xs, (size_t)n * h->kmax));
   CHASE_TRY(dalloc(h, &h->Xt, (size_t)n * h->kmax));
   CHASE_TRY(dalloc(h, &h->Tq, (size_t)n * h->kmax));

@@ -79,8 +79,10 @@ struct HxApply {
 };
 Err hx_apply(const HxApply& a, void* ws, size_t ws_bytes, hipStream_t s);
 
-// Complex block -> X4 (pads written as zero) and back.
-Err hx_pack(const c128* X, int64_t ldx, int64_t m, int k, int kind, double* Y, int64_t ldc, hipStream_t s);
+// Complex block -> X4 (pads written as zero, also those of the block Z, which
+// products will be written to, if given) and back.
+Err hx_pack(const c128* X, int64_t ldx, int64_t m, int k, int kind, double* Y, int64_t ldc, hipStream_t s,
+            double* Z = nullptr);
 Err hx_unpack(const double* Y, int64_t ldc, int64_t m, int k, int kind, c128* X, int64_t ldx, hipStream_t s);
 
 }  // namespace chase

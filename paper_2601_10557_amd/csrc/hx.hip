@@ -574,12 +574,17 @@ __device__ __forceinline__ void pack_place(int64_t* q, int* j) {
 }
 
 __global__ __launch_bounds__(256) void hx_pack_kernel(const c128* X, int64_t ldx, int64_t m, int k, int general,
-                                                      double* Y, int64_t ldc4, int64_t k4) {
+                                                      double* Y, int64_t ldc4, int64_t k4, double* Z) {
   int64_t q;
   int j;
   pack_place(&q, &j);
   if (q >= k4 || j >= k) return;
   const Rows2 v = load_rows(X, ldx, m, q, j, general != 0);
+  if (Z && 2 * q >= m) {  // zeros past row 2m of another block
+    const int64_t at = q * ldc4 + (general ? 8 : 4) * j;
+    store4(Z + at, doublex4{0, 0, 0, 0});
+    if (general) store4(Z + at + 4, doublex4{0, 0, 0, 0});
+  }
   if (!general) {
     store4(Y + q * ldc4 + 4 * j, doublex4{v.a0.re, v.a0.im, v.a1.re, v.a1.im});
     return;
@@ -670,11 +675,11 @@ Err hx_apply(const HxApply& a, void* ws, size_t ws_bytes, hipStream_t s) {
   return ok();
 }
 
-Err hx_pack(const c128* X, int64_t ldx, int64_t m, int k, int kind, double* Y, int64_t ldc, hipStream_t s) {
+Err hx_pack(const c128* X, int64_t ldx, int64_t m, int k, int kind, double* Y, int64_t ldc, hipStream_t s, double* Z) {
   if (k <= 0) return ok();
   const int64_t k4 = hx_k4(m);
   hipLaunchKernelGGL(hx_pack_kernel, pack_grid(k4, k), dim3(256), 0, s, X, ldx, m, k, kind == HX_GENERAL ? 1 : 0, Y,
-                     4 * ldc, k4);
+                     4 * ldc, k4, Z);
   CHASE_LAUNCH_CHECK();
   return ok();
 }

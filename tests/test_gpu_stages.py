@@ -887,3 +887,25 @@ def test_singular_qsq_leaves_the_outputs_alone(prob, solver):
     assert st == _lib.ERR_SINGULAR_QSQ
     assert list(ritz) == [5.0, 6.0]
     assert bool((Z == 7.0 - 3.0j).all())
+
+
+# the recurrence keeps the product of each degree in the buffer that other
+# products pack into: whatever those left there (NaN of more columns, so at other
+# places), also past row 2m, the filter's columns do not see it
+@pytest.mark.parametrize("m,k", [(5, 3), (33, 9), (64, 7), (75, 20)])
+def test_filter_fp64_after_a_product_of_nan(m, k):
+    print_case("filter_after_nan", m=m, k=k)
+    p = problem(m=m, seed=m, nev=1, nex=0)
+    A, B = dev_blocks(p)
+    s = PHSolver(A, B, k, 0)
+    s.apply_h(torch.full((512, p.n), float("nan"), dtype=torch.complex128, device="cuda").T)
+    rng = np.random.default_rng(m)
+    W = complex_normal(rng, (p.n, k))
+    degs = [1 + j % 3 for j in range(k)]
+    degs.sort()
+    Wd = to_dev(W)
+    s.filter(Wd, 1.0, 2.5, 6.0, degs=degs, prec=FP64)
+    ref = chebyshev.chebyshev_filter(p.A, p.B, W, np.array(degs), 1.0, 2.5, 6.0)
+    err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.max(err) < 1e-11, err
+    s.close()
