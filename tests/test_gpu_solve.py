@@ -301,3 +301,46 @@ def test_timing_of_the_last_filter_after_a_failed_solve():
     s.apply_h(to_dev(p.w0_raw))
     assert s.last_timing()[1] == 1
     s.close()
+
+
+def test_solve_projects_off_locked_pairs_on_wide_real_products():
+    # With 168 of 600 pairs locked after four iterations the fifth one projects 864
+    # columns of 8000 reals off 336: C = Qp^T X and X -= Qp C, both real and wide
+    # enough for the 64 x 64 tiles (8000 x 864 >= 400 x 128 x 128 outputs, K = 336
+    # beyond the short products).  A fault there would leave the new basis
+    # non-orthogonal: every pair locked then against H V formed by matmul, and
+    # eq. 3.5 between the old and the new ones
+    m, nev, nex, tol = 4000, 560, 40, 1e-7
+    print_case("solve_projection_wide_real", m=m, nev=nev, nex=nex)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+
+    def normal(*shape):
+        return torch.complex(torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen),
+                             torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen))
+
+    d = torch.linspace(1.0, 9.0, m, dtype=torch.float64, device="cuda")
+    B = normal(m, m) * (0.05 / m ** 0.5)
+    B = (0.5 * (B + B.T)).contiguous()
+    A = torch.diag(d).to(torch.complex128)
+    W0 = (torch.eye(2 * m, nev + nex, dtype=torch.complex128, device="cuda") + 1e-2 * normal(2 * m, nev + nex) / m ** 0.5)
+    Lz = normal(2 * m, 4)
+    locked = []
+    for max_iter in (4, 5):
+        s = PHSolver(A, B, nev, nex, deg=10, tol=tol, max_iter=max_iter, precision=FP64)
+        ev, V, res, info = s.solve(W0.T.contiguous().T, Lz.T.contiguous().T, raise_on_noconv=False)
+        locked.append(info.locked)
+        s.close()
+    before, now = locked
+    cols = 2 * (nev + nex - before)
+    assert 2 * m * cols >= 400 * 128 * 128 and 2 * m * cols * 2 * before > 2.8e8, locked
+    assert now > before
+    lam = torch.from_numpy(np.asarray(ev)[:now]).cuda().to(torch.complex128)
+    V = V[:, :now]
+    X, Y = V[:m], V[m:]
+    HV = torch.cat([A @ X + B @ Y, -(B.conj() @ X) - A.conj() @ Y])
+    r = torch.linalg.vector_norm(HV - V * lam[None, :], dim=0).cpu().numpy()
+    assert np.all(r <= 1.5 * tol), r.max()
+    assert np.all(np.abs(r - np.asarray(res)[:now]) <= 1e-10)
+    D = (X.conj().T.contiguous() @ X - Y.conj().T.contiguous() @ Y).cpu().numpy()
+    assert np.max(np.abs(D - np.diag(np.diag(D)))) < 1e-5
