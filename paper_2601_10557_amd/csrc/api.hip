@@ -198,7 +198,7 @@ Err alloc_shadow(chase_ph_t h) {
 
 Err refresh_shadow(chase_ph_t h) {
   CHASE_TRY(alloc_shadow(h));
-  CHASE_TRY(make_d<c64>(h->A, h->p.tda ? nullptr : h->B, h->ld, h->p.a_conj, h->D32, h->ldd, h->m, h->st));
+  CHASE_TRY(make_d(h->A, h->p.tda ? nullptr : h->B, h->ld, h->p.a_conj, h->D32, h->ldd, h->m, h->st));
   h->shadow_ready = true;
   return ok();
 }
@@ -1702,7 +1702,7 @@ Err create_impl(const chase_ph_params* p, const void* dA, const void* dB, int64_
   CHASE_TRY(dalloc(h, &h->dws.tmp, (size_t)h->kp * 64));
   CHASE_TRY(dalloc(h, &h->dws.U, (size_t)h->kp * 64));
   CHASE_TRY(dalloc(h, &h->dws.flag, 4));
-  CHASE_TRY(dalloc(h, &h->dws.pflag, (size_t)h->kp / 8 + 1));
+  CHASE_TRY(dalloc(h, &h->dws.pflag, (size_t)h->kp / 16));
   CHASE_TRY(dalloc(h, &h->dws.dscalar, 4));
   // pinned host staging for the small reads of every iteration (flags,
   // counts, Ritz values, residuals: at most kmax doubles)

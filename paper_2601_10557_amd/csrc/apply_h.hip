@@ -1,5 +1,5 @@
 // Block-structured product H X, H = [[A, B], [-conj(B), -conj(A)]]
-// (Section 1, eq. 1.1), as one real GEMM over the real structure of H.
+// (Section 1, eq. 1.1), in c64, as one real GEMM over the real structure of H.
 //
 // H is real-linear on K-real vectors (Thm 3.1: H K conj = -K conj H): for
 // u = [a; conj(a)],
@@ -439,9 +439,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // The remainder workgroups are short and bound by the read of M.  Where the
 // main tiles leave some of the 512 places empty (two a CU) they come after
 // those and fill them (m = 4000, two products, first / last: k = 200 1006 / 967
-// us, k = 330 1544 / 1487; m = 8000, k = 260 4404 / 4349); where the main tiles
+// us, k = 330 1544 / 1487; m = 8000, k = 260 4404 / 4349; where few are, 8 of 512,
+// m = 8000, k = 530 8580 / 8450, m = 3000, k = 210 663 / 660); where the main tiles
 // take every place they come first (k = 145 792 / 799, k = 260 1202 / 1201; mixed
-// orders put two main tiles on some CUs and none on others).  Each part starts
+// orders put two main tiles on some CUs and none on others).  The K split leaves
+// the last round of main tiles at least 440 of 512 full or full, at all sizes.  Each part starts
 // at a multiple of 8 (nrem and nmain rounded up, the padding workgroups exit at
 // once) so that the XCD of a workgroup stays blockIdx mod 8 in both.
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED, int BMR, int BNR, int BKR,
@@ -667,7 +669,6 @@ Err launch_pair_f32(const ApplyHArgs& am, const Plan& pm, void* wsm, const Apply
 }
 
 Err pack(const ApplyHArgs& a, hipStream_t s) {
-  using C = typename ApplyHArgs::C;
   const bool kr = a.tda != 0;
   const int kc = kr ? (a.k + 1) / 2 * 2 : a.k;
   const int tj = kr ? 32 : 16;
@@ -703,7 +704,7 @@ Err launch_wide_f32(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t 
 // column-wise, and so is the fused epilogue): the first k - r columns,
 // 2(k - r) a multiple of 128, on the widest tiles the plan picks, and the
 // last r <= 20 on the narrow tile with their own K split, both in one
-// launch (hx_pair_kernel, remainder workgroups first).  Y is packed for all
+// launch (hx_pair_kernel).  Y is packed for all
 // k columns before.  (A main part whose 2(k - r) is not a multiple of 128
 // would keep a padded tile column and pay the remainder on top.)
 Err launch_split(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
@@ -756,7 +757,6 @@ Err launch_any(const ApplyHArgs& a0, void* ws, size_t ws_bytes, hipStream_t s) {
 
 // D = [A + B, i (A - B)] column-interleaved (m x 2m, ldd); A is conj of the
 // buffer when a_conj.  Rows m .. ldd of every column are zero.
-template <typename C>
 __global__ void make_d_kernel(const c128* A, const c128* B, int64_t ld, int a_conj, C* D, int64_t ldd, int64_t m) {
   const int64_t total = ldd * m;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
@@ -783,15 +783,12 @@ Err launch_apply_h_f32(const ApplyHArgs& a, void* ws, size_t ws_bytes, hipStream
   return launch_any(a, ws, ws_bytes, s);
 }
 
-template <typename C>
-Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, C* D, int64_t ldd, int64_t m, hipStream_t s) {
+Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, c64* D, int64_t ldd, int64_t m, hipStream_t s) {
   const int64_t total = ldd * m;
   const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(ceil_div(total, 256), 16384));
-  hipLaunchKernelGGL((make_d_kernel<C>), dim3(blocks), dim3(256), 0, s, A, B, ld, a_conj, D, ldd, m);
+  hipLaunchKernelGGL(make_d_kernel, dim3(blocks), dim3(256), 0, s, A, B, ld, a_conj, D, ldd, m);
   CHASE_LAUNCH_CHECK();
   return ok();
 }
-
-template Err make_d<c64>(const c128*, const c128*, int64_t, int, c64*, int64_t, int64_t, hipStream_t);
 
 }  // namespace chase

@@ -32,20 +32,6 @@ constexpr int PB = 16;    // rows eliminated in registers at a time
 constexpr int NT = 256;
 constexpr int NTP = 512;  // panel kernel
 
-__device__ __forceinline__ double rcp_refined(double d) {  // to within about an ulp, d normal
-  double q = __builtin_amdgcn_rcp(d);
-  q = q * (2.0 - d * q);
-  q = q * (2.0 - d * q);
-  return q;
-}
-
-__device__ __forceinline__ double rsqrt_refined(double y) {
-  double r = __builtin_amdgcn_rsq(y);
-  r = r * (1.5 - 0.5 * y * r * r);
-  r = r * (1.5 - 0.5 * y * r * r);
-  return r;
-}
-
 // A non-positive or non-finite pivot is replaced by 1 so that the block stays
 // finite (it is flagged, and the result discarded).
 __device__ __forceinline__ double pivot(double d) { return d > 0.0 && isfinite(d) ? d : 1.0; }
@@ -97,7 +83,7 @@ __device__ __forceinline__ void panel_rows(Shared& sh, int kb, int w) {
   for (int j = 0; j < PB; ++j) {
     const double draw = lane_value(x[j].re, j);
     dv = lane == j ? draw : dv;
-    const double inv = rcp_refined(pivot(draw));
+    const double inv = rcp_nr(pivot(draw));
     const double tr = x[j].re * inv, ti = x[j].im * inv;
 #pragma unroll
     for (int i = j + 1; i < PB; ++i) {
@@ -115,8 +101,8 @@ __device__ __forceinline__ void panel_rows(Shared& sh, int kb, int w) {
   if (diag && w == 0) {
     const double d = pivot(dv);
     sh.d[p + lane] = dv;
-    sh.id[p + lane] = rcp_refined(d);
-    sh.rs[p + lane] = rsqrt_refined(d);
+    sh.id[p + lane] = rcp_nr(d);
+    sh.rs[p + lane] = rsqrt_nr(d);
   }
 }
 

@@ -22,17 +22,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <typename R>
-struct Cplx;
-template <>
-struct Cplx<float> {
-  using T = c64;
-};
-template <>
-struct Cplx<double> {
-  using T = c128;
-};
-
 // Status with message, returned by internal helpers.
 struct Err {
   chase_ph_status st = CHASE_PH_OK;
@@ -67,8 +56,26 @@ inline Err fail(chase_ph_status st, const std::string& m) { return Err{st, m}; }
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// 1 / sqrt(y) and 1 / d for normal positive y and nonzero d: hardware
+// estimates refined by two Newton steps each (r <- r (3 - y r^2) / 2 and
+// q <- q (2 - d q)), which take the estimate to within about an ulp.
+__device__ __forceinline__ double rsqrt_nr(double y) {
+  double r = __builtin_amdgcn_rsq(y);
+  r = r * (1.5 - 0.5 * y * r * r);
+  r = r * (1.5 - 0.5 * y * r * r);
+  return r;
+}
+
+__device__ __forceinline__ double rcp_nr(double d) {
+  double q = __builtin_amdgcn_rcp(d);
+  q = q * (2.0 - d * q);
+  q = q * (2.0 - d * q);
+  return q;
+}
+
 // ----------------------------------------------------------------------------
-// Block-structured operator H X from the blocks A, B (apply_h.hip).
+// Block-structured operator H X from the blocks A, B, in c64 (apply_h.hip; c128:
+// hx.h).
 //
 // Computes, for the active columns of an n x k block X, H X as one real
 // GEMM of M = D read as a real 2m x 2m matrix, D = [A + B, i (A - B)]
@@ -98,10 +105,6 @@ struct ApplyHArgs {
   const C* S;       // may be null
   int64_t lds;
   const R* dcol;    // k per-column scalars for S (device)
-  // 1: every column of X is K-real (x = [a; conj(a)]), so H x = [t; -conj(t)]
-  // with t from the real coordinates of a: the product runs on k real columns
-  // (c128 path, no P/Q/S)
-  int kreal = 0;
   // 1: Hermitian product A X on the resonant block alone (TDA; D built with
   // B = 0, so M is the real form of A): X is m x k, Y = alpha A X + ... is
   // m x k; the product runs on k real columns
@@ -118,8 +121,7 @@ struct ApplyHArgs {
 // D = [A + B, i (A - B)] column-interleaved (m x 2m, ldd; rows m .. ldd zero)
 // from the c128 blocks (ld); A is conj of its buffer when a_conj; B may be
 // null (B = 0: D = [A, i A], the real form of A).
-template <typename C>
-Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, C* D, int64_t ldd, int64_t m, hipStream_t s);
+Err make_d(const c128* A, const c128* B, int64_t ld, int a_conj, c64* D, int64_t ldd, int64_t m, hipStream_t s);
 
 // ws: device workspace for split-K partial products (ws_bytes may be 0:
 // then the K range is never split, nor the columns).

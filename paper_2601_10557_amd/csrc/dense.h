@@ -7,10 +7,10 @@ namespace chase {
 struct DenseWs {
   c128* panel = nullptr;   // kp_max x 64
   c128* tmp = nullptr;     // kp_max x 64 (batched 64 x 64 blocks)
-  c128* U = nullptr;       // kp_max x 64 (one rotation block per Jacobi pair)
+  c128* U = nullptr;       // kp_max x 64 (a rotation block per Jacobi pair, of two rounds)
   c128 *k1 = nullptr, *k2 = nullptr, *k3 = nullptr, *k4 = nullptr;  // kp_max x kp_max each (jacobi_eigh)
   int* flag = nullptr;     // 4 ints: positives, negatives (select_positive), two Cholesky breakdowns
-  int* pflag = nullptr;    // kp_max / 8 ints (Jacobi pair rotated?)
+  int* pflag = nullptr;    // kp_max / 16 ints (Jacobi pair rotated?, of two rounds)
   double* dscalar = nullptr;  // 4 doubles
   void* gemm_ws = nullptr;     // split-K partials of the batched GEMMs (may be null)
   size_t gemm_ws_bytes = 0;

@@ -80,23 +80,6 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// 1 / sqrt(y) and 1 / d for normal positive y and nonzero d: hardware
-// estimates refined by two Newton steps each (r <- r (3 - y r^2) / 2 and
-// q <- q (2 - d q)), which take the estimate to within about an ulp.
-__device__ __forceinline__ double rsqrt_nr(double y) {
-  double r = __builtin_amdgcn_rsq(y);
-  r = r * (1.5 - 0.5 * y * r * r);
-  r = r * (1.5 - 0.5 * y * r * r);
-  return r;
-}
-
-__device__ __forceinline__ double rcp_nr(double d) {
-  double q = __builtin_amdgcn_rcp(d);
-  q = q * (2.0 - d * q);
-  q = q * (2.0 - d * q);
-  return q;
-}
-
 // X = L^{-1} by forward substitution on the 64 unit right-hand sides at
 // once: thread (w, c) holds X[4 t + w][c] in b[t]; step k finishes row k
 // (x_k = b_k / L[k][k]) on wave k mod 4, which publishes it, and every
@@ -464,8 +447,9 @@ __device__ __forceinline__ void next_rotations(c128* lds, const c128* G, int64_t
 // npair (npair + 1) / 2 G blocks; the rest: V blocks.  The data block and the
 // rotation blocks are staged in LDS; each of the four waves computes one
 // 16 x 16 quarter of each 32 x 32 product on MFMA.  Bound by the chain of a
-// round's 16 rotation steps (0.65 us each); kp = 384: 20.9 us a
-// round, with rotations and update in launches of their own 25.5
+// round's rotations; kp = 384: 20.8 us a round, of which the 16 rotation steps take
+// 10.4 (0.65 each), the two products before them 6, and launch, loads and stores
+// the rest.  In launches of their own the rotations take 14.8 and the update 10.0.
 __global__ __launch_bounds__(256) void jacobi_round_kernel(const c128* G, c128* Gn, c128* V, int64_t ld, int kp, int nbj,
                                                            int round, const c128* Uw, const int* pflag, c128* Un,
                                                            int* pflagn, double thr, int nspec) {

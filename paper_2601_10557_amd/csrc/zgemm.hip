@@ -51,8 +51,6 @@ struct ZgemmDev {
   c128* ws;        // split-K partials: a workgroup's outputs per (split, batch, tile)
 };
 
-// Lane l of a fragment of 16 rows (columns) and 8 k holds row l % 16 at k = 2 (l / 16) + s, s = 0, 1: two loads of one c128, 128 contiguous
-// bytes per row where k runs along memory, 256 per k where the rows do.
 __device__ __forceinline__ int xcd_remap(int w, int T) {
   // workgroup w runs on XCD w % 8: give each XCD a contiguous range, so that
   // the tiles of a strip and of a K range stay in one L2
@@ -122,6 +120,10 @@ __device__ __forceinline__ void put4(const ZgemmDev& g, int bt, int64_t gi, int6
 
 // cr + i ci = op(A) S op(B) over k in [kbeg, kend) for the 16 F x 16 F outputs
 // at (m0, n0), a slab of 8 loaded ahead of its use.
+// Lane l of a fragment of 16 rows of A or columns of B and 8 k holds row
+// feed_row(l) of A, column l % 16 of B, at k = 2 (l / 16) + s, s = 0, 1: two loads of
+// one c128, 128 contiguous bytes per row where k runs along memory, 256 per k
+// where the rows do.
 template <bool REAL, int TA, int TBT, int F>
 __device__ __forceinline__ void accumulate(const ZgemmDev& g, int bt, int64_t m0, int64_t n0, int64_t kbeg, int64_t kend,
                                            doublex4 (&cr)[F][F], doublex4 (&ci)[F][F]) {
