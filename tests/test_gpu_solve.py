@@ -251,9 +251,9 @@ def test_solve_clustered_spectrum_to_convergence(prec):
 
 
 def test_solve_on_wide_real_products():
-    # 840 columns of 8000 reals: the orthonormalisation's Gram matrix, its
-    # triangular product and the projection off the locked pairs run on the
-    # widest tiles of the real GEMM, with cut-off tiles (840 = 13 x 64 + 8).
+    # 840 columns of 8000 reals: the orthonormalisation's Gram matrix and its
+    # triangular product run on the widest tiles of the real GEMM, with cut-off
+    # tiles (840 = 13 x 64 + 8).
     # Every returned pair against H V formed by matmul, and eq. 3.5
     m, nev, nex, tol = 4000, 400, 20, 1e-7
     print_case("solve_wide_real", m=m, nev=nev, nex=nex)

@@ -93,8 +93,8 @@ def test_apply_h_fp64_kreal(prob, solver80, k):
     assert np.max(np.abs(Y - Yg)) <= 1e-13 * np.max(np.abs(ref))
 
 
-# every c128 tile shape (0: 128 x 128, 1: 128 x 64, 2: 128 x 32, all on
-# the f64 16x16x4 MFMA)
+# every c128 tile width ("w,parts": tiles of at most 8 >> w fragments of 16
+# columns, about so many parts of K each)
 @pytest.mark.parametrize("plan", ["0,1", "0,3", "1,1", "1,4", "2,1", "2,6"])
 @pytest.mark.parametrize("k", [37, 61])
 def test_apply_h_fp64_every_tile_plan(prob, solver, plan, k, monkeypatch):
@@ -107,9 +107,8 @@ def test_apply_h_fp64_every_tile_plan(prob, solver, plan, k, monkeypatch):
     assert np.max(np.abs(Y - ref)) <= 1e-12 * np.max(np.abs(ref))
 
 
-# K-real columns whose last 128-wide tile ends before the columns of the
-# second wave (1 to 33 of them; the first forced plan is that tile), and the
-# same for the 64-wide tile (1 column past it)
+# K-real columns a few past a multiple of 128 (1 to 33 of them) and of 64: the last
+# tile has few of its columns
 @pytest.mark.parametrize("k,plan", [(129, "0,1"), (130, "0,3"), (161, "0,1"), (129, "1,1"), (129, "1,4")])
 def test_apply_h_fp64_kreal_short_last_tile(prob, solver80, k, plan, monkeypatch):
     print_case("apply_h_fp64_kreal_short_tile", m=prob.m, k=k, plan=plan)
@@ -151,9 +150,9 @@ def test_apply_h_fp32_wide_last_column(prob, solver, k):
     assert np.max(np.abs(Y32 - ref32)) <= 1e-5 * np.max(np.abs(ref32))
 
 
-# the split launch with every main tile shape (the remainder keeps the
+# the c64 split launch with every main tile shape (the remainder keeps the
 # narrow one): one pair kernel per main shape, or two plain launches when
-# the main part is on the narrow shape too
+# the main part is on the narrow shape too; c128 products on the same plans
 @pytest.mark.parametrize("plan", ["0,1", "0,3", "1,2", "2,4"])
 @pytest.mark.parametrize("k", [73, 145])
 def test_apply_h_column_split_every_main_plan(prob, solver, plan, k, monkeypatch):
@@ -454,7 +453,7 @@ def test_rr_near_diagonal_quotient(prob, solver80, kh, eps):
 
 
 # the same further from diagonal, around the limits of the refinement steps
-# (||o_ij / (g_jj - g_ii)||_F of 0.04 and 0.1): the series to E^8, to E^12, sweeps
+# (||o_ij / (g_jj - g_ii)||_F of 0.035 and 0.095): the series to E^8, to E^12, sweeps
 @pytest.mark.parametrize("kh", [6, 32])
 @pytest.mark.parametrize("eps", [3e-2, 6e-2, 0.1, 0.2, 0.4])
 def test_rr_refinement_limits(prob, solver80, kh, eps):
