@@ -66,7 +66,8 @@ __device__ __forceinline__ void lower_tile(int64_t t, int64_t* I, int64_t* J) {
 // loads, so the fragments come straight from V one step ahead (lane l holds
 // row l % 16, eigenpair l / 16) and no wave waits for another.  m = 4000,
 // nev = 200: 800 us (64 TF/s, 512 MB written), 915 on LDS slabs with a barrier
-// every two steps; the stores past the L2 are 12 of the difference.
+// every two steps.
+template <bool NT_STORES>
 __global__ __launch_bounds__(NT, 2) void adjoint_kernel(const c128* __restrict__ V, int64_t ldv, int64_t m, int nev,
                                                         const double* __restrict__ gt, c128* GA, c128* GB,
                                                         int64_t ldg) {
@@ -150,7 +151,10 @@ __global__ __launch_bounds__(NT, 2) void adjoint_kernel(const c128* __restrict__
   // D = 16 x 16 block: lane holds rows (lane >> 4) + 4 r, column lane & 15
   typedef double doublex2 __attribute__((ext_vector_type(2)));
   auto put = [&](c128* p, double re, double im) __attribute__((always_inline)) {
-    __builtin_nontemporal_store(doublex2{re, im}, reinterpret_cast<doublex2*>(p));
+    if constexpr (NT_STORES)
+      __builtin_nontemporal_store(doublex2{re, im}, reinterpret_cast<doublex2*>(p));
+    else
+      *reinterpret_cast<doublex2*>(p) = doublex2{re, im};
   };
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -181,7 +185,15 @@ Err adjoint_contract(const c128* V, int64_t ldv, int64_t m, int nev, const doubl
   const int64_t T = ceil_div(m, TB);
   const int64_t tiles = T * (T + 1) / 2;
   if (tiles > 0x7fffffffLL) return fail(CHASE_PH_ERR_ARG, "eigval_backward: m too large");
-  hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)tiles), dim3(NT), 0, s, V, ldv, m, nev, dgt, GA, GB, ldg);
+  // Stores past the L2 while both outputs are at most 32 MiB and columns start on 64
+  // bytes, the four rows of one store (us, nev = 20, through the L2 / past it: m = 800
+  // 45.0 / 43.3, 1000 46.5 / 44.5, 1400 50.0 / 52.5, 4000 165 / 179, 6000 298 / 351).  Other
+  // columns write parts of lines, which only the L2 merges: m = 1777 61 / 109.
+  const bool past = m <= 1024 && ldg % 4 == 0 && ((uintptr_t)GA | (uintptr_t)GB) % 64 == 0;
+  if (past)
+    hipLaunchKernelGGL(adjoint_kernel<true>, dim3((unsigned)tiles), dim3(NT), 0, s, V, ldv, m, nev, dgt, GA, GB, ldg);
+  else
+    hipLaunchKernelGGL(adjoint_kernel<false>, dim3((unsigned)tiles), dim3(NT), 0, s, V, ldv, m, nev, dgt, GA, GB, ldg);
   CHASE_LAUNCH_CHECK();
   return ok();
 }

@@ -908,3 +908,36 @@ def test_filter_fp64_after_a_product_of_nan(m, k):
     err = np.linalg.norm(to_host(Wd) - ref, axis=0) / np.linalg.norm(ref, axis=0)
     assert np.max(err) < 1e-11, err
     s.close()
+
+
+# both kinds of stores of the adjoint: columns that start on 64 bytes of outputs of up
+# to 32 MiB (m = 64, 1024) and all others, by m, by the leading dimension and by the
+# first element; pads and neighbours stay as they were.  Sums of nev products of
+# unit vectors' entries: 1e-12 of the largest entry
+@pytest.mark.parametrize("m,nev,pad,shift", [(64, 5, 0, 0), (64, 5, 1, 0), (64, 5, 4, 1), (65, 4, 0, 0), (130, 7, 2, 4),
+                                             (1024, 3, 0, 0), (1028, 3, 0, 0)])
+def test_backward_stores(m, nev, pad, shift):
+    import ctypes
+    print_case("backward_stores", m=m, nev=nev, pad=pad, shift=shift)
+    rng = np.random.default_rng(m + nev)
+    V = complex_normal(rng, (2 * m, nev))
+    V[m:] *= 0.3
+    V /= np.linalg.norm(V, axis=0)
+    g = rng.standard_normal(nev)
+    x, y = V[:m], V[m:]
+    gt = g / (np.sum(np.abs(x) ** 2, axis=0) - np.sum(np.abs(y) ** 2, axis=0))
+    refA = (x * gt) @ x.conj().T + (y.conj() * gt) @ y.T
+    refB = (x * gt) @ y.conj().T + (y.conj() * gt) @ x.T
+    ldg = m + pad
+    A, B = (torch.full((ldg * m + shift,), 9.0 + 1.0j, dtype=torch.complex128, device="cuda") for _ in range(2))
+    Vd = to_dev(V)
+    hg = (ctypes.c_double * nev)(*g)
+    st = _lib.load().chase_ph_eigval_backward_noalloc(m, nev, Vd.data_ptr(), 2 * m, hg, A.data_ptr() + 16 * shift,
+                                                      B.data_ptr() + 16 * shift, ldg,
+                                                      torch.cuda.current_stream().cuda_stream)
+    assert st == _lib.OK
+    for out, ref in ((A, refA), (B, refB)):
+        assert bool((out[:shift] == 9.0 + 1.0j).all())
+        cols = out[shift:].reshape(m, ldg).cpu().numpy()  # a row: one column
+        assert np.all(cols[:, m:] == 9.0 + 1.0j)
+        assert np.max(np.abs(cols[:, :m].T - ref)) <= 1e-12 * np.max(np.abs(ref))
