@@ -404,26 +404,93 @@ __device__ __forceinline__ void hx_tile(const ApplyHArgs& a, int splits, int kps
   });
   vm_wait<0>();  // the trailing repeat copies
 
-  R* wsp = ws + (int64_t)sp * M2 * N;
+  // The partial sums in a loop of their own: as one of the branches of every element
+  // of the full epilogue, they were stored from here and there in 100 KB of code
+  // (us a product: m = 1000, k = 80 67 / 53, m = 4000, k = 72 234 / 212, m = 2000, k = 100
+  // 104.6 / 95.8, m = 4000, k = 260 601 / 583).
+  if (splits > 1) {
+    R* wsp = ws + (int64_t)sp * M2 * N;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int col = n0 + wn0 + j * Tr::NB + bcol;
+      R* wc = wsp + (int64_t)col * M2;
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int r = 0; r < Tr::NACC; r += 2) {
+          const int row = m0 + wm0 + i * Tr::MB + Tr::phys_row(r, lane);   // even
+          if (row < M2 && col < N) *reinterpret_cast<C*>(wc + row) = C{acc[i][j][r], acc[i][j][r + 1]};
+        }
+    }
+    return;
+  }
+  // a block's P, Q and S are all loaded before the first is waited for; the lane
+  // number anew, so that no block's addresses are kept through the others
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+    for (int j = 0; j < FN; ++j) {
+      constexpr int H = Tr::NACC / 2;
+      __builtin_amdgcn_sched_barrier(0);
+      int el = lane;
+      __asm__ volatile("" : "+v"(el));
+      const int col = n0 + wn0 + j * Tr::NB + Tr::acc_col(el);
+      const bool odd = !a.tda && (col & 1);
+      const int ocol = a.tda ? col : col >> 1;
+      int64_t orow[H];
+      bool ok[H];
+      R hr[H], hi[H];
 #pragma unroll
-      for (int r = 0; r < Tr::NACC; r += 2) {
-        const int row = m0 + wm0 + i * Tr::MB + Tr::phys_row(r, lane);   // even
-        const int col = n0 + wn0 + j * Tr::NB + bcol;
-        const R tr = acc[i][j][r], ti = acc[i][j][r + 1];
-        if (splits > 1) {
-          if (row < M2 && col < N) {
-            wsp[(int64_t)col * M2 + row] = tr;
-            wsp[(int64_t)col * M2 + row + 1] = ti;
-          }
-        } else {
+      for (int t = 0; t < H; ++t) {
+        const int row = m0 + wm0 + i * Tr::MB + Tr::phys_row(2 * t, el);   // even
+        ok[t] = row < M2 && col < N;
+        orow[t] = (row >> 1) + (odd ? m : 0);
+        const R tr = acc[i][j][2 * t], ti = acc[i][j][2 * t + 1];
+        hr[t] = tr;
+        hi[t] = ti;
+        if (!a.tda) {
           const R pr = shfl1(tr), pi_ = shfl1(ti);
-          if (row < M2 && col < N) finish_pair(a, row >> 1, col, tr, ti, pr, pi_);
+          // t_u + i t_v; -conj(t_u) - i conj(t_v)
+          hr[t] = odd ? -pr - ti : tr - pi_;
+          hi[t] = odd ? pi_ - tr : ti + pr;
         }
       }
+      C p[H], q[H], x[H];
+      R d = 0;
+      if (a.P) {
+#pragma unroll
+        for (int t = 0; t < H; ++t)
+          if (ok[t]) p[t] = a.P[(int64_t)ocol * a.ldp + orow[t]];
+      }
+      if (a.Q) {
+#pragma unroll
+        for (int t = 0; t < H; ++t)
+          if (ok[t]) q[t] = a.Q[(int64_t)ocol * a.ldq + orow[t]];
+      }
+      if (a.S && col < N) {
+        d = a.dcol[ocol];
+#pragma unroll
+        for (int t = 0; t < H; ++t)
+          if (ok[t]) x[t] = a.S[(int64_t)ocol * a.lds + orow[t]];
+      }
+#pragma unroll
+      for (int t = 0; t < H; ++t) {
+        R yr = a.alpha * hr[t], yi = a.alpha * hi[t];
+        if (a.P) {
+          yr += a.beta * p[t].re;
+          yi += a.beta * p[t].im;
+        }
+        if (a.Q) {
+          yr += a.gamma * q[t].re;
+          yi += a.gamma * q[t].im;
+        }
+        if (a.S) {
+          yr += d * x[t].re;
+          yi += d * x[t].im;
+        }
+        if (ok[t]) a.Y[(int64_t)ocol * a.ldy + orow[t]] = C{yr, yi};
+      }
+    }
 }
 
 template <typename Tr, int BM, int BN, int BK, int NST, int WGM, int WGN, int SCHED = 0>
