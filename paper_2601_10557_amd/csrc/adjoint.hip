@@ -185,11 +185,12 @@ Err adjoint_contract(const c128* V, int64_t ldv, int64_t m, int nev, const doubl
   const int64_t T = ceil_div(m, TB);
   const int64_t tiles = T * (T + 1) / 2;
   if (tiles > 0x7fffffffLL) return fail(CHASE_PH_ERR_ARG, "eigval_backward: m too large");
-  // Stores past the L2 while both outputs are at most 32 MiB and columns start on 64
-  // bytes, the four rows of one store (us, nev = 20, through the L2 / past it: m = 800
-  // 45.0 / 43.3, 1000 46.5 / 44.5, 1400 50.0 / 52.5, 4000 165 / 179, 6000 298 / 351).  Other
-  // columns write parts of lines, which only the L2 merges: m = 1777 61 / 109.
-  const bool past = m <= 1024 && ldg % 4 == 0 && ((uintptr_t)GA | (uintptr_t)GB) % 64 == 0;
+  // Stores past the L2 where columns start on 64 bytes, the four rows of one store,
+  // while both outputs are at most 32 MiB or behind enough MFMAs (us, through the L2 /
+  // past it: m = 800, nev = 20 43.6 / 41.4, m = 1000 45.3 / 43.9, 1300 47.5 / 49.0, 4000
+  // 163 / 178, 8000 483 / 585; m = 4000, nev = 100 429 / 433, 200 816 / 804 on the handle).
+  // Other columns write parts of lines, which only the L2 merges: m = 1777 61 / 109.
+  const bool past = (m <= 1024 || nev >= 160) && ldg % 4 == 0 && ((uintptr_t)GA | (uintptr_t)GB) % 64 == 0;
   if (past)
     hipLaunchKernelGGL(adjoint_kernel<true>, dim3((unsigned)tiles), dim3(NT), 0, s, V, ldv, m, nev, dgt, GA, GB, ldg);
   else

@@ -911,11 +911,11 @@ def test_filter_fp64_after_a_product_of_nan(m, k):
 
 
 # both kinds of stores of the adjoint: columns that start on 64 bytes of outputs of up
-# to 32 MiB (m = 64, 1024) and all others, by m, by the leading dimension and by the
-# first element; pads and neighbours stay as they were.  Sums of nev products of
+# to 32 MiB (m = 64, 1024) or of many eigenpairs (160), and all others, by m, by the
+# leading dimension and by the first element; pads and neighbours stay as they were.  Sums of nev products of
 # unit vectors' entries: 1e-12 of the largest entry
 @pytest.mark.parametrize("m,nev,pad,shift", [(64, 5, 0, 0), (64, 5, 1, 0), (64, 5, 4, 1), (65, 4, 0, 0), (130, 7, 2, 4),
-                                             (1024, 3, 0, 0), (1028, 3, 0, 0)])
+                                             (1024, 3, 0, 0), (1028, 3, 0, 0), (1028, 161, 0, 0)])
 def test_backward_stores(m, nev, pad, shift):
     import ctypes
     print_case("backward_stores", m=m, nev=nev, pad=pad, shift=shift)
