@@ -505,10 +505,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // shape and K split, next to the main columns, without a second stream.
 // The remainder workgroups are short and bound by the read of M.  Where the
 // main tiles leave some of the 512 places empty (two a CU) they come after
-// those and fill them (m = 4000, two products, first / last: k = 200 1006 / 967
-// us, k = 330 1544 / 1487; m = 8000, k = 260 4404 / 4349; where few are, 8 of 512,
-// m = 8000, k = 530 8580 / 8450, m = 3000, k = 210 663 / 660); where the main tiles
-// take every place they come first (k = 145 792 / 799, k = 260 1202 / 1201; mixed
+// those and fill them (m = 4000, two products, first / last: k = 200 970 / 934
+// us, k = 330 1493 / 1449; m = 8000, k = 260 4377 / 4325; where few are, 8 of 512,
+// m = 8000, k = 530 8547 / 8425, m = 3000, k = 210 615 / 613); where the main tiles
+// take every place they come first (k = 145 759 / 757, k = 260 1162 / 1162; mixed
 // orders put two main tiles on some CUs and none on others).  The K split leaves
 // the last round of main tiles at least 440 of 512 full or full, at all sizes.  Each part starts
 // at a multiple of 8 (nrem and nmain rounded up, the padding workgroups exit at
